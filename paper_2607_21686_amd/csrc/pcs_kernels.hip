@@ -170,6 +170,7 @@ typedef uint32_t v4u32 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) v4u32 g_v4u32;
 typedef __attribute__((address_space(1))) uint64_t g_u64;
 typedef __attribute__((address_space(1))) uint32_t g_u32;
+typedef __attribute__((address_space(1))) uint16_t g_u16;
 typedef __attribute__((address_space(1))) uint8_t g_u8;
 
 __device__ __forceinline__ uint4 load16(uint64_t a)
@@ -1338,9 +1339,6 @@ __device__ __forceinline__ void load_keys(const SelView &v, uint64_t g0, uint64_
 #pragma unroll
         for (int j = 0; j < 4; ++j) k[u][j] = score_key(x[u][j]);
 }
-// Key of score i, read alone.
-__device__ __forceinline__ uint32_t key_at(uint64_t scores, uint64_t i) { return score_key(((const g_u32 *)scores)[i]); }
-
 // The single scores a selection reads one at a time (before and after the
 // whole groups), one per lane of wavefront 0: lane l < 8 holds score l of
 // [0, e_lo) ++ [e_hi, n).  `raw` is loaded at once; its key is formed later,
@@ -1777,40 +1775,121 @@ __global__ __launch_bounds__(1024) void k_sel_place(uint64_t scores, uint32_t n,
     }
 }
 
-// Moves of a bank shrink, every part in one launch; work item w is slice sl
-// of kept entry j of the part whose items hold w (the part is the same for
-// all lanes of a workgroup).  Kept indices increase, so kept[j] >= j, and in
-// place the entries overwritten are the destinations j < keep.  A source
-// kept[j] < keep (other than j itself) is such a destination, written by
-// another item of the same pass: STAGE copies those sources to the part's
-// staging area (slot j) first.  The place pass then writes destination j
-// from the staging area, or straight from a source kept[j] >= keep, which no
-// destination overwrites, and in place skips kept[j] == j (already there).
-// Out-of-place parts gather straight from the source and do nothing in the
-// stage pass.
-__device__ __forceinline__ void move_granule(uint64_t a, uint64_t d, uint64_t g)
+// Moves of a bank shrink, every part in one launch.  Kept indices increase,
+// so kept[j] >= j, and in place the entries overwritten are the destinations
+// j < keep.  A source kept[j] < keep (other than j itself) is such a
+// destination, written by another item of the same pass: STAGE copies those
+// sources to the part's staging area (slot j) first.  The place pass then
+// writes destination j from the staging area, or straight from a source
+// kept[j] >= keep, which no destination overwrites, and in place skips
+// kept[j] == j (already there).  Out-of-place parts gather straight from the
+// source and do nothing in the stage pass.
+//
+// Bound: HBM, 2 x kept bytes.  Each lane moves kMoveUnroll granules, all
+// their indices loaded before the first granule and all granules before the
+// first store, and short entries are laid end to end: one 256-lane workgroup
+// per entry and one granule per lane left three lanes of four idle on a
+// 1 KiB row, with one load in flight on the fourth: 24,000 rows of 16 such
+// arrays (788 MB moved) 457 us, now 155 us.
+template <int G>
+struct Granule {
+    uint64_t v;
+};
+template <>
+struct Granule<16> {
+    uint4 v;
+};
+template <int G>
+__device__ __forceinline__ Granule<G> load_granule_nt(uint64_t a)
 {
-    if (g == 16) store16_nt(d, load16_nt(a));
-    else if (g == 4) *(g_u32 *)d = *(const g_u32 *)a;
-    else *(g_u8 *)d = *(const g_u8 *)a;
+    Granule<G> r;
+    if constexpr (G == 16) r.v = load16_nt(a);
+    else if constexpr (G == 8) r.v = __builtin_nontemporal_load((const g_u64 *)a);
+    else if constexpr (G == 4) r.v = *(const g_u32 *)a;
+    else if constexpr (G == 2) r.v = *(const g_u16 *)a;
+    else r.v = *(const g_u8 *)a;
+    return r;
 }
-template <bool STAGE>
-__global__ __launch_bounds__(256) void k_move_entries(const ShrinkParts P, const uint32_t *__restrict__ kept,
-                                                      uint64_t keep)
+template <int G>
+__device__ __forceinline__ void store_granule_nt(uint64_t a, const Granule<G> &r)
 {
+    if constexpr (G == 16) store16_nt(a, r.v);
+    else if constexpr (G == 8) __builtin_nontemporal_store(r.v, (g_u64 *)a);
+    else if constexpr (G == 4) *(g_u32 *)a = (uint32_t)r.v;
+    else if constexpr (G == 2) *(g_u16 *)a = (uint16_t)r.v;
+    else *(g_u8 *)a = (uint8_t)r.v;
+}
+
+// One work item: kMoveUnroll granules per lane.  first: the item's number
+// within its part.
+template <bool STAGE, int G>
+__device__ __forceinline__ void move_item(const ShrinkPart &q, uint64_t first, const uint32_t *__restrict__ kept,
+                                          uint64_t keep)
+{
+    const uint64_t gpe = q.eb / G, spe = move_slices(gpe);
+    uint64_t j[kMoveUnroll], x[kMoveUnroll];
+    bool ok[kMoveUnroll];
+    if (spe) {
+        const uint64_t e = first / spe, g0 = (first % spe) * kMoveItem;
+#pragma unroll
+        for (uint32_t u = 0; u < kMoveUnroll; ++u) {
+            j[u] = e;
+            x[u] = g0 + u * kMoveLanes + threadIdx.x;
+            ok[u] = x[u] < gpe;
+        }
+    } else {
+        // The item's first granule belongs to entry e0, at granule r0 of it;
+        // r0 + an offset within the item stays far below 2^32.
+        const uint64_t g0 = first * kMoveItem, e0 = g0 / gpe;
+        const uint32_t r0 = (uint32_t)(g0 - e0 * gpe), per = (uint32_t)gpe;
+#pragma unroll
+        for (uint32_t u = 0; u < kMoveUnroll; ++u) {
+            const uint32_t r = r0 + u * kMoveLanes + threadIdx.x, d = r / per;
+            j[u] = e0 + d;
+            x[u] = r - d * per;
+            ok[u] = j[u] < keep;
+        }
+    }
+    uint64_t e[kMoveUnroll];
+#pragma unroll
+    for (uint32_t u = 0; u < kMoveUnroll; ++u) e[u] = kept[ok[u] ? j[u] : 0];
+    const bool in_place = q.stage != 0;
+    uint64_t a[kMoveUnroll], d[kMoveUnroll];
+#pragma unroll
+    for (uint32_t u = 0; u < kMoveUnroll; ++u) {
+        const bool staged = in_place && e[u] < keep;
+        if (STAGE) ok[u] = ok[u] && staged && e[u] != j[u];
+        else ok[u] = ok[u] && !(in_place && e[u] == j[u]);
+        a[u] = (!STAGE && staged ? q.stage + j[u] * q.eb : q.src + e[u] * q.eb) + x[u] * G;
+        d[u] = (STAGE ? q.stage : q.dst) + j[u] * q.eb + x[u] * G;
+    }
+    Granule<G> v[kMoveUnroll];
+#pragma unroll
+    for (uint32_t u = 0; u < kMoveUnroll; ++u)
+        if (ok[u]) v[u] = load_granule_nt<G>(a[u]);
+#pragma unroll
+    for (uint32_t u = 0; u < kMoveUnroll; ++u)
+        if (ok[u]) store_granule_nt<G>(d[u], v[u]);
+}
+
+template <bool STAGE>
+__global__ __launch_bounds__(kMoveLanes) void k_move_entries(const ShrinkParts P, const uint32_t *__restrict__ kept,
+                                                             uint64_t keep)
+{
+    // The part's index: the last one that begins at or before the item, by
+    // one vector load of every part's begin (parts without items share the
+    // begin of the next part and lose, parts past n never match).
+    const uint64_t begin = P.item_begin[threadIdx.x & (kShrinkParts - 1)];
     for (uint64_t w = blockIdx.x; w < P.items; w += gridDim.x) {
-        uint32_t p = 0;
-        while (p + 1 < P.n && P.p[p + 1].item_begin <= w) ++p;
+        const uint32_t p = (uint32_t)__popcll(__ballot(begin <= w)) - 1;
         const ShrinkPart &q = P.p[p];
-        const uint64_t r = w - q.item_begin, j = r / q.spe, x = ((r % q.spe) * 256 + threadIdx.x) * q.g;
-        if (x >= q.eb) continue;
-        const uint64_t e = kept[j];
-        const bool in_place = q.stage != 0;
-        if (STAGE) {
-            if (in_place && e < keep && e != j) move_granule(q.src + e * q.eb + x, q.stage + j * q.eb + x, q.g);
-        } else if (!(in_place && e == j)) {
-            const uint64_t a = in_place && e < keep ? q.stage + j * q.eb : q.src + e * q.eb;
-            move_granule(a + x, q.dst + j * q.eb + x, q.g);
+        const uint64_t first = w - P.item_begin[p];
+        switch (q.gl) {
+        case 4: move_item<STAGE, 16>(q, first, kept, keep); break;
+        case 3: move_item<STAGE, 8>(q, first, kept, keep); break;
+        case 2: move_item<STAGE, 4>(q, first, kept, keep); break;
+        case 1: move_item<STAGE, 2>(q, first, kept, keep); break;
+        default: move_item<STAGE, 1>(q, first, kept, keep); break;
         }
     }
 }
@@ -2077,8 +2156,8 @@ hipError_t launch_move_entries(const ShrinkParts &parts, const uint32_t *kept, u
     if (parts.n > kShrinkParts) return hipErrorInvalidValue;
     if (parts.items == 0) return hipSuccess;
     const uint32_t grid = (uint32_t)std::min<uint64_t>(parts.items, 1u << 20);
-    if (stage) run_kernel(k_move_entries<true>, dim3(grid), dim3(256), s, parts, kept, keep);
-    else run_kernel(k_move_entries<false>, dim3(grid), dim3(256), s, parts, kept, keep);
+    if (stage) run_kernel(k_move_entries<true>, dim3(grid), dim3(kMoveLanes), s, parts, kept, keep);
+    else run_kernel(k_move_entries<false>, dim3(grid), dim3(kMoveLanes), s, parts, kept, keep);
     return hipGetLastError();
 }
 

@@ -148,20 +148,37 @@ struct LongLists {
 // The entry moves of a bank shrink, every part in one launch.  Part p moves
 // the kept entries of entry_bytes eb from src to dst (stage: in place, the
 // staging area for entries the compaction would overwrite before reading
-// them; 0 out of place) in g-byte granules (16, 4 or 1, what the addresses
-// and eb allow), spe slices of 256 granules per entry; its work items are
-// [item_begin, item_begin + keep * spe).
+// them; 0 out of place) in granules of 1 << gl bytes (16 to 1, what the
+// addresses and eb allow).  Its work items, kMoveItem granules each, are
+// [item_begin[p], item_begin[p + 1]): move_slices() slices of every kept
+// entry, or, for entries of at most kMoveStreamGranules granules, slices of
+// all kept entries laid end to end, so that a slice holds several entries
+// and no lane idles on a short one.
+constexpr uint32_t kMoveLanes = 256, kMoveUnroll = 4;
+constexpr uint32_t kMoveItem = kMoveLanes * kMoveUnroll;
+constexpr uint64_t kMoveStreamGranules = 4 * kMoveItem;
 struct ShrinkPart {
     uint64_t src, dst, stage;
     uint64_t eb;
-    uint64_t item_begin;
-    uint64_t g, spe;
+    uint32_t gl, pad;
 };
+// Slices per entry (0: the part's entries are laid end to end).
+constexpr uint64_t move_slices(uint64_t gpe)
+{
+    return gpe <= kMoveStreamGranules ? 0 : gpe / kMoveItem + (gpe % kMoveItem != 0);
+}
+// Work items of a part that moves `keep` entries of gpe granules.
+constexpr uint64_t move_items(uint64_t keep, uint64_t gpe)
+{
+    const uint64_t spe = move_slices(gpe), all = keep * gpe;
+    return spe ? keep * spe : all / kMoveItem + (all % kMoveItem != 0);
+}
 constexpr uint32_t kShrinkParts = 64;
 struct ShrinkParts {
     uint32_t n;
     uint32_t pad;
     uint64_t items;
+    uint64_t item_begin[kShrinkParts];  // parts past n begin at `items`
     ShrinkPart p[kShrinkParts];
 };
 static_assert(sizeof(ShrinkParts) + 64 <= 4096, "shrink parts must fit in the kernel arguments");

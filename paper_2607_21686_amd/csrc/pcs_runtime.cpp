@@ -1248,12 +1248,13 @@ int pcs_bank_shrink(pcs_ctx *c, const pcs_bank_part *parts, uint32_t nparts, uin
         const auto aligned = [&](uint64_t g) {
             return q.entry_bytes % g == 0 && q.src % g == 0 && q.dst % g == 0 && sp.stage % g == 0;
         };
-        sp.g = aligned(16) ? 16 : aligned(4) ? 4 : 1;
-        sp.spe = (q.entry_bytes / sp.g + 255) / 256;
-        sp.item_begin = P.items;
-        if (moves(q)) P.items += keep * sp.spe;  // else the part has no items
+        sp.gl = 0;
+        while (sp.gl < 4 && aligned(2ULL << sp.gl)) ++sp.gl;
+        P.item_begin[p] = P.items;
+        if (moves(q)) P.items += move_items(keep, q.entry_bytes >> sp.gl);  // else the part has no items
         any_in_place = any_in_place || sp.stage != 0;
     }
+    for (uint32_t p = nparts; p < kShrinkParts; ++p) P.item_begin[p] = P.items;
     for (uint32_t step = 0; step < select_steps((uint32_t)n_entries); ++step)
         if (int st = launch(c, "shrink", [&] {
                 return launch_shrink_select(d_scores, (uint32_t)n_entries, (uint32_t)keep, kept,

@@ -1,0 +1,67 @@
+"""Entry moves of a bank shrink at the edges of their work items: every
+granule size (16 to 1 bytes, what the entry size and the addresses allow),
+entries laid end to end (at most 4096 granules) and cut into slices (more),
+counts on both sides of a 1024-granule item, in place and out of place, parts
+that move nothing between parts that do.  Bytes and indices are compared with
+the CPU oracle exactly."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from tests.gpu_util import arena, dev, host, log
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def pcs():
+    import paper_2607_21686_amd as P
+    return P
+
+
+# entry bytes of the parts, entries, kept
+CASES = [
+    ([1], 5000, 1023), ([1], 5000, 1025), ([2], 3000, 1024), ([28], 513, 146), ([28], 513, 147),
+    ([24], 700, 341), ([24, 3, 1, 16, 2], 700, 342),
+    ([4096 * 16], 9, 4), ([4097 * 16], 9, 4), ([4096], 9, 5), ([4097], 9, 5), ([4098 * 4, 7, 4096 * 8], 12, 7),
+    ([199680, 28], 21, 3), ([16], 40000, 1), ([48, 6], 40000, 39999),
+]
+
+
+@pytest.mark.parametrize("inplace", [False, True])
+@pytest.mark.parametrize("sizes,n,keep", CASES)
+def test_moves_match_oracle(pcs, sizes, n, keep, inplace):
+    rng = np.random.default_rng([n, keep, len(sizes)])
+    parts = [rng.integers(0, 256, n * eb, dtype=np.uint8) for eb in sizes]
+    scores = rng.standard_normal(n).astype(np.float32)
+    want_kept, want = oracle.bank_shrink(list(zip(parts, sizes)), scores, keep)
+    log("moves", sizes, n, keep, "in place" if inplace else "out of place")
+    ctx = pcs.Context(arena(64 << 20))
+    srcs = [dev(p) for p in parts]
+    dsts = [None if inplace else torch.zeros(keep * eb, dtype=torch.uint8, device="cuda") for eb in sizes]
+    kept = torch.zeros(keep, dtype=torch.int32, device="cuda")
+    ctx.bank_shrink([(a, d, eb) for a, d, eb in zip(srcs, dsts, sizes)], torch.from_numpy(scores).cuda(), keep, kept)
+    assert np.array_equal(host(kept).view(np.uint32), want_kept)
+    for a, d, eb, w in zip(srcs, dsts, sizes, want):
+        got = host(a if d is None else d)[:keep * eb]
+        assert np.array_equal(got, np.asarray(w).reshape(-1)[:keep * eb])
+    ctx.close()
+
+
+@pytest.mark.parametrize("offset,eb", [(8, 24), (4, 24), (2, 24), (1, 24), (16, 1000)])
+def test_moves_follow_the_source_alignment(pcs, offset, eb):
+    """The granule is what the source address allows too."""
+    n, keep = 900, 333
+    rng = np.random.default_rng([offset, eb])
+    bank = rng.integers(0, 256, n * eb, dtype=np.uint8)
+    scores = rng.standard_normal(n).astype(np.float32)
+    _, (want,) = oracle.bank_shrink([(bank, eb)], scores, keep)
+    ctx = pcs.Context(arena(8 << 20))
+    whole = torch.zeros(n * eb + offset, dtype=torch.uint8, device="cuda")
+    src = whole[offset:]
+    src.copy_(dev(bank))
+    dst = torch.zeros(keep * eb, dtype=torch.uint8, device="cuda")
+    ctx.bank_shrink([(src, dst, eb)], torch.from_numpy(scores).cuda(), keep)
+    assert np.array_equal(host(dst), np.asarray(want).reshape(-1)[:keep * eb])
+    ctx.close()
