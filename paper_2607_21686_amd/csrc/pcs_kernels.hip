@@ -1470,9 +1470,9 @@ __device__ __forceinline__ void place_group(const uint32_t (&k)[4], bool ok, uin
 //   3. Each wavefront compacts its kept indices with ballots.
 // Larger banks take the multi-workgroup selection (k_sel_*), which follows
 // the same steps with a launch per pass.
-// Up to here one workgroup is faster (26 us at 16384 scores, 45 us at 32768)
-// than the twelve launches of the multi-workgroup selection (55 us at 16385
-// to 65536, 69 us at 2^20, 1.7 ms at 2^28 where one workgroup took 330 ms).
+// Up to here one workgroup is as fast (23 us at 16384 scores, 38-41 us at
+// 32768) as the five launches of the multi-workgroup selection (40 us at
+// 32769 to 131072, 70 us at 2^20, 0.14 ms at 2^24, 1.3 ms at 2^28).
 constexpr uint32_t kSelectOneWorkgroupEntries = 32768;
 __global__ __launch_bounds__(1024) void k_shrink_select(uint64_t scores, uint32_t n, uint32_t keep,
                                                         uint32_t *__restrict__ kept)
@@ -1594,18 +1594,32 @@ __global__ __launch_bounds__(1024) void k_shrink_select(uint64_t scores, uint32_
 }
 
 // ---- multi-workgroup selection (banks of more than kSelectOneWorkgroupEntries
-// scores).  The same steps as k_shrink_select, a launch each: k_sel_init,
-// then per radix pass k_sel_hist (every workgroup adds its LDS histogram
-// into the pass's device histogram) and k_sel_pick (one wavefront narrows the
-// prefix), then k_sel_count (keys below / equal to K* per wavefront range),
-// k_sel_scan (where each range's kept indices go) and k_sel_place.  The
-// whole groups are cut into one range of a multiple of 64 groups per
+// scores), five launches: three histogram passes over the next 8, 12 and 12
+// bits, k_sel_count and k_sel_place.  In each of the first four, the last
+// workgroup to finish does what needs every workgroup's part: it finds the
+// pass's bucket (the prefix of K* grows), or turns the ranges' counts into
+// the places of their kept indices.  Bound: launches and the round trips to
+// memory within each (the scores' own reads are under 1 us of 40 us at 48,000
+// scores).  A launch per step (init, four 8-bit passes with a pick each,
+// count, scan, place: twelve) took 64 us there, 350 us at 2^24 (now 141 us:
+// five streams over the scores, at most 512 workgroups) and 1.7 ms at 2^28.
+//
+// The whole groups are cut into one range of a multiple of 64 groups per
 // wavefront of the grid, read with 8 groups per lane in flight; range 0 and
 // range R - 1 are the single scores, held by wavefront 0 of workgroup 0.
+// The first pass counts into a histogram the caller keeps at zero (it and
+// the tickets lie in the arena's first unit): its last workgroup clears it
+// again, and clears the other passes' histogram, which lies in scratch.
+constexpr uint32_t kSelBuckets = 4096;
 struct SelState {
-    uint32_t prefix, pmask, need, pad;
-    uint32_t hist[2][256];  // pass p adds into hist[p % 2]; pick p clears the other
+    uint32_t prefix, need, pad[2];
+    uint32_t hist[kSelBuckets];  // passes 1 and 2
 };
+struct SelUnit {
+    uint32_t ticket[kSelectTickets];
+    uint32_t hist[kSelectFirstBuckets];
+};
+static_assert(sizeof(SelUnit) == kUnitSelectBytes, "selection words of the first unit");
 constexpr int kSelU = 8;
 __device__ __forceinline__ void sel_wave_range(const SelView &v, uint64_t gw, uint64_t nwaves, uint64_t &w0,
                                                uint64_t &w1)
@@ -1616,23 +1630,71 @@ __device__ __forceinline__ void sel_wave_range(const SelView &v, uint64_t gw, ui
     w1 = v.gf0 + umin(gw * per + per, nfull);
 }
 
-__global__ __launch_bounds__(256) void k_sel_init(SelState *__restrict__ st, uint32_t keep)
+// Values that pass between workgroups of one launch: stored and loaded at
+// agent scope, since the eight XCDs' L2 caches are not coherent with one
+// another.
+template <class V>
+__device__ __forceinline__ void agent_store(V *p, V v)
 {
-    if (threadIdx.x == 0) {
-        st->prefix = 0;
-        st->pmask = 0;
-        st->need = keep;
-    }
-    st->hist[0][threadIdx.x] = 0;
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class V>
+__device__ __forceinline__ V agent_load(const V *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__global__ __launch_bounds__(1024) void k_sel_hist(uint64_t scores, uint32_t n, SelState *__restrict__ st, int p)
+// True in every thread of the last workgroup of the launch to get here (of
+// `of` that do); the ticket is then back at zero.  What the workgroups pass
+// to the last one goes through agent_store or agent-scope atomics: each
+// wavefront waits until its own have reached memory, and thread 0 then takes
+// the ticket, with release and acquire, for the workgroup.  (A __threadfence
+// in every thread does the same and writes the L2 cache back once per
+// wavefront: the selection of 2^20 scores took 309 us with it, 70 us now.)
+__device__ __forceinline__ bool last_workgroup(uint32_t *ticket, uint32_t of, uint32_t *flag)
 {
-    __shared__ uint32_t hist[256];
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t n = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1;
+        *flag = n == of;
+        if (n == of) agent_store(ticket, 0u);
+    }
+    __syncthreads();
+    return *flag != 0;
+}
+
+// Exclusive prefix of x over the 1024 threads of a workgroup (ws: 33 words).
+__device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t *ws)
+{
+    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const uint32_t incl = wave_incl_scan(x);
+    if (lane == 63) ws[wave] = incl;
+    __syncthreads();
+    if (wave == 0) {
+        const uint32_t w = lane < 16 ? ws[lane] : 0;
+        const uint32_t wi = wave_incl_scan(w);
+        if (lane < 16) ws[16 + lane] = wi - w;
+    }
+    __syncthreads();
+    return incl - x + ws[16 + wave];
+}
+
+// Pass P narrows K* by its bits [kShift, kShift + log2(kBuckets)).
+template <int P>
+__global__ __launch_bounds__(1024) void k_sel_hist(uint64_t scores, uint32_t n, uint32_t keep,
+                                                   SelState *__restrict__ st, SelUnit *__restrict__ unit)
+{
+    constexpr uint32_t kBuckets = P == 0 ? kSelectFirstBuckets : kSelBuckets;
+    constexpr uint32_t kShift = P == 0 ? 24 : P == 1 ? 12 : 0;
+    constexpr uint32_t kAbove = P == 0 ? 0 : P == 1 ? 0xFF000000u : 0xFFFFF000u;  // bits already known
+    __shared__ uint32_t hist[kBuckets];
+    __shared__ uint32_t ws[33];
+    __shared__ uint32_t flag;
     const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const SelView v = sel_view(scores, n);
-    const uint32_t shift = 24 - 8 * p, prefix = st->prefix, pmask = st->pmask;
-    if (t < 256) hist[t] = 0;
+    const uint32_t prefix = P == 0 ? 0 : st->prefix, need = P == 0 ? keep : st->need;
+    for (uint32_t b = t; b < kBuckets; b += 1024) hist[b] = 0;
     __syncthreads();
     uint64_t w0, w1;
     sel_wave_range(v, (uint64_t)blockIdx.x * 16 + wave, (uint64_t)gridDim.x * 16, w0, w1);
@@ -1644,37 +1706,61 @@ __global__ __launch_bounds__(1024) void k_sel_hist(uint64_t scores, uint32_t n, 
         for (int u = 0; u < kSelU; ++u)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                hist_add<true>(hist, (k[u][j] >> shift) & 255u, ok[u] && (k[u][j] & pmask) == prefix);
+                hist_add<true>(hist, (k[u][j] >> kShift) & (kBuckets - 1), ok[u] && (k[u][j] & kAbove) == prefix);
     }
     if (blockIdx.x == 0 && wave == 0) {
         const SelSingle es = sel_single(v, scores, n, lane, true);
         const uint32_t ek = score_key(es.raw);
-        hist_add<true>(hist, (ek >> shift) & 255u, es.in && (ek & pmask) == prefix);
+        hist_add<true>(hist, (ek >> kShift) & (kBuckets - 1), es.in && (ek & kAbove) == prefix);
     }
     __syncthreads();
-    if (t < 256 && hist[t]) atomicAdd(&st->hist[p & 1][t], hist[t]);
-}
-
-__global__ __launch_bounds__(64) void k_sel_pick(SelState *__restrict__ st, int p)
-{
-    const uint32_t lane = threadIdx.x, shift = 24 - 8 * p;
-    uint32_t bucket, rest;
-    if (pick_bucket(st->hist[p & 1], st->need, lane, bucket, rest)) {
-        st->prefix |= bucket << shift;
-        st->pmask |= 255u << shift;
-        st->need = rest;
-    }
+    uint32_t *global = P == 0 ? unit->hist : st->hist;
+    for (uint32_t b = t; b < kBuckets; b += 1024)
+        if (hist[b]) atomicAdd(&global[b], hist[b]);
+    if (!last_workgroup(&unit->ticket[P], gridDim.x, &flag)) return;
+    // The bucket in which the running count first reaches `need`.
+    constexpr uint32_t kPer = (kBuckets + 1023) / 1024;
+    uint32_t h[kPer], sum = 0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) st->hist[(p + 1) & 1][4 * lane + i] = 0;
+    for (uint32_t i = 0; i < kPer; ++i) {
+        h[i] = t * kPer + i < kBuckets ? agent_load(&global[t * kPer + i]) : 0;
+        sum += h[i];
+    }
+    uint32_t cum = block_excl_scan(sum, ws);
+    if (cum < need && cum + sum >= need) {
+        uint32_t i = 0;
+#pragma unroll
+        for (uint32_t k = 0; k + 1 < kPer; ++k)
+            if (i == k && cum + h[k] < need) {
+                cum += h[k];
+                i = k + 1;
+            }
+        st->prefix = prefix | (t * kPer + i) << kShift;
+        st->need = need - cum;
+    }
+    // Each thread clears what it read, for the next pass or call.
+    if (P != 2)
+        for (uint32_t i = 0; i < kPer; ++i)
+            if (t * kPer + i < kBuckets) global[t * kPer + i] = 0;
+    if (P == 0)
+        for (uint32_t b = t; b < kSelBuckets; b += 1024) st->hist[b] = 0;
 }
 
-// Range r's keys below K* (lt[r]) and equal to K* (eq[r]).
+// Range r's keys below K* (lt[r]) and equal to K* (eq[r]); then, in the last
+// workgroup, where each range starts: the kept entries before it (pos) are
+// the keys below K* before it plus the first `need` K* keys, so pos =
+// LT + min(need, EQ) and rank = EQ for the exclusive prefix sums LT and EQ of
+// the counts.
 __global__ __launch_bounds__(1024) void k_sel_count(uint64_t scores, uint32_t n, const SelState *__restrict__ st,
-                                                    uint32_t *__restrict__ lt_out, uint32_t *__restrict__ eq_out)
+                                                    SelUnit *__restrict__ unit, uint32_t *__restrict__ lt_out,
+                                                    uint32_t *__restrict__ eq_out, uint32_t *__restrict__ pos_out,
+                                                    uint32_t *__restrict__ rank_out)
 {
+    __shared__ uint32_t ws[33];
+    __shared__ uint32_t flag;
     const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const SelView v = sel_view(scores, n);
-    const uint32_t prefix = st->prefix;
+    const uint32_t prefix = st->prefix, need = st->need;
     const uint64_t gw = (uint64_t)blockIdx.x * 16 + wave, nwaves = (uint64_t)gridDim.x * 16;
     uint64_t w0, w1;
     sel_wave_range(v, gw, nwaves, w0, w1);
@@ -1692,60 +1778,35 @@ __global__ __launch_bounds__(1024) void k_sel_count(uint64_t scores, uint32_t n,
             }
     }
     if (lane == 0) {
-        lt_out[1 + gw] = lt;
-        eq_out[1 + gw] = eq;
+        agent_store(&lt_out[1 + gw], lt);
+        agent_store(&eq_out[1 + gw], eq);
     }
     if (blockIdx.x == 0 && wave == 0) {
         const SelSingle es = sel_single(v, scores, n, lane, true);
         uint32_t c[4];
         count_singles(es, score_key(es.raw), prefix, c);
         if (lane == 0) {
-            lt_out[0] = c[0];
-            eq_out[0] = c[1];
-            lt_out[nwaves + 1] = c[2];
-            eq_out[nwaves + 1] = c[3];
+            agent_store(&lt_out[0], c[0]);
+            agent_store(&eq_out[0], c[1]);
+            agent_store(&lt_out[nwaves + 1], c[2]);
+            agent_store(&eq_out[nwaves + 1], c[3]);
         }
     }
-}
-
-// Where each of the R ranges starts: the kept entries before it (pos) are
-// the keys below K* before it plus the first `need` K* keys, so pos =
-// LT + min(need, EQ) and rank = EQ for the exclusive prefix sums LT and EQ of
-// the counts.  One workgroup; every thread scans a contiguous segment.
-__global__ __launch_bounds__(1024) void k_sel_scan(const SelState *__restrict__ st, const uint32_t *__restrict__ lt,
-                                                   const uint32_t *__restrict__ eq, uint32_t R,
-                                                   uint32_t *__restrict__ pos_out, uint32_t *__restrict__ rank_out)
-{
-    __shared__ uint32_t wsum[2][33];
-    const uint32_t t = threadIdx.x, wave = t >> 6, lane = t & 63;
-    const uint32_t per = (R + 1023) / 1024, s0 = min(t * per, R), s1 = min(s0 + per, R);
+    if (!last_workgroup(&unit->ticket[3], gridDim.x, &flag)) return;
+    const uint32_t R = (uint32_t)nwaves + 2, per = (R + 1023) / 1024, s0 = min(t * per, R), s1 = min(s0 + per, R);
     uint32_t a = 0, b = 0;
     for (uint32_t r = s0; r < s1; ++r) {
-        a += lt[r];
-        b += eq[r];
+        a += agent_load(&lt_out[r]);
+        b += agent_load(&eq_out[r]);
     }
-    const uint32_t ia = wave_incl_scan(a), ib = wave_incl_scan(b);
-    if (lane == 63) {
-        wsum[0][wave] = ia;
-        wsum[1][wave] = ib;
-    }
+    uint32_t LT = block_excl_scan(a, ws);
     __syncthreads();
-    if (wave == 0) {
-        const uint32_t x = lane < 16 ? wsum[0][lane] : 0, y = lane < 16 ? wsum[1][lane] : 0;
-        const uint32_t xi = wave_incl_scan(x), yi = wave_incl_scan(y);
-        if (lane < 16) {
-            wsum[0][16 + lane] = xi - x;
-            wsum[1][16 + lane] = yi - y;
-        }
-    }
-    __syncthreads();
-    const uint32_t need = st->need;
-    uint32_t LT = ia - a + wsum[0][16 + wave], EQ = ib - b + wsum[1][16 + wave];
+    uint32_t EQ = block_excl_scan(b, ws);
     for (uint32_t r = s0; r < s1; ++r) {
         pos_out[r] = LT + min(need, EQ);
         rank_out[r] = EQ;
-        LT += lt[r];
-        EQ += eq[r];
+        LT += agent_load(&lt_out[r]);
+        EQ += agent_load(&eq_out[r]);
     }
 }
 
@@ -1892,6 +1953,12 @@ __global__ __launch_bounds__(kMoveLanes) void k_move_entries(const ShrinkParts P
         default: move_item<STAGE, 1>(q, first, kept, keep); break;
         }
     }
+}
+
+// Clears n words (the arena's first unit, when its context is created).
+__global__ __launch_bounds__(256) void k_clear(uint64_t addr, uint32_t n)
+{
+    for (uint32_t i = threadIdx.x; i < n; i += 256) ((g_u32 *)addr)[i] = 0;
 }
 
 // Flips the lowest bit of one byte (the control of the discovery procedure
@@ -2101,12 +2168,15 @@ hipError_t launch_merkle_scan_place(const ArgLists &lists, const uint64_t *nodes
 
 // Scratch of a multi-workgroup selection: SelState, then lt, eq, pos and
 // rank arrays of R = 16 x workgroups + 2 ranges.
-constexpr uint32_t kSelBlocks = 2048;
-static uint32_t select_blocks(uint32_t n) { return std::max<uint32_t>(1, std::min<uint32_t>((n + 4095) / 4096, kSelBlocks)); }
+constexpr uint32_t kSelBlocks = 512;
+static uint32_t select_blocks(uint32_t n)
+{
+    return std::max<uint32_t>(1, std::min<uint32_t>(n / 4096 + (n % 4096 != 0), kSelBlocks));
+}
 static uint64_t sel_array_bytes(uint32_t R) { return ((uint64_t)R * 4 + 255) / 256 * 256; }
 static uint64_t sel_state_bytes() { return (sizeof(SelState) + 255) / 256 * 256; }
 
-uint32_t select_steps(uint32_t n) { return n > kSelectOneWorkgroupEntries ? 12 : 1; }
+uint32_t select_steps(uint32_t n) { return n > kSelectOneWorkgroupEntries ? 5 : 1; }
 
 uint64_t select_scratch_bytes(uint32_t n)
 {
@@ -2115,7 +2185,7 @@ uint64_t select_scratch_bytes(uint32_t n)
 }
 
 hipError_t launch_shrink_select(const float *scores, uint32_t n, uint32_t keep, uint32_t *kept, uint64_t scratch,
-                                uint32_t step, hipStream_t s)
+                                uint64_t unit, uint32_t step, hipStream_t s)
 {
     if (n == 0 || keep == 0) return hipSuccess;
     if (keep > n || step >= select_steps(n)) return hipErrorInvalidValue;
@@ -2125,25 +2195,20 @@ hipError_t launch_shrink_select(const float *scores, uint32_t n, uint32_t keep, 
         run_kernel(k_shrink_select, dim3(1), dim3(1024), s, sc, n, keep, kept);
         return hipGetLastError();
     }
-    if (!scratch || (scratch & 255)) return hipErrorInvalidValue;
+    if (!scratch || (scratch & 255) || !unit) return hipErrorInvalidValue;
     const uint32_t B = select_blocks(n), R = B * 16 + 2;
     SelState *st = (SelState *)scratch;
+    SelUnit *su = (SelUnit *)unit;
     uint32_t *lt = (uint32_t *)(scratch + sel_state_bytes());
     uint32_t *eq = (uint32_t *)((uint64_t)lt + sel_array_bytes(R));
     uint32_t *pos = (uint32_t *)((uint64_t)eq + sel_array_bytes(R));
     uint32_t *rank = (uint32_t *)((uint64_t)pos + sel_array_bytes(R));
-    if (step == 0) {
-        run_kernel(k_sel_init, dim3(1), dim3(256), s, st, keep);
-    } else if (step <= 8) {
-        const int p = (int)(step - 1) / 2;
-        if (step % 2) run_kernel(k_sel_hist, dim3(B), dim3(1024), s, sc, n, st, p);
-        else run_kernel(k_sel_pick, dim3(1), dim3(64), s, st, p);
-    } else if (step == 9) {
-        run_kernel(k_sel_count, dim3(B), dim3(1024), s, sc, n, (const SelState *)st, lt, eq);
-    } else if (step == 10) {
-        run_kernel(k_sel_scan, dim3(1), dim3(1024), s, (const SelState *)st, (const uint32_t *)lt,
-                   (const uint32_t *)eq, R, pos, rank);
-    } else {
+    switch (step) {
+    case 0: run_kernel(k_sel_hist<0>, dim3(B), dim3(1024), s, sc, n, keep, st, su); break;
+    case 1: run_kernel(k_sel_hist<1>, dim3(B), dim3(1024), s, sc, n, keep, st, su); break;
+    case 2: run_kernel(k_sel_hist<2>, dim3(B), dim3(1024), s, sc, n, keep, st, su); break;
+    case 3: run_kernel(k_sel_count, dim3(B), dim3(1024), s, sc, n, (const SelState *)st, su, lt, eq, pos, rank); break;
+    default:
         run_kernel(k_sel_place, dim3(B), dim3(1024), s, sc, n, (const SelState *)st, (const uint32_t *)pos,
                    (const uint32_t *)rank, kept);
     }
@@ -2158,6 +2223,12 @@ hipError_t launch_move_entries(const ShrinkParts &parts, const uint32_t *kept, u
     const uint32_t grid = (uint32_t)std::min<uint64_t>(parts.items, 1u << 20);
     if (stage) run_kernel(k_move_entries<true>, dim3(grid), dim3(kMoveLanes), s, parts, kept, keep);
     else run_kernel(k_move_entries<false>, dim3(grid), dim3(kMoveLanes), s, parts, kept, keep);
+    return hipGetLastError();
+}
+
+hipError_t launch_clear(uint64_t addr, uint32_t bytes, hipStream_t s)
+{
+    run_kernel(k_clear, dim3(1), dim3(256), s, addr, bytes / 4);
     return hipGetLastError();
 }
 

@@ -145,6 +145,15 @@ struct LongLists {
     uint64_t block_begin[kLongLists + 1];
 };
 
+// Words of the arena's first unit, which the library keeps (byte offsets).
+// Bump: two bump words of incremental slot placement and a call's payload
+// top.  Select: tickets and the first histogram of a large bank's selection,
+// zero between calls (the launch that uses them clears them again).
+constexpr uint64_t kUnitBump = 0;
+constexpr uint64_t kUnitSelect = 64;
+constexpr uint32_t kSelectTickets = 4, kSelectFirstBuckets = 256;
+constexpr uint64_t kUnitSelectBytes = 4 * (kSelectTickets + kSelectFirstBuckets);
+
 // The entry moves of a bank shrink, every part in one launch.  Part p moves
 // the kept entries of entry_bytes eb from src to dst (stage: in place, the
 // staging area for entries the compaction would overwrite before reading

@@ -95,11 +95,11 @@ struct pcs_ctx {
     std::shared_ptr<pcs::Segment> seg;       // the open segment, if any
     hipEvent_t exact_ev = nullptr;           // an exact-size incremental call waits on it
 
-    // The arena's first unit, kept by the library: words 0 and 2 are the bump
-    // words of incremental slot placement (a call reads word bump_par and
-    // writes the other, which the next call reads), word 1 a call's payload
-    // top.
-    uint64_t bump_dev = 0, top_dev = 0;
+    // The arena's first unit, kept by the library (kUnit*).  At bump_dev,
+    // words 0 and 2 are the bump words of incremental slot placement (a call
+    // reads word bump_par and writes the other, which the next call reads),
+    // word 1 a call's payload top.
+    uint64_t unit_dev = 0, bump_dev = 0, top_dev = 0;
     uint32_t bump_par = 0;
 
     pcs::TileDevice dev{0, 0};  // CU count and real-time counter rate of the arena's device (0: unknown)
@@ -898,7 +898,8 @@ int pcs_ctx_create(void *d_arena, uint64_t arena_bytes, void *hip_stream, pcs_ct
         pcs_ctx_destroy(c);
         return PCS_E_INVAL;
     }
-    c->bump_dev = c->arena_dev + own;
+    c->unit_dev = c->arena_dev + own;
+    c->bump_dev = c->unit_dev + kUnitBump;
     c->top_dev = c->bump_dev + 8;
     {
         hipPointerAttribute_t at;
@@ -908,6 +909,11 @@ int pcs_ctx_create(void *d_arena, uint64_t arena_bytes, void *hip_stream, pcs_ct
             hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, at.device) == hipSuccess && cus > 0 &&
             khz > 0)
             c->dev = TileDevice{(uint32_t)cus, (uint32_t)khz};
+    }
+    // Tickets and counters in the unit start at zero and are left at zero.
+    if (launch_clear(c->unit_dev, (uint32_t)kAlign, c->stream) != hipSuccess) {
+        pcs_ctx_destroy(c);
+        return PCS_E_HIP;
     }
     if (hipHostMalloc(&c->na_host, kNoAllocStagingBytes, hipHostMallocDefault) != hipSuccess ||
         hipEventCreateWithFlags(&c->na_ev, hipEventDisableTiming) != hipSuccess ||
@@ -1258,7 +1264,8 @@ int pcs_bank_shrink(pcs_ctx *c, const pcs_bank_part *parts, uint32_t nparts, uin
     for (uint32_t step = 0; step < select_steps((uint32_t)n_entries); ++step)
         if (int st = launch(c, "shrink", [&] {
                 return launch_shrink_select(d_scores, (uint32_t)n_entries, (uint32_t)keep, kept,
-                                            sel_bytes ? base + o_sel : 0, step, c->stream);
+                                            sel_bytes ? base + o_sel : 0, c->unit_dev + kUnitSelect, step,
+                                            c->stream);
             }))
             return st;
     if (P.items == 0) return PCS_OK;  // no part moves (none given, or in place keeping every entry)

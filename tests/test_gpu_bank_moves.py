@@ -2,7 +2,8 @@
 granule size (16 to 1 bytes, what the entry size and the addresses allow),
 entries laid end to end (at most 4096 granules) and cut into slices (more),
 counts on both sides of a 1024-granule item, in place and out of place, parts
-that move nothing between parts that do.  Bytes and indices are compared with
+that move nothing between parts that do; and the multi-workgroup selection
+where its buckets and ties are uneven.  Bytes and indices are compared with
 the CPU oracle exactly."""
 import numpy as np
 import pytest
@@ -64,4 +65,25 @@ def test_moves_follow_the_source_alignment(pcs, offset, eb):
     dst = torch.zeros(keep * eb, dtype=torch.uint8, device="cuda")
     ctx.bank_shrink([(src, dst, eb)], torch.from_numpy(scores).cuda(), keep)
     assert np.array_equal(host(dst), np.asarray(want).reshape(-1)[:keep * eb])
+    ctx.close()
+
+
+@pytest.mark.parametrize("kind", ["ties", "one bucket", "last bit", "both signs", "extremes"])
+@pytest.mark.parametrize("n", [32769, 100003])
+def test_large_selection_buckets(pcs, n, kind):
+    """Five calls in a row on one context (the selection's words must come
+    back to zero), keeping one, some, all but one and all entries."""
+    rng = np.random.default_rng([n, len(kind)])
+    s = {"ties": lambda: np.zeros(n, np.float32),
+         "one bucket": lambda: (1.0 + rng.integers(0, 4096, n) * 2.0 ** -23).astype(np.float32),
+         "last bit": lambda: rng.integers(0, 2, n).astype(np.uint32).view(np.float32),
+         "both signs": lambda: rng.standard_normal(n).astype(np.float32),
+         "extremes": lambda: rng.choice(np.array([np.nan, np.inf, -np.inf, -0.0, 0.0, 3e38], np.float32), n)}[kind]()
+    ctx = pcs.Context(arena(8 << 20))
+    sd = torch.from_numpy(s).cuda()
+    for keep in (1, 7, n // 3, n - 1, n):
+        want, _ = oracle.bank_shrink([], s, keep)
+        kept = torch.zeros(keep, dtype=torch.int32, device="cuda")
+        ctx.bank_shrink([], sd, keep, kept)
+        assert np.array_equal(host(kept).view(np.uint32), want), (kind, keep)
     ctx.close()
