@@ -27,17 +27,20 @@ bool take_kernel_events_used();
 
 // Kernel launchers (pcs_kernels.hip).  All are asynchronous on `s`.
 enum TileMode : int {
-    kModeHash = 0,    // fingerprint the buffer's runs
+    kModeHash = 0,    // fingerprint the buffer
     kModePack = 1,    // ... and store every chunk to its snapshot slot (checkpoint)
     kModeDiff = 2,    // ... and mark chunks new or changed against the parent (incremental):
                       // bit c of the group's 64-bit mask (an 8-chunk sub-tile writes its
                       // byte of it)
-    kModeVerify = 3,  // copy snapshot slots to the buffer's runs (restore), fingerprint
+    kModeVerify = 3,  // copy snapshot slots to the buffer (restore), fingerprint
                       // the restored bytes and mark chunks whose fingerprint differs
                       // from the one stored at checkpoint time
 };
-hipError_t launch_group_map(const JobBuf *bufs, const Run *runs, uint32_t nbuf, uint64_t ngroups, GroupRef *map,
-                            hipStream_t s);
+// Stages a job's tables: `bytes` (a multiple of 16) from mapped host memory to
+// device memory, and each group's buffer to `map` (host_bufs: the job's
+// buffers on the host side).
+hipError_t launch_stage(uint64_t host, uint64_t dev, uint64_t bytes, const JobBuf *host_bufs, uint32_t nbuf,
+                        uint32_t *map, hipStream_t s);
 // The device a tile launch runs on: its CU count and the rate of its constant
 // real-time counter (kHz); zeros: unknown.
 struct TileDevice {
@@ -98,20 +101,28 @@ hipError_t launch_classify(const Tab &tab, uint64_t ngroups, const uint64_t *has
 template <class Tab>
 hipError_t launch_labels(const Tab &tab, const uint64_t *bitmap, uint8_t *labels, hipStream_t s);
 // Classification and labels of a small job (tables in the kernel arguments,
-// at most kClassifyFusedGroups groups) in one single-workgroup launch.
-constexpr uint64_t kClassifyFusedGroups = 1024;
+// at most kClassifyFusedGroups groups) in one single-workgroup launch: one CU
+// reads every replay's fingerprints (128 groups, three replays: 8.3 us, about
+// what the two launches of a larger job take; 620 groups: 38 against 8 us).
+constexpr uint64_t kClassifyFusedGroups = 128;
 hipError_t launch_classify_small(const ArgTables &tab, uint64_t ngroups, const uint64_t *hashes, uint32_t K,
                                  uint64_t total, uint64_t *bitmap, uint8_t *labels, hipStream_t s);
-// Per-list Merkle reductions (one workgroup per list, or one for all the
-// lists of a small job).  pre: every buffer list of more than
+// Per-list Merkle reductions of a job with device tables, one workgroup per
+// list.  pre: every buffer list of more than
 // kMerkleLdsValues values had its first level reduced by
 // launch_merkle_blocks (into scratch_a at the list's offset).
 hipError_t launch_merkle(const MerkleList *lists, uint32_t nlists, const uint64_t *in,
                          uint64_t *scratch_a, uint64_t *scratch_b, uint64_t *roots_out,
                          uint64_t max_count, bool pre, hipStream_t s);
-hipError_t launch_merkle_small(const ArgLists &lists, const uint64_t *in, uint64_t *scratch_a,
-                               uint64_t *scratch_b, bool pre, hipStream_t s);
 hipError_t launch_merkle_blocks(const LongLists &lists, const uint64_t *in, uint64_t *scratch_a, hipStream_t s);
+// Every root of a job in the argument tables (`tiles` nodes per group, `nodes`
+// of them in `in`) in one workgroup; a job of more than kMerkleArgValues
+// nodes has its lists' first level reduced by every CU first.  Two calls:
+// first = true launches that level into scratch (nothing for a smaller job),
+// first = false the rest.
+constexpr uint64_t kMerkleArgValues = 16384;
+hipError_t launch_merkle_args(const ArgTables &tab, uint32_t tiles, uint64_t nodes, const uint64_t *in,
+                              uint64_t *scratch, bool first, hipStream_t s);
 // Exclusive scan of the set-bit counts of per-group dirty masks (offsets
 // and total), then the placement of the slots (SlotBump).
 hipError_t launch_scan(const uint64_t *dirty_mask, uint64_t n, uint64_t *offsets, uint64_t *total,
@@ -122,8 +133,7 @@ constexpr uint64_t kScanCompactMaxGroups = 4096;
 // launch reduces the Merkle lists, scans the dirty masks (total also to
 // *total and the pinned host words), places the slots and copies the dirty
 // chunks.  bump.bump and bump.bump_out must differ.
-hipError_t launch_merkle_scan_place(const ArgLists &lists, const uint64_t *nodes, uint64_t *scratch_a,
-                                    uint64_t *scratch_b, const ArgTables &tab, uint64_t ngroups,
+hipError_t launch_merkle_scan_place(const ArgTables &tab, uint32_t tiles, const uint64_t *nodes, uint64_t ngroups,
                                     const uint64_t *dirty_mask, const SlotBump &bump, uint64_t *total,
                                     uint64_t arena_base, hipStream_t s);
 hipError_t launch_reverse_slots(uint64_t top, uint64_t dst, uint64_t n, hipStream_t s);

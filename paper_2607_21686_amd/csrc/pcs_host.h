@@ -126,12 +126,14 @@ struct Layout {
     uint32_t kind;
     uint64_t nbytes, nchunks, ngroups;
     uint64_t row_bytes, window, outer;  // RING shape (restore compatibility)
+    Geom geom;                          // where the logical bytes lie
+    uint64_t nruns;                     // physically contiguous pieces (Run)
 };
 
-// Validates one descriptor and appends its runs (logical start, physical
-// address), merging physically adjacent pieces.  PCS_OK, or PCS_E_INVAL with
-// the reason in *err.  Every address a run covers lies in
-// [ptr, ptr + extent) without wrapping 64 bits.
+// Validates one descriptor, fills its layout and, unless runs is null,
+// appends its runs (logical start, physical address), merging physically
+// adjacent pieces.  PCS_OK, or PCS_E_INVAL with the reason in *err.  Every
+// address a run covers lies in [ptr, ptr + extent) without wrapping 64 bits.
 inline int describe(const pcs_buf &b, uint32_t idx, Layout *lay, std::vector<Run> *runs, std::string *err)
 {
     if (b.flags != 0) return set_err(err, "buffer %u: flags must be 0", idx), PCS_E_INVAL;
@@ -144,7 +146,9 @@ inline int describe(const pcs_buf &b, uint32_t idx, Layout *lay, std::vector<Run
         if (b.ptr > UINT64_MAX - b.nbytes)
             return set_err(err, "buffer %u: address range wraps", idx), PCS_E_INVAL;
         L.nbytes = b.nbytes;
-        rs.push_back({0, b.ptr});
+        L.geom = Geom{b.ptr, b.nbytes, 0, 0, 0, 0, 0};
+        L.nruns = 1;
+        if (runs) rs.push_back({0, b.ptr});
     } else if (b.kind == PCS_RING) {
         if (b.row_bytes == 0 || b.row_bytes % 16 || b.ptr % 16 || b.outer_stride % 16)
             return set_err(err, "buffer %u: ring ptr, row_bytes and outer_stride must be multiples of 16", idx),
@@ -169,6 +173,19 @@ inline int describe(const pcs_buf &b, uint32_t idx, Layout *lay, std::vector<Run
         L.row_bytes = b.row_bytes;
         L.window = b.window;
         L.outer = b.outer;
+        const uint64_t first = std::min(b.window, b.capacity - b.head);
+        const bool wraps = first < b.window;
+        if (total == 0) {
+            L.geom = Geom{b.ptr, 0, 0, 0, 0, 0, 0};
+            L.nruns = 1;
+        } else if (!wraps && (b.outer == 1 || win_bytes == b.outer_stride)) {  // one contiguous piece
+            L.geom = Geom{b.ptr + b.head * b.row_bytes, total, 0, 0, 0, 0, 0};
+            L.nruns = 1;
+        } else {
+            L.geom = Geom{b.ptr, total, win_bytes, first * b.row_bytes, b.head * b.row_bytes, b.outer_stride,
+                          1.0 / (double)win_bytes};
+            L.nruns = b.outer * (wraps ? 2 : 1);
+        }
         uint64_t lpos = 0;
         auto add = [&](uint64_t addr, uint64_t len) {
             if (len == 0) return;
@@ -182,20 +199,19 @@ inline int describe(const pcs_buf &b, uint32_t idx, Layout *lay, std::vector<Run
             rs.push_back({lpos, addr});
             lpos += len;
         };
-        for (uint64_t o = 0; o < b.outer && total; ++o) {
+        for (uint64_t o = 0; o < b.outer && total && runs; ++o) {
             const uint64_t base = b.ptr + o * b.outer_stride;
-            const uint64_t first = std::min(b.window, b.capacity - b.head);
             add(base + b.head * b.row_bytes, first * b.row_bytes);
             add(base, (b.window - first) * b.row_bytes);
         }
-        if (rs.empty()) rs.push_back({0, b.ptr});
+        if (rs.empty() && runs) rs.push_back({0, b.ptr});
     } else {
         return set_err(err, "buffer %u: unknown kind %u", idx, b.kind), PCS_E_INVAL;
     }
     L.nchunks = div_up(L.nbytes, kChunk);
     L.ngroups = div_up(L.nchunks, kGroupChunks);
     *lay = L;
-    runs->insert(runs->end(), rs.begin(), rs.end());
+    if (runs) runs->insert(runs->end(), rs.begin(), rs.end());
     return PCS_OK;
 }
 

@@ -51,16 +51,22 @@ namespace {
 thread_local hipEvent_t t_start = nullptr, t_stop = nullptr;
 thread_local bool t_used = false;
 
+// lds: dynamic LDS no kernel uses, to bound the workgroups a CU holds.
+template <class K, class... Args>
+void run_kernel_lds(K kernel, dim3 grid, dim3 block, uint32_t lds, hipStream_t s, Args... args)
+{
+    if (!t_start) {
+        hipLaunchKernelGGL(kernel, grid, block, lds, s, args...);
+        return;
+    }
+    hipExtLaunchKernelGGL(kernel, grid, block, lds, s, t_start, t_stop, 0, args...);
+    t_start = t_stop = nullptr;
+    t_used = true;
+}
 template <class K, class... Args>
 void run_kernel(K kernel, dim3 grid, dim3 block, hipStream_t s, Args... args)
 {
-    if (!t_start) {
-        hipLaunchKernelGGL(kernel, grid, block, 0, s, args...);
-        return;
-    }
-    hipExtLaunchKernelGGL(kernel, grid, block, 0, s, t_start, t_stop, 0, args...);
-    t_start = t_stop = nullptr;
-    t_used = true;
+    run_kernel_lds(kernel, grid, block, 0, s, args...);
 }
 
 // XXH64 primes (xxHash specification).
@@ -72,7 +78,7 @@ constexpr uint64_t P5 = 0x27D4EB2F165667C5ULL;
 
 __device__ __forceinline__ uint64_t umin(uint64_t a, uint64_t b) { return a < b ? a : b; }
 
-// 64-bit rotate left by a constant 0 < r < 32: two v_alignbit_b32.
+// 64-bit rotate left by 0 < r < 32: two v_alignbit_b32.
 __device__ __forceinline__ uint64_t rotl(uint64_t x, int r)
 {
     const uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32);
@@ -89,10 +95,10 @@ __device__ __forceinline__ uint64_t xround(uint64_t acc, uint64_t lane)
     return acc * P1;
 }
 
-__device__ __forceinline__ uint64_t xmerge(uint64_t acc, uint64_t v)
+// The same with lane * P2 already formed.
+__device__ __forceinline__ uint64_t xstep(uint64_t acc, uint64_t scaled)
 {
-    acc ^= xround(0, v);
-    return acc * P1 + P4;
+    return rotl(acc + scaled, 31) * P1;
 }
 
 __device__ __forceinline__ uint64_t avalanche(uint64_t h)
@@ -120,41 +126,108 @@ __device__ __forceinline__ uint64_t node_hash(uint64_t l, uint64_t r)
     return avalanche(acc);
 }
 
-__device__ __forceinline__ uint64_t shfl64(uint64_t v, int src)
+// A 64-bit DPP move (CTL below 0x100: a permutation of each lane quad, two
+// bits per lane; 0x100 + n: from n lanes above within a row of 16).
+template <int CTL>
+__device__ __forceinline__ uint64_t dpp64(uint64_t v)
 {
-    const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)v, src, 64);
-    const uint32_t hi = (uint32_t)__shfl((int)(uint32_t)(v >> 32), src, 64);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTL, 0xF, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTL, 0xF, 0xF, false);
     return ((uint64_t)hi << 32) | lo;
 }
 
-// Promote-odd Merkle reduction of lanes [0, m) of one wavefront (m <= 64,
-// wave-uniform).  The result is valid in lane 0.
-__device__ uint64_t wave_merkle(uint64_t v, uint32_t m)
+__device__ __forceinline__ uint32_t lane_word(uint32_t v, uint32_t lane)
 {
-    const int lane = (int)(threadIdx.x & 63);
-    while (m > 1) {
-        const uint64_t a = shfl64(v, (2 * lane) & 63);
-        const uint64_t b = shfl64(v, (2 * lane + 1) & 63);
-        const uint32_t half = m >> 1;
-        if ((uint32_t)lane < half)
-            v = node_hash(a, b);
-        else if ((uint32_t)lane == half && (m & 1))
-            v = a;  // lane 2*half = m-1: the odd node is promoted
-        m = (m + 1) >> 1;
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)lane);
+}
+__device__ __forceinline__ uint64_t lane_word(uint64_t v, uint32_t lane)
+{
+    return ((uint64_t)lane_word((uint32_t)(v >> 32), lane) << 32) | lane_word((uint32_t)v, lane);
+}
+
+// The value 16 lanes above (S = 16: in lanes 0-15 and 32-47) or 32 lanes
+// above (S = 32: in lanes 0-31).
+template <int S>
+__device__ __forceinline__ uint64_t row_swap(uint64_t v)
+{
+    const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+    if constexpr (S == 16) {
+        const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+        const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+        return ((uint64_t)b[1] << 32) | a[1];
+    } else {
+        const auto a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+        const auto b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+        return ((uint64_t)b[1] << 32) | a[1];
+    }
+}
+
+// The value S lanes above (S a power of two), in the lanes l with
+// l mod 2 S < S; other lanes get something else.  DPP moves and row swaps: none
+// waits on the LDS path as a shuffle does.
+template <int S>
+__device__ __forceinline__ uint64_t from_above(uint64_t v)
+{
+    if constexpr (S == 1) return dpp64<0xF5>(v);
+    else if constexpr (S == 2) return dpp64<0xAA>(v);
+    else if constexpr (S == 4) return dpp64<0x104>(v);
+    else if constexpr (S == 8) return dpp64<0x108>(v);
+    else return row_swap<S>(v);
+}
+
+// Promote-odd Merkle reduction of m values of one wavefront (m wave-uniform,
+// at most 2^LEVELS): value i lies in lane S * i.  A level's node stays in the
+// lane of its left child, so nothing is compacted; the root is valid in
+// lane 0.
+template <int S, int LEVELS>
+__device__ __forceinline__ uint64_t wave_merkle(uint64_t v, uint32_t m)
+{
+    if constexpr (LEVELS > 0) {
+        if (m <= 1) return v;
+        const uint64_t right = from_above<S>(v);
+        const uint32_t i = (threadIdx.x & 63) / S;
+        if (i + 1 < m) v = node_hash(v, right);  // lanes of odd i compute a value nothing reads
+        return wave_merkle<2 * S, LEVELS - 1>(v, (m + 1) / 2);
     }
     return v;
 }
 
-// The run of [begin, begin + count) that holds logical offset L: the largest
-// index whose lstart <= L (runs are sorted by lstart, the first at 0).
-__device__ __forceinline__ uint32_t find_run(const Run *runs, uint32_t begin, uint32_t count, uint64_t L)
+// Four such reductions at once: value i of list q (n[q] of them, at most 64)
+// is lane i of v[q]; the root of list q ends in lane q.  A level halves the
+// lanes a list needs, so the first two levels interleave the lists (0 and 1
+// in even and odd lanes, then all four) and the rest run on all of them: 7
+// nodes per lane where four reductions one after another take 24.  (n by
+// value: a choice between array elements would put the array in memory.)
+__device__ __forceinline__ uint64_t wave_merkle4(const uint64_t (&v)[4], uint32_t n0, uint32_t n1, uint32_t n2,
+                                                 uint32_t n3)
 {
-    uint32_t lo = begin, hi = begin + count;
-    while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (runs[mid].lstart <= L) lo = mid; else hi = mid;
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t even_n = (lane & 2) ? n2 : n0, odd_n = (lane & 2) ? n3 : n1;
+    uint64_t w[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint64_t a = v[2 * h], b = v[2 * h + 1];
+        const uint64_t below = dpp64<0xA0>(b), above = dpp64<0xF5>(a);  // (moved before any lane branches)
+        const bool odd = lane & 1;
+        const uint64_t left = odd ? below : a, right = odd ? b : above;
+        w[h] = (lane | 1) < (odd ? (h ? n3 : n1) : (h ? n2 : n0)) ? node_hash(left, right) : left;
     }
-    return lo;
+    const uint64_t below = dpp64<0x44>(w[1]), above = dpp64<0xEE>(w[0]);
+    const bool second = lane & 2;
+    const uint64_t left = second ? below : w[0], right = second ? w[1] : above;
+    uint32_t m = (((lane & 1) ? odd_n : even_n) + 1) >> 1;
+    uint32_t i = lane >> 2;  // this lane's node of list lane & 3
+    uint64_t r = 2 * i + 1 < m ? node_hash(left, right) : left;
+    const auto level = [&](uint64_t above) {  // lanes of even i; the others compute a value nothing reads
+        m = (m + 1) >> 1;
+        if (i + 1 < m) r = node_hash(r, above);
+        i >>= 1;
+    };
+    level(from_above<4>(r));
+    level(from_above<8>(r));
+    level(from_above<16>(r));
+    level(from_above<32>(r));
+    return r;
 }
 
 // The tile a workgroup takes (xcd_tile_of).  Measured on MI355X against the
@@ -212,89 +285,262 @@ __device__ void store_partial(uint64_t a, uint4 v, uint32_t n)
     for (uint32_t k = 0; k < n; ++k) p[k] = (uint8_t)(w[k >> 2] >> (8 * (k & 3)));
 }
 
-// ---------------------------------------------------------------- group map
-
-// One lane per group: its buffer (the largest b with group_begin <= g; empty
-// buffers own no group and lose ties) and the run holding its first byte, so
-// that the tile kernels start without searching.
-__global__ void k_group_map(const JobBuf *__restrict__ bufs, const Run *__restrict__ runs, uint32_t nbuf,
-                            uint64_t ngroups, GroupRef *__restrict__ map)
+// Inclusive prefix sum across the 64 lanes of a wavefront, in DPP moves (no
+// LDS round trips): shifts by 1, 2, 4 and 8 lanes within each row of 16
+// lanes, then row 0's total (lane 15) into row 1 and row 2's into row 3
+// (row_bcast:15), then rows 0-1's total (lane 31) into rows 2 and 3
+// (row_bcast:31).  A lane whose source lies outside its row, or a row the
+// row mask leaves out, adds 0 (the `old` operand).
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x)
 {
-    const uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= ngroups) return;
-    uint32_t lo = 0, hi = nbuf;
-    while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (bufs[mid].group_begin <= g) lo = mid; else hi = mid;
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);  // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);  // row_shr:2
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);  // row_shr:4
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);  // row_shr:8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);  // row_bcast:15
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);  // row_bcast:31
+    return x;
+}
+
+// ---------------------------------------------------------------- job tables
+
+// Stages a job's tables for the kernels that follow on the stream: copies
+// n16 16-byte units from mapped host memory to device memory, and one lane
+// per group writes the map entry of its buffer.  The map part starts from
+// group counts on the host side of the link, so a wavefront takes one buffer
+// at a time (two reads over the link) and fills that buffer's entries.
+// Workgroups [0, copy_blocks) copy, the rest map.  One launch where a copy
+// and a map launch took two (2.9 + 3.2 us and the gap between them).
+constexpr uint32_t kStageLanes = 256, kStageUnits = 4 * kStageLanes;
+__global__ __launch_bounds__(kStageLanes) void k_stage(uint64_t host, uint64_t dev, uint64_t n16, uint32_t copy_blocks,
+                                                       const JobBuf *__restrict__ host_bufs, uint32_t nbuf,
+                                                       uint32_t *__restrict__ map)
+{
+    const uint32_t t = threadIdx.x;
+    if (blockIdx.x < copy_blocks) {
+        const uint64_t u0 = (uint64_t)blockIdx.x * kStageUnits + t;
+        uint4 v[4];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k)
+            if (u0 + k * kStageLanes < n16) v[k] = load16(host + 16 * (u0 + k * kStageLanes));
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k)
+            if (u0 + k * kStageLanes < n16) store16(dev + 16 * (u0 + k * kStageLanes), v[k]);
+        return;
     }
-    const JobBuf &jb = bufs[lo];
-    const uint64_t x0 = (g - jb.group_begin) * kGroupChunks * kChunk;
-    map[g] = GroupRef{lo, find_run(runs, jb.run_begin, jb.run_count, x0)};
+    const uint32_t b = (blockIdx.x - copy_blocks) * (kStageLanes / 64) + (t >> 6);
+    if (b >= nbuf) return;
+    const uint64_t first = host_bufs[b].group_begin, chunks = host_bufs[b].nchunks();
+    const uint64_t n = chunks / kGroupChunks + (chunks % kGroupChunks != 0);
+    for (uint64_t i = t & 63; i < n; i += 64) map[first + i] = b;
+}
+
+// What a tile kernel needs of one buffer, in registers of the wavefront that
+// asked (the same in every lane).
+struct TileBuf {
+    Geom g;
+    uint64_t nchunks, chunk_begin, group_begin;
+    uint64_t slots;        // device address of chunk 0's slot (pack, restore)
+    uint64_t slot_list;    // restore: address of its manifest entries (0: slots are contiguous)
+    uint64_t hash[2];      // addresses of chunk 0's fingerprint outputs
+    uint64_t parent_hash;  // diff, verify: address of the fingerprint chunk 0 is compared with
+    uint64_t parent_chunks, manifest, parent_manifest, parent_slot0;  // diff
+};
+
+// Group G's buffer, read by a whole wavefront.
+template <int MODE>
+__device__ __forceinline__ TileBuf tile_buf(const DevTables &tab, uint64_t G)
+{
+    const JobBuf &jb = tab.bufs[__builtin_amdgcn_readfirstlane(tab.map[G])];
+    TileBuf b;
+    b.g = jb.g;
+    b.nchunks = jb.nchunks();
+    b.chunk_begin = jb.chunk_begin;
+    b.group_begin = jb.group_begin;
+    b.slots = jb.payload;
+    b.slot_list = MODE == kModeVerify ? jb.manifest : 0;
+    b.hash[0] = jb.hash_dst[0];
+    b.hash[1] = jb.hash_dst[1];
+    b.parent_hash = jb.parent_hash;
+    b.parent_chunks = jb.parent_chunks;
+    b.manifest = jb.manifest;
+    b.parent_manifest = jb.parent_manifest;
+    b.parent_slot0 = jb.parent_slot0;
+    return b;
+}
+
+// The argument tables in a wavefront's registers: lane l holds buffers l and
+// 64 + l % 32 and ring l % 8.  Every load is issued before any is used, so a
+// workgroup learns its buffer in one round trip to memory; a search, one
+// dependent load a step and several more for the chosen entry, took
+// 5,700 cycles of an 8-chunk tile's 20,000.
+static_assert(kArgBufs == 96 && kArgRings == 8, "lanes of ArgLanes");
+struct ArgLanes {
+    ArgBuf lo, hi;
+    ArgRing ring;
+    uint64_t valid_lo, valid_hi, rings;  // ballots
+    __device__ __forceinline__ explicit ArgLanes(const ArgTables &t)
+    {
+        const uint32_t lane = threadIdx.x & 63;
+        lo = t.bufs[lane];
+        hi = t.bufs[64 + (lane & 31)];
+        ring = t.rings[lane & 7];
+        valid_lo = __ballot(lane < t.nbuf);
+        valid_hi = __ballot(lane < 32 && 64 + lane < t.nbuf);
+        rings = __ballot(lane < t.nring);
+    }
+    // The buffer of group G: the last one that begins at or before it (an
+    // empty buffer begins where the next one does and loses).
+    __device__ __forceinline__ uint32_t find(uint64_t G) const
+    {
+        const uint64_t a = __ballot(lo.group_begin <= G) & valid_lo, b = __ballot(hi.group_begin <= G) & valid_hi;
+        return (uint32_t)(__popcll(a) + __popcll(b)) - 1;
+    }
+    __device__ __forceinline__ ArgBuf buf(uint32_t i) const
+    {
+        const uint32_t l = i & 63;
+        ArgBuf r;
+        if (i < 64) {
+            r.addr = lane_word(lo.addr, l);
+            r.nbytes = lane_word(lo.nbytes, l);
+            r.chunk_begin = lane_word(lo.chunk_begin, l);
+            r.group_begin = lane_word(lo.group_begin, l);
+            r.aux = lane_word(lo.aux, l);
+        } else {
+            r.addr = lane_word(hi.addr, l);
+            r.nbytes = lane_word(hi.nbytes, l);
+            r.chunk_begin = lane_word(hi.chunk_begin, l);
+            r.group_begin = lane_word(hi.group_begin, l);
+            r.aux = lane_word(hi.aux, l);
+        }
+        return r;
+    }
+    __device__ __forceinline__ Geom geom(uint32_t i, const ArgBuf &b) const
+    {
+        Geom g{b.addr, b.nbytes, 0, 0, 0, 0, 0};
+        const uint64_t m = __ballot(ring.buf == i) & rings;
+        if (m) {
+            const uint32_t l = (uint32_t)__builtin_ctzll(m);
+            g.win = lane_word(ring.win, l);
+            g.first = lane_word(ring.first, l);
+            g.head = lane_word(ring.head, l);
+            g.stride = lane_word(ring.stride, l);
+            g.inv_win = __longlong_as_double((long long)lane_word((uint64_t)__double_as_longlong(ring.inv_win), l));
+        }
+        return g;
+    }
+};
+template <int MODE>
+__device__ __forceinline__ TileBuf tile_buf(const ArgTables &tab, uint64_t G)
+{
+    const ArgLanes lanes(tab);
+    const uint32_t i = lanes.find(G);
+    const ArgBuf a = lanes.buf(i);
+    TileBuf b;
+    b.g = lanes.geom(i, a);
+    b.nchunks = chunks_of(a.nbytes);
+    b.chunk_begin = a.chunk_begin;
+    b.group_begin = a.group_begin;
+    const bool listed = MODE == kModeVerify && (a.aux & kAuxManifest);
+    b.slots = listed ? 0 : a.aux;
+    b.slot_list = listed ? a.aux & ~kAuxManifest : 0;
+    b.hash[0] = tab.hash[0] ? tab.hash[0] + 8 * b.chunk_begin : 0;
+    b.hash[1] = tab.hash[1] ? tab.hash[1] + 8 * b.chunk_begin : 0;
+    const uint64_t pb = MODE == kModeDiff ? (uint32_t)a.aux : b.chunk_begin;
+    b.parent_hash = tab.parent_hash + 8 * pb;
+    b.parent_chunks = a.aux >> 32;
+    b.manifest = tab.manifest ? tab.manifest + 8 * b.chunk_begin : 0;
+    b.parent_manifest = tab.parent_manifest ? tab.parent_manifest + 8 * pb : 0;
+    b.parent_slot0 = tab.parent_slot0 + pb * kChunk;
+    return b;
+}
+
+// A tile's setup, by the first wavefront of a workgroup: its buffer, then
+// lane c describes chunk c of the tile (CPW chunks, `part` of its group).
+// The others read from LDS after a barrier what the tile needs: each field is
+// written on its own, and the geometry only for a tile with a chunk of more
+// than two pieces, so that few registers are live at once (all at once they
+// cost the 1024-lane hash tiles their second workgroup per CU).
+struct TileInfo {
+    uint64_t c0;  // the tile's first chunk
+    uint32_t nv;  // its chunks (0: the buffer's last group ends before this tile)
+    bool many;    // a chunk of it spans more than two pieces
+    bool ragged;  // its last chunk ends inside a granule
+    uint64_t hash[2], parent_hash, parent_chunks, manifest, parent_manifest, parent_slot0;
+    Geom g;
+};
+template <int MODE, int CPW, class Tab>
+__device__ __forceinline__ void tile_setup(const Tab &tab, uint64_t G, uint32_t part, uint64_t arena_base,
+                                           TileInfo *info, ChunkLoc *loc)
+{
+    const uint32_t t = threadIdx.x;
+    if (t < 64) {
+        const TileBuf b = tile_buf<MODE>(tab, G);
+        const uint64_t c0 = (G - b.group_begin) * kGroupChunks + part * CPW;
+        const uint32_t nv = c0 < b.nchunks ? (uint32_t)umin(CPW, b.nchunks - c0) : 0;
+        bool pieces = false;
+        if (t < CPW) {
+            ChunkLoc l{0, 0, 0, 0, 0};
+            if (t < nv) {
+                l = chunk_loc(b.g, c0 + t);
+                pieces = l.a1 == 0;
+                if (MODE == kModeVerify && b.slot_list) l.slot = arena_base + ((const g_u64 *)b.slot_list)[c0 + t];
+                else if (MODE == kModePack || MODE == kModeVerify) l.slot = b.slots + (c0 + t) * kChunk;
+            }
+            loc[t] = l;
+        }
+        const auto put = [&](uint64_t *field, uint64_t v) {
+            if (t == 0) *field = v;
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        put(&info->c0, c0);
+        if (t == 0) info->nv = nv;
+        put(&info->hash[0], b.hash[0]);
+        put(&info->hash[1], b.hash[1]);
+        if (MODE == kModeDiff || MODE == kModeVerify) put(&info->parent_hash, b.parent_hash);
+        if (MODE == kModeDiff) {
+            put(&info->parent_chunks, b.parent_chunks);
+            put(&info->manifest, b.manifest);
+            put(&info->parent_manifest, b.parent_manifest);
+            put(&info->parent_slot0, b.parent_slot0);
+        }
+        const bool many = __any(pieces);
+        if (t == 0) {
+            info->many = many;
+            info->ragged = (b.g.nbytes & 15) != 0 && c0 + nv == b.nchunks;
+        }
+        if (many) {
+            put(&info->g.addr, b.g.addr);
+            put(&info->g.nbytes, b.g.nbytes);
+            put(&info->g.win, b.g.win);
+            put(&info->g.first, b.g.first);
+            put(&info->g.head, b.g.head);
+            put(&info->g.stride, b.g.stride);
+            if (t == 0) info->g.inv_win = b.g.inv_win;
+        }
+    }
+    __syncthreads();
 }
 
 // ---------------------------------------------------------------- fingerprint
 
-// Physical address of logical offset L of a buffer (binary search of its
-// runs): the path for the few chunks that straddle a ring wrap.
-__device__ uint64_t phys_addr(const Run *runs, uint32_t begin, uint32_t count, uint64_t L)
+// U granules of a lane, granule k at at[k]: its 16 bytes at offset x of a chunk
+// of len[k] bytes, zero past the chunk's end.  Every whole granule's load is
+// issued before the rare partial ones, which wait byte by byte (ragged: there
+// is one in the tile; decided per granule, each load waited for the last).
+template <int U>
+__device__ __forceinline__ void load_granules(const uint64_t (&at)[U], const uint32_t (&len)[U], uint32_t x, bool ragged,
+                                              uint4 (&r)[U])
 {
-    const Run r = runs[find_run(runs, begin, count, L)];
-    return r.addr + (L - r.lstart);
-}
-
-// Where one chunk's bytes lie: byte x (x < len) is at (x < split ? a1 : a2)
-// + x when the chunk spans at most two physical runs (it straddles a ring's
-// wrap, or the end of one ring row set and the start of the next, when that
-// boundary falls inside it); a1 = 0 marks a chunk spanning more runs (rows
-// shorter than a chunk), whose addresses are searched per access.  Run
-// boundaries are 16-byte aligned, so no 16-byte granule crosses one.
-struct ChunkLoc {
-    uint64_t a1, a2;
-    uint32_t split, len;
-};
-
-// Per-chunk setup shared by the tile kernels: lane c < 64 of the first
-// wavefront describes chunk c of the group.  r0 is the run holding the
-// group's first byte; a chunk's run is found by stepping forward from there
-// (a group usually lies in one or two runs), with a search for groups that
-// span many short runs.
-__device__ __forceinline__ void chunk_table(const JobBuf &jb, const Run *runs, uint32_t r0, uint64_t c0,
-                                            uint32_t nv, ChunkLoc *loc)
-{
-    const uint32_t t = threadIdx.x;
-    if (t < kGroupChunks) {
-        ChunkLoc l{0, 0, 0, 0};
-        if (t < nv) {
-            const uint64_t cb = (c0 + t) * kChunk;
-            l.len = (uint32_t)umin(kChunk, jb.nbytes - cb);
-            const uint32_t last = jb.run_begin + jb.run_count - 1;
-            uint32_t idx = r0;
-            Run r = runs[idx];
-            uint64_t end = idx < last ? runs[idx + 1].lstart : jb.nbytes;
-            for (int k = 0; end <= cb; ++k) {  // cb < nbytes: ends at the last run at the latest
-                if (k == 2) {
-                    idx = find_run(runs, idx + 1, last - idx, cb);
-                } else {
-                    ++idx;
-                }
-                r = runs[idx];
-                end = idx < last ? runs[idx + 1].lstart : jb.nbytes;
-            }
-            const uint64_t a1 = r.addr + (cb - r.lstart);
-            if (cb + l.len <= end) {
-                l.a1 = l.a2 = a1;
-                l.split = l.len;
-            } else {  // idx < last here, since the last run ends at nbytes
-                const Run r2 = runs[idx + 1];
-                const uint64_t end2 = idx + 1 < last ? runs[idx + 2].lstart : jb.nbytes;
-                if (cb + l.len <= end2) {
-                    l.a1 = a1;
-                    l.split = (uint32_t)(end - cb);
-                    l.a2 = r2.addr - l.split;  // byte `split` of the chunk is r2's first byte
-                }
-            }
-        }
-        loc[t] = l;
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+        r[k] = make_uint4(0, 0, 0, 0);
+        if (x + 16 <= len[k]) r[k] = load16_nt(at[k]);
+    }
+    if (ragged) {
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            if (x < len[k] && x + 16 > len[k]) r[k] = load_partial(at[k], len[k] - x);
     }
 }
 
@@ -302,28 +548,6 @@ __device__ __forceinline__ void chunk_table(const JobBuf &jb, const Run *runs, u
 __device__ __forceinline__ uint64_t sel4(uint64_t a, uint64_t b, uint64_t c, uint64_t d, uint32_t i)
 {
     return i == 0 ? a : i == 1 ? b : i == 2 ? c : d;
-}
-
-// A workgroup's buffer: through the map, or by searching a table of at most
-// kArgBufs buffers (largest b with group_begin <= G; empty buffers lose ties).
-__device__ __forceinline__ uint32_t buf_index(const DevTables &t, uint64_t G) { return t.map[G].buf; }
-__device__ __forceinline__ uint32_t buf_index(const ArgTables &t, uint64_t G)
-{
-    uint32_t lo = 0, hi = t.nbuf;
-    while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (t.bufs[mid].group_begin <= G) lo = mid; else hi = mid;
-    }
-    return lo;
-}
-
-// A workgroup's buffer and the run holding its group's first byte.
-__device__ __forceinline__ GroupRef group_ref(const DevTables &t, uint64_t G) { return t.map[G]; }
-__device__ __forceinline__ GroupRef group_ref(const ArgTables &t, uint64_t G)
-{
-    const uint32_t b = buf_index(t, G);
-    const JobBuf &jb = t.bufs[b];
-    return GroupRef{b, find_run(t.runs, jb.run_begin, jb.run_count, (G - jb.group_begin) * kGroupChunks * kChunk)};
 }
 
 // First-round stagger.  The workgroups of a launch's first round (one per CU)
@@ -346,6 +570,36 @@ __device__ __forceinline__ void stagger_start(const Stagger &stg)
         __builtin_amdgcn_s_sleep(2);
 }
 
+// N stripes of one accumulator's chain, the lane words (already multiplied by
+// P2) 32 bytes apart in LDS: the next B are loaded while B are consumed, so
+// the chain waits on its own arithmetic alone (28 cycles a round measured
+// with the words in registers; 64 when each group of eight reads waited).  A
+// loop, not unrolled: unrolled, the compiler moves all N loads up front and
+// out of registers.
+template <int N>
+__device__ __forceinline__ uint64_t chain(uint64_t va, const uint8_t *p)
+{
+    constexpr int B = 16;
+    static_assert(N % (2 * B) == 0, "whole pairs of batches");
+    uint64_t d[B], e[B];
+#pragma unroll
+    for (int i = 0; i < B; ++i) d[i] = *reinterpret_cast<const uint64_t *>(p + 32 * i);
+#pragma unroll 1
+    for (int s = 0; s < N; s += 2 * B, p += 64 * B) {
+#pragma unroll
+        for (int i = 0; i < B; ++i) e[i] = *reinterpret_cast<const uint64_t *>(p + 32 * (B + i));
+#pragma unroll
+        for (int i = 0; i < B; ++i) va = xstep(va, d[i]);
+        if (s + 2 * B < N) {
+#pragma unroll
+            for (int i = 0; i < B; ++i) d[i] = *reinterpret_cast<const uint64_t *>(p + 32 * (2 * B + i));
+        }
+#pragma unroll
+        for (int i = 0; i < B; ++i) va = xstep(va, e[i]);
+    }
+    return va;
+}
+
 // Fingerprint tile kernels (k_hash, k_hash_staggered; the body is
 // hash_tile).  One workgroup = one tile of CPW chunks of one
 // buffer: a whole 64-chunk group, or for small jobs an eighth of one, so
@@ -354,15 +608,20 @@ __device__ __forceinline__ void stagger_start(const Stagger &stg)
 // chunk of the tile:
 // all T lanes load it with coalesced 16-byte loads (SL/16 lanes per chunk
 // slice), kModePack stores it to the chunk's snapshot slot (zero-padding a
-// partial last chunk) and kModeVerify to the buffer's runs, and every lane
+// partial last chunk) and kModeVerify to the buffer's pieces, and every lane
 // writes it to an LDS tile; then lane quads of the first 4*CPW lanes hash
 // the tile while the next slice's loads are in flight.  Lane q of a quad owns
 // XXH64 accumulator q, which reads exactly bytes [8q, 8q+8) of each 32-byte
-// stripe.  A wavefront issues a lane's rounds one after another (a round is
-// about ten instructions, most of them 32-bit multiply steps of the 64-bit
-// products), so one accumulator per lane halves the instructions a chunk's
+// stripe.  A wavefront issues a lane's rounds one after another, so one
+// accumulator per lane halves the instructions a chunk's
 // chain costs each wavefront and spreads the hashing over twice as many
-// wavefronts as lane pairs with two accumulators each would.  kModeDiff /
+// wavefronts as lane pairs with two accumulators each would.  For the same
+// reason the words of a sub-tile, whose time is that chain's, reach LDS already
+// multiplied by P2, the half of a round
+// that does not depend on the accumulator: all T lanes share that work, and
+// the chain keeps one multiplication of two.  (Whole groups are bound by
+// memory, and the registers this takes cost them a workgroup per CU.)
+// kModeDiff /
 // kModeVerify ballot one flag per chunk into a per-group mask (the group is
 // one bitmap word; a diff sub-tile writes its byte of the word).  WB: the
 // pack stores go through the caches (write-back) instead of streaming past
@@ -376,192 +635,271 @@ __device__ __forceinline__ void hash_tile(const Tab &tab, uint64_t *__restrict__
     constexpr uint32_t LPS = SL / 16;                   // lanes per chunk slice
     constexpr int U = CPW * SL / 16 / T;                // granules per lane per step
     constexpr uint32_t kTiles = kGroupChunks / CPW;     // tiles per 64-chunk group
-    constexpr bool kFromSlots = MODE == kModeVerify;    // source is the snapshot, destination the runs
+    constexpr uint32_t kHashers = 64 * ((4 * CPW + 63) / 64);  // lanes of the wavefronts that hold accumulators
+    constexpr bool kScaled = CPW == 8;                  // words reach LDS multiplied by P2
+    constexpr bool kFromSlots = MODE == kModeVerify;    // source is the snapshot, destination the pieces
     static_assert(U >= 1 && T % LPS == 0 && kGroupChunks % CPW == 0, "tile shape");
     static_assert(T >= 4 * CPW, "one lane per accumulator");
     static_assert(CPW == kGroupChunks || MODE != kModeVerify, "verify flags need whole groups");
-    static_assert(CPW == kGroupChunks || CPW == 8 || MODE != kModeDiff, "a diff sub-tile writes one mask byte");
+    static_assert(kSteps > 1 || (MODE != kModeVerify && (MODE != kModePack || WB)), "one-step tiles store write-back");
+    static_assert(CPW == kGroupChunks || CPW == 8, "a sub-tile is hashed by one wavefront; diff writes one mask byte");
     __shared__ __attribute__((aligned(16))) uint8_t tile[CPW * kRow];
-    __shared__ ChunkLoc cloc[kGroupChunks];
-    __shared__ uint64_t leaves[CPW];
+    __shared__ ChunkLoc cloc[CPW];
+    __shared__ TileInfo info;
+    __shared__ uint64_t partial[4];
     __shared__ uint32_t dflag[CPW];
 
     const uint32_t tile_id = xcd_tile();
     if constexpr (STAGGER) stagger_start(stg);
     const uint64_t G = tile_id / kTiles;
-    const GroupRef gr = group_ref(tab, G);
-    const JobBuf &jb = tab.bufs[gr.buf];
-    const Run *runs = tab.runs;
     const uint32_t t = threadIdx.x;
-    const uint64_t c0 = (G - jb.group_begin) * kGroupChunks + (tile_id % kTiles) * CPW;
-    if (c0 >= jb.nchunks) {  // a buffer's last group may end before this tile
+    tile_setup<MODE, CPW>(tab, G, tile_id % kTiles, arena_base, &info, cloc);
+    const uint32_t nv = __builtin_amdgcn_readfirstlane(info.nv);
+    if (nv == 0) {
         // A diff sub-tile owns byte (tile % 8) of its group's dirty mask:
         // an empty one writes it as 0 so every byte of the mask is defined.
         if (MODE == kModeDiff && kTiles > 1 && t == 0 && flag_mask)
             ((g_u8 *)flag_mask)[G * kTiles + tile_id % kTiles] = 0;
         return;
     }
-    const uint32_t nv = (uint32_t)umin(CPW, jb.nchunks - c0);
-    const uint32_t run_begin = jb.run_begin, run_count = jb.run_count;
-    const g_u64 *man = (const g_u64 *)jb.manifest;
-    chunk_table(jb, runs, gr.run, c0, nv, cloc);
-    __syncthreads();
+    const uint64_t c0 = info.c0;
 
-    // This lane's granules: chunk (k*T + t) / LPS, slot t % LPS of each slice.
-    const uint32_t slot = (t % LPS) * 16;
-    uint64_t ga[U], gb[U];  // runs side: where the chunk's bytes lie (ChunkLoc)
-    uint64_t sa[U];         // slots side: the chunk's 4096-byte slot (0 if the group has no such chunk)
-    uint32_t gs[U], gl[U];
-#pragma unroll
-    for (int k = 0; k < U; ++k) {
-        const uint32_t c = (k * T + t) / LPS;
-        const ChunkLoc l = c < nv ? cloc[c] : ChunkLoc{0, 0, 0, 0};
-        ga[k] = l.a1;
-        gb[k] = l.a2;
-        gs[k] = l.split;
-        gl[k] = l.len;
-        sa[k] = 0;
-        if (c < nv && (MODE == kModePack || kFromSlots))
-            sa[k] = (kFromSlots && man) ? arena_base + man[c0 + c] : jb.payload + (c0 + c) * kChunk;
-    }
-    auto runs_addr = [&](int k, uint32_t x) -> uint64_t {
-        const uint32_t c = (k * T + t) / LPS;
-        return ga[k] ? (x < gs[k] ? ga[k] : gb[k]) + x : phys_addr(runs, run_begin, run_count, (c0 + c) * kChunk + x);
-    };
-    auto load_granule = [&](int k, uint32_t x) -> uint4 {
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (x < gl[k]) {
-            if (kFromSlots) {
-                v = load16_nt(sa[k] + x);  // slots are whole 4096-byte granules, zero padded
-            } else {
-                const uint64_t a = runs_addr(k, x);
-                v = x + 16 <= gl[k] ? load16_nt(a) : load_partial(a, gl[k] - x);
-            }
-        }
-        return v;
-    };
-
-    uint4 r[U];
-#pragma unroll
-    for (int k = 0; k < U; ++k) r[k] = load_granule(k, slot);
-
+    const uint32_t slot = (t % LPS) * 16;  // this lane's place in each slice
+    const bool ragged = __builtin_amdgcn_readfirstlane(info.ragged);
     const uint32_t ci = t >> 2, q = t & 3;
     const bool hasher = t < 4 * CPW && ci < nv;
     const uint32_t len = hasher ? cloc[ci].len : 0;
     const uint32_t nst = len >> 5;
-    // Incremental checkpoint: where the parent holds this chunk, fetched now
-    // and entered in the new manifest at the end if the chunk is clean (a
-    // dirty chunk's entry is its slot, written once the slots are placed).
-    uint64_t parent_loc = 0;
-    if (MODE == kModeDiff && hasher && q == 0 && jb.manifest && c0 + ci < jb.parent_chunks)
-        parent_loc = jb.parent_manifest ? ((const g_u64 *)jb.parent_manifest)[c0 + ci]
-                                        : jb.parent_slot0 + (c0 + ci) * kChunk;
+    const uint64_t i = c0 + ci;
+    // What the chunk's fingerprint is compared with and, in an incremental
+    // checkpoint, where the parent holds it (entered in the new manifest if
+    // the chunk is clean; a dirty chunk's entry is its slot, written once the
+    // slots are placed): fetched now, used at the end.
+    uint64_t parent_loc = 0, want = 0;
+    bool compare = false;
+    if (hasher && q == 0) {
+        if (MODE == kModeDiff && i < info.parent_chunks) {
+            compare = true;
+            want = ((const g_u64 *)info.parent_hash)[i];
+            if (info.manifest)
+                parent_loc = info.parent_manifest ? ((const g_u64 *)info.parent_manifest)[i]
+                                                    : info.parent_slot0 + i * kChunk;
+        }
+        if (MODE == kModeVerify) want = ((const g_u64 *)info.parent_hash)[i];
+    }
     // Accumulator q with seed 0: P1 + P2, P2, 0, -P1.
     uint64_t va = q == 0 ? P1 + P2 : q == 1 ? P2 : q == 2 ? 0 : 0 - P1;
     uint64_t tw0 = 0, tw1 = 0, tw2 = 0, tw3 = 0;  // the chunk's tail (< 32 bytes), zero padded
 
-    for (uint32_t step = 0; step < kSteps; ++step) {
+    // A granule's words to the LDS tile.
+    const auto stage = [&](uint32_t c, uint32_t x, uint32_t clen, uint4 v) {
+        uint64_t w0 = ((uint64_t)v.y << 32) | v.x, w1 = ((uint64_t)v.w << 32) | v.z;
+        if (kScaled && x < (clen & ~31u)) {  // a whole stripe's words; the tail goes in as it is
+            w0 *= P2;
+            w1 *= P2;
+        }
+        *reinterpret_cast<ulonglong2 *>(tile + c * kRow + slot) = make_ulonglong2(w0, w1);
+    };
+    // Hashes the slice in the LDS tile.
+    const auto hash_slice = [&](uint32_t step) {
+        const uint32_t s0 = step * (SL / 32);
+        const uint8_t *row = tile + (t < 4 * CPW ? ci : 0) * kRow;
+        bool whole = false;
+        if constexpr (kScaled) {
+            whole = __all(!hasher || nst >= s0 + SL / 32);
+            if (whole) va = chain<SL / 32>(va, row + 8 * q);
+        }
+        if (!whole && hasher) {
+            const uint32_t ns = nst > s0 ? (uint32_t)umin(SL / 32, nst - s0) : 0;
+#pragma unroll 8
+            for (uint32_t s = 0; s < ns; ++s) {
+                const uint64_t w = *reinterpret_cast<const uint64_t *>(row + 32 * s + 8 * q);
+                va = kScaled ? xstep(va, w) : xround(va, w);
+            }
+            const uint32_t tp = nst * 32;  // tail start, 32-aligned, inside this slice if here
+            if (tp < len && tp >= step * SL && tp < (step + 1) * SL) {
+                const ulonglong2 x = *reinterpret_cast<const ulonglong2 *>(row + tp - step * SL);
+                const ulonglong2 y = *reinterpret_cast<const ulonglong2 *>(row + tp - step * SL + 16);
+                tw0 = x.x;
+                tw1 = x.y;
+                tw2 = y.x;
+                tw3 = y.y;
+            }
+        }
+    };
+
+    if (__builtin_amdgcn_readfirstlane(info.many)) {
+        // A tile with a chunk of more than two pieces: every granule's address
+        // from the geometry, one at a time (a loop of its own: its arithmetic
+        // beside the other loop's prefetched slice does not fit the registers).
+        for (uint32_t step = 0; step < kSteps; ++step) {
+            const uint32_t x = step * SL + slot;
+#pragma unroll 1
+            for (int k = 0; k < U; ++k) {
+                const uint32_t c = (k * T + t) / LPS;
+                if (c >= nv) break;
+                const uint32_t clen = cloc[c].len;
+                const uint64_t at = x < clen ? locate(info.g, (c0 + c) * kChunk + x).addr : 0;
+                uint4 v = make_uint4(0, 0, 0, 0);
+                if (x < clen) {
+                    if (kFromSlots) v = load16_nt(cloc[c].slot + x);
+                    else v = x + 16 <= clen ? load16_nt(at) : load_partial(at, clen - x);
+                }
+                if (MODE == kModePack) store16(cloc[c].slot + x, v);
+                if (kFromSlots && x < clen) {
+                    if (x + 16 <= clen) store16_nt(at, v);
+                    else store_partial(at, v, clen - x);
+                }
+                stage(c, x, clen, v);
+            }
+            __syncthreads();
+            if (t < kHashers) hash_slice(step);
+            __syncthreads();
+        }
+    } else if constexpr (kSteps == 1) {
+        // Whole chunks in one step: nothing is prefetched, so a granule's
+        // place is read from LDS where it is used (the memory clobber keeps
+        // the compiler from holding all of them over the loads).
+        uint4 r[U];
+        uint64_t at[U];
+        uint32_t clen[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const ChunkLoc &l = cloc[(k * T + t) / LPS];
+            at[k] = (slot < l.split ? l.a1 : l.a2) + slot;
+            clen[k] = l.len;
+        }
+        load_granules<U>(at, clen, slot, ragged, r);
+        asm volatile("" ::: "memory");
 #pragma unroll
         for (int k = 0; k < U; ++k) {
             const uint32_t c = (k * T + t) / LPS;
             if (c < nv) {
-                const uint32_t x = step * SL + slot;
-                if (MODE == kModePack) {
-                    if (WB) store16(sa[k] + x, r[k]);
-                    else store16_nt(sa[k] + x, r[k]);
-                }
-                if (kFromSlots && x < gl[k]) {
-                    if (x + 16 <= gl[k]) store16_nt(runs_addr(k, x), r[k]);
-                    else store_partial(runs_addr(k, x), r[k], gl[k] - x);
-                }
-                *reinterpret_cast<uint4 *>(tile + c * kRow + slot) = r[k];
+                if (MODE == kModePack) store16(cloc[c].slot + slot, r[k]);
+                stage(c, slot, cloc[c].len, r[k]);
             }
         }
         __syncthreads();
-        if (step + 1 < kSteps) {
+        if (t < kHashers) hash_slice(0);
+        __syncthreads();
+    } else {
+        // This lane's granules: chunk (k*T + t) / LPS of each slice.
+        uint64_t ga[U], gb[U];  // pieces side: where the chunk's bytes lie (ChunkLoc)
+        uint64_t sa[U];         // slots side: the chunk's 4096-byte slot (0 if the group has no such chunk)
+        uint32_t gs[U], gl[U];
 #pragma unroll
-            for (int k = 0; k < U; ++k) r[k] = load_granule(k, (step + 1) * SL + slot);
+        for (int k = 0; k < U; ++k) {
+            const ChunkLoc l = cloc[(k * T + t) / LPS];
+            ga[k] = l.a1;
+            gb[k] = l.a2;
+            gs[k] = l.split;
+            gl[k] = l.len;
+            sa[k] = l.slot;
         }
-        if (hasher) {
-            const uint8_t *row = tile + ci * kRow;
-            const uint32_t s0 = step * (SL / 32);
-            const uint32_t ns = nst > s0 ? umin(SL / 32, nst - s0) : 0;
-#pragma unroll 8
-            for (uint32_t s = 0; s < ns; ++s) {
-                const uint2 d = *reinterpret_cast<const uint2 *>(row + 32 * s + 8 * q);
-                va = xround(va, ((uint64_t)d.y << 32) | d.x);
+        const auto piece_addr = [&](int k, uint32_t x) -> uint64_t { return (x < gs[k] ? ga[k] : gb[k]) + x; };
+        uint4 r[U];
+        const auto load_slice = [&](uint32_t x) {
+            uint64_t at[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) at[k] = kFromSlots ? sa[k] + x : piece_addr(k, x);
+            load_granules<U>(at, gl, x, ragged && !kFromSlots, r);
+            if (kFromSlots && ragged) {  // slots are whole 4096-byte granules, zero padded
+#pragma unroll
+                for (int k = 0; k < U; ++k)
+                    if (x < gl[k] && x + 16 > gl[k]) r[k] = load16_nt(at[k]);
             }
-            const uint32_t tp = nst * 32;  // tail start, 32-aligned, inside this slice if here
-            if (q == 0 && tp < len && tp >= step * SL && tp < (step + 1) * SL) {
-                const uint4 x = *reinterpret_cast<const uint4 *>(row + tp - step * SL);
-                const uint4 y = *reinterpret_cast<const uint4 *>(row + tp - step * SL + 16);
-                tw0 = ((uint64_t)x.y << 32) | x.x;
-                tw1 = ((uint64_t)x.w << 32) | x.z;
-                tw2 = ((uint64_t)y.y << 32) | y.x;
-                tw3 = ((uint64_t)y.w << 32) | y.z;
+        };
+        load_slice(slot);
+        for (uint32_t step = 0; step < kSteps; ++step) {
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const uint32_t c = (k * T + t) / LPS;
+                if (c < nv) {
+                    const uint32_t x = step * SL + slot;
+                    if (MODE == kModePack) {
+                        if (WB) store16(sa[k] + x, r[k]);
+                        else store16_nt(sa[k] + x, r[k]);
+                    }
+                    if (kFromSlots && x < gl[k]) {
+                        if (x + 16 <= gl[k]) store16_nt(piece_addr(k, x), r[k]);
+                        else store_partial(piece_addr(k, x), r[k], gl[k] - x);
+                    }
+                    stage(c, x, gl[k], r[k]);
+                }
             }
+            __syncthreads();
+            if (step + 1 < kSteps) load_slice((step + 1) * SL + slot);
+            if (t < kHashers) hash_slice(step);
+            __syncthreads();
         }
-        __syncthreads();
     }
 
-    if (t < 4 * CPW) {
-        // Accumulators 1-3 of a quad to its lane 0 (a quad never straddles
-        // a wavefront).
-        const uint64_t v2 = shfl64(va, (int)(t + 1) & 63);
-        const uint64_t v3 = shfl64(va, (int)(t + 2) & 63);
-        const uint64_t v4 = shfl64(va, (int)(t + 3) & 63);
+    uint64_t h = 0;
+    if (t < kHashers) {
+        // Each lane's own part of the merge, then the quad's four together
+        // (every lane of a quad ends with the same value).
+        const uint64_t rot = rotl(va, q == 0 ? 1 : q == 1 ? 7 : q == 2 ? 12 : 18);
+        uint64_t acc = rot + dpp64<0xB1>(rot);  // lanes 0+1, 2+3
+        acc += dpp64<0x4E>(acc);
+        const uint64_t m = xround(0, va);
+        acc = (acc ^ dpp64<0x00>(m)) * P1 + P4;
+        acc = (acc ^ dpp64<0x55>(m)) * P1 + P4;
+        acc = (acc ^ dpp64<0xAA>(m)) * P1 + P4;
+        acc = (acc ^ dpp64<0xFF>(m)) * P1 + P4;
+        if (len < 32) acc = P5;
+        acc += len;
+        // Tail: 8-byte lanes, one 4-byte lane, single bytes (offsets
+        // relative to the tail start).
+        uint32_t o = 0;
+        const uint32_t rem = len - nst * 32;
+        for (; rem - o >= 8; o += 8) {
+            acc ^= xround(0, sel4(tw0, tw1, tw2, tw3, o >> 3));
+            acc = rotl(acc, 27) * P1 + P4;
+        }
+        if (rem - o >= 4) {
+            acc ^= (uint64_t)(uint32_t)sel4(tw0, tw1, tw2, tw3, o >> 3) * P1;
+            acc = rotl(acc, 23) * P2 + P3;
+            o += 4;
+        }
+        for (; o < rem; ++o) {
+            const uint64_t byte = (sel4(tw0, tw1, tw2, tw3, o >> 3) >> (8 * (o & 7))) & 0xFF;
+            acc ^= byte * P5;
+            acc = rotl(acc, 11) * P1;
+        }
+        h = avalanche(acc);
         if (hasher && q == 0) {
-            uint64_t acc;
-            if (len >= 32) {
-                acc = rotl(va, 1) + rotl(v2, 7) + rotl(v3, 12) + rotl(v4, 18);
-                acc = xmerge(acc, va);
-                acc = xmerge(acc, v2);
-                acc = xmerge(acc, v3);
-                acc = xmerge(acc, v4);
-            } else {
-                acc = P5;
-            }
-            acc += len;
-            // Tail: 8-byte lanes, one 4-byte lane, single bytes (offsets
-            // relative to the tail start).
-            uint32_t o = 0;
-            const uint32_t rem = len - nst * 32;
-            for (; rem - o >= 8; o += 8) {
-                acc ^= xround(0, sel4(tw0, tw1, tw2, tw3, o >> 3));
-                acc = rotl(acc, 27) * P1 + P4;
-            }
-            if (rem - o >= 4) {
-                acc ^= (uint64_t)(uint32_t)sel4(tw0, tw1, tw2, tw3, o >> 3) * P1;
-                acc = rotl(acc, 23) * P2 + P3;
-                o += 4;
-            }
-            for (; o < rem; ++o) {
-                const uint64_t byte = (sel4(tw0, tw1, tw2, tw3, o >> 3) >> (8 * (o & 7))) & 0xFF;
-                acc ^= byte * P5;
-                acc = rotl(acc, 11) * P1;
-            }
-            const uint64_t h = avalanche(acc);
-            const uint64_t i = c0 + ci;
-            if (jb.hash_dst[0]) ((g_u64 *)jb.hash_dst[0])[i] = h;
-            if (jb.hash_dst[1]) ((g_u64 *)jb.hash_dst[1])[i] = h;
-            leaves[ci] = h;
+            if (info.hash[0]) ((g_u64 *)info.hash[0])[i] = h;
+            if (info.hash[1]) ((g_u64 *)info.hash[1])[i] = h;
             if (MODE == kModeDiff) {
-                const bool d = i >= jb.parent_chunks || ((const g_u64 *)jb.parent_hash)[i] != h;
+                const bool d = !compare || want != h;
                 dflag[ci] = d ? 1u : 0u;
-                if (!d && jb.manifest) ((g_u64 *)jb.manifest)[i] = parent_loc;
+                if (!d && info.manifest) ((g_u64 *)info.manifest)[i] = parent_loc;
             }
-            if (MODE == kModeVerify) dflag[ci] = ((const g_u64 *)jb.parent_hash)[i] != h ? 1u : 0u;
+            if (MODE == kModeVerify) dflag[ci] = want != h ? 1u : 0u;
+        }
+        // The tile's Merkle node (an aligned subtree): 16 chunks per
+        // wavefront, chunk c of it in lane 4c, then the wavefronts' roots.
+        if (nodes) {
+            const uint32_t wave = t >> 6, mine = nv > 16 * wave ? (uint32_t)umin(16, nv - 16 * wave) : 0;
+            const uint64_t root = wave_merkle<4, CPW == 8 ? 3 : 4>(h, mine);
+            if (CPW == 8) {
+                if (t == 0) nodes[tile_id] = root;
+            } else if ((t & 63) == 0) {
+                partial[wave] = root;
+            }
         }
     }
+    if (CPW == 8 && MODE != kModeDiff) return;
     __syncthreads();
     if (t < 64) {
-        const uint64_t v = t < nv ? leaves[t] : 0;
-        const uint64_t root = wave_merkle(v, nv);
-        if (t == 0 && nodes) nodes[tile_id] = root;  // the tile's Merkle node (an aligned subtree)
+        if (CPW != 8 && nodes) {
+            const uint64_t root = wave_merkle<1, 2>(partial[t & 3], (nv + 15) / 16);
+            if (t == 0) nodes[tile_id] = root;
+        }
         if (MODE == kModeDiff || MODE == kModeVerify) {
             // Bit c of group G's mask = chunk c of the group; a sub-tile
             // writes its 8 bits as byte (tile % 8) of the little-endian word.
-            const uint64_t mask = __ballot(t < nv && dflag[t] != 0);
+            const uint64_t mask = __ballot(t < nv && dflag[t & (CPW - 1)] != 0);
             if (t == 0 && flag_mask) {
                 if (kTiles == 1) flag_mask[G] = mask;
                 else ((g_u8 *)flag_mask)[G * kTiles + tile_id % kTiles] = (uint8_t)mask;
@@ -570,9 +908,18 @@ __device__ __forceinline__ void hash_tile(const Tab &tab, uint64_t *__restrict__
     }
 }
 
+// Wavefronts per SIMD a tile kernel's registers must leave room for.
+constexpr int tile_waves(int MODE, int T, int CPW)
+{
+    if (CPW == 8) return 4;  // four 256-lane workgroups a CU, as many as LDS holds
+    if (MODE == kModePack || MODE == kModeVerify) return 4;
+    return T == 1024 ? 8 : 3;
+}
+
 template <class Tab, int MODE, int T, int SL, int CPW, bool WB>
-__global__ __launch_bounds__(T) void k_hash(const Tab tab, uint64_t *__restrict__ nodes,
-                                            uint64_t *__restrict__ flag_mask, uint64_t arena_base)
+__global__ __launch_bounds__(T, tile_waves(MODE, T, CPW)) void k_hash(const Tab tab, uint64_t *__restrict__ nodes,
+                                                                      uint64_t *__restrict__ flag_mask,
+                                                                      uint64_t arena_base)
 {
     hash_tile<Tab, MODE, T, SL, CPW, false, WB>(tab, nodes, flag_mask, arena_base, Stagger{0, 0});
 }
@@ -626,7 +973,7 @@ __device__ uint64_t reduce_list(const uint64_t *src, uint64_t m, uint64_t *sa, u
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     if (!cnt[u]) continue;
-                    const uint64_t r = wave_merkle(v[u], cnt[u]);
+                    const uint64_t r = wave_merkle<1, 6>(v[u], cnt[u]);
                     if (lane == 0) scratch[k][blk0 + u * NW] = r;
                 }
             }
@@ -642,7 +989,7 @@ __device__ uint64_t reduce_list(const uint64_t *src, uint64_t m, uint64_t *sa, u
             for (uint64_t blk = wave; blk < nb; blk += NW) {
                 const uint32_t cnt = (uint32_t)umin(64, m - 64 * blk);
                 const uint64_t v = lane < cnt ? lds[64 * blk + lane] : 0;
-                const uint64_t r = wave_merkle(v, cnt);
+                const uint64_t r = wave_merkle<1, 6>(v, cnt);
                 if (lane == 0) lds2[blk] = r;
             }
             __syncthreads();
@@ -651,7 +998,7 @@ __device__ uint64_t reduce_list(const uint64_t *src, uint64_t m, uint64_t *sa, u
         }
         if (wave == 0) {
             const uint64_t v = lane < m ? ls[lane] : 0;
-            root = wave_merkle(v, (uint32_t)m);
+            root = wave_merkle<1, 6>(v, (uint32_t)m);
         }
     }
     __syncthreads();
@@ -678,93 +1025,137 @@ __global__ __launch_bounds__(NT) void k_merkle(const MerkleList *__restrict__ li
     }
 }
 
-// Promote-odd Merkle root of ls[0, m) already in LDS (m <= 4096), computed
-// by the workgroup (NT lanes); valid in thread 0.  Ends with a barrier.
-template <int NT>
-__device__ uint64_t reduce_lds(const uint64_t *ls, uint64_t m, uint64_t *lds2)
+// The Merkle lists of a job in the argument tables, as items: aligned blocks
+// of 64 values of one buffer's list, numbered through the buffers.  Lane l of
+// a wavefront holds the lists of buffers l and 64 + l: their counts, and the
+// items up to and including theirs.  pre: the lists' first level is done, so
+// each holds a value per block, at the list's own offset (k_merkle_items).
+struct ArgItems {
+    uint64_t begin[2], count[2];
+    uint32_t incl[2], items[2];
+    uint32_t total;
+    __device__ __forceinline__ ArgItems(const ArgTables &t, uint32_t tiles, bool pre)
+    {
+        const uint32_t lane = threadIdx.x & 63, per = kGroupChunks / tiles;
+        uint32_t base = 0;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t j = h * 64 + lane;
+            const ArgBuf &b = t.bufs[j < kArgBufs ? j : 0];
+            const uint64_t n = j < t.nbuf ? chunks_of(b.nbytes) : 0;
+            begin[h] = (uint64_t)b.group_begin * tiles;
+            count[h] = (n + per - 1) / per;
+            if (pre) count[h] = (count[h] + 63) / 64;
+            items[h] = (uint32_t)((count[h] + 63) / 64);
+            incl[h] = base + wave_incl_scan(items[h]);
+            base = lane_word(incl[h], 63);
+        }
+        total = base;
+    }
+    // Item i < total: where its list begins (the first one whose items reach
+    // past i), the values it holds and where they lie.
+    __device__ __forceinline__ void item(uint32_t i, uint64_t &at, uint32_t &n, uint64_t &list) const
+    {
+        const uint64_t a = __ballot(incl[0] > i), b = __ballot(incl[1] > i);
+        const uint32_t l = (uint32_t)__builtin_ctzll(a ? a : b);
+        list = a ? lane_word(begin[0], l) : lane_word(begin[1], l);
+        const uint64_t cnt = a ? lane_word(count[0], l) : lane_word(count[1], l);
+        const uint32_t first = a ? lane_word(incl[0] - items[0], l) : lane_word(incl[1] - items[1], l);
+        const uint64_t off = 64ull * (i - first);
+        at = list + off;
+        n = (uint32_t)umin(64, cnt - off);
+    }
+};
+
+// Every root of a job in the argument tables, by one workgroup of NT lanes:
+// its wavefronts share the items of all lists (four in flight each), then the
+// lists themselves, then wavefront 0 takes the session's.  Lists one after
+// another, each behind barriers, took 17 us for a step's sixteen.  ITEMS:
+// room for the items' roots.  Ends with a barrier.
+template <int NT, int ITEMS>
+__device__ void merkle_args(const ArgTables &tab, uint32_t tiles, const uint64_t *in, bool pre)
 {
     constexpr uint32_t NW = NT / 64;
-    const uint32_t t = threadIdx.x, wave = t >> 6, lane = t & 63;
-    uint64_t root = 0;
-    if (m == 0) {
-        root = empty_hash();
-    } else {
-        if (m > 64) {
-            const uint64_t nb = (m + 63) / 64;
-            for (uint64_t blk = wave; blk < nb; blk += NW) {
-                const uint32_t cnt = (uint32_t)umin(64, m - 64 * blk);
-                const uint64_t v = lane < cnt ? ls[64 * blk + lane] : 0;
-                const uint64_t r = wave_merkle(v, cnt);
-                if (lane == 0) lds2[blk] = r;
-            }
-            __syncthreads();
-            ls = lds2;
-            m = nb;
-        }
-        if (wave == 0) root = wave_merkle(lane < m ? ls[lane] : 0, (uint32_t)m);
-    }
-    __syncthreads();
-    return root;
-}
-
-// The lists of a small job, reduced by one workgroup of NT lanes: every
-// buffer list, then every session list over the buffer roots just computed
-// (kept in LDS).  Buffer lists that follow each other in `in` and hold at
-// most 4096 values together (a job's buffers, the usual case) are loaded
-// into LDS in one pass, so the lists wait on one round trip to memory, not
-// one each.  Ends with a barrier.
-template <int NT>
-__device__ void merkle_lists(const ArgLists &L, const uint64_t *in, uint64_t *sa, uint64_t *sb, uint64_t *lds,
-                             uint64_t *lds2, uint64_t *roots, bool pre = false)
-{
-    bool one_pass = L.nbuf_lists > 0;
-    const uint64_t lo = one_pass ? L.lists[0].begin : 0;
-    uint64_t hi = lo;
-    for (uint32_t j = 0; j < L.nbuf_lists; ++j) {
-        one_pass = one_pass && L.lists[j].begin == hi;
-        hi = L.lists[j].begin + L.lists[j].count;
-    }
-    one_pass = one_pass && hi - lo <= 4096;
-    if (one_pass) {
-        for (uint64_t j = threadIdx.x; j < hi - lo; j += NT) lds[j] = in[lo + j];
-        __syncthreads();
-    }
-    for (uint32_t j = 0; j < L.nbuf_lists; ++j) {
-        const MerkleList &Lst = L.lists[j];
-        const uint64_t root =
-            one_pass ? reduce_lds<NT>(lds + (Lst.begin - lo), Lst.count, lds2)
-                     : reduce_list<NT>(in + Lst.begin, Lst.count, sa + Lst.begin, sb + Lst.begin, lds, lds2, pre);
-        if (threadIdx.x == 0) {
-            roots[j] = root;
-            if (Lst.dst[0]) *(g_u64 *)Lst.dst[0] = root;
-            if (Lst.dst[1]) *(g_u64 *)Lst.dst[1] = root;
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x < 64) {
-        const uint32_t lane = threadIdx.x;
-        for (uint32_t j = L.nbuf_lists; j < L.nlists; ++j) {
-            const MerkleList &Lst = L.lists[j];
-            const uint32_t cnt = (uint32_t)Lst.count;
-            const uint64_t v = lane < cnt ? roots[Lst.begin + lane] : 0;
-            const uint64_t root = cnt ? wave_merkle(v, cnt) : empty_hash();
-            if (lane == 0) {
-                if (Lst.dst[0]) *(g_u64 *)Lst.dst[0] = root;
-                if (Lst.dst[1]) *(g_u64 *)Lst.dst[1] = root;
-            }
-        }
-    }
-    __syncthreads();
-}
-
-// One workgroup for a small job's Merkle lists.
-__global__ __launch_bounds__(1024) void k_merkle_small(const ArgLists L, const uint64_t *__restrict__ in,
-                                                       uint64_t *__restrict__ sa, uint64_t *__restrict__ sb, bool pre)
-{
-    __shared__ uint64_t lds[4096];
-    __shared__ uint64_t lds2[64];
+    __shared__ uint64_t part[ITEMS];
     __shared__ uint64_t roots[kArgBufs];
-    merkle_lists<1024>(L, in, sa, sb, lds, lds2, roots, pre);
+    const uint32_t t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+    const ArgItems it(tab, tiles, pre);
+    for (uint32_t i0 = wave; i0 < it.total; i0 += 4 * NW) {
+        uint64_t v[4];
+        uint32_t n[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            n[u] = 0;
+            v[u] = 0;
+            if (i0 + u * NW < it.total) {
+                uint64_t at, list;
+                it.item(i0 + u * NW, at, n[u], list);
+                if (lane < n[u]) v[u] = in[at + lane];
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        const uint64_t r = wave_merkle4(v, n[0], n[1], n[2], n[3]);
+        if (lane < 4 && i0 + lane * NW < it.total) part[i0 + lane * NW] = r;
+    }
+    __syncthreads();
+    for (uint32_t b = wave; b < tab.nbuf; b += NW) {
+        const uint32_t l = b & 63;
+        uint32_t n = b < 64 ? lane_word(it.items[0], l) : lane_word(it.items[1], l);
+        const uint64_t *p = part + (b < 64 ? lane_word(it.incl[0], l) : lane_word(it.incl[1], l)) - n;
+        uint64_t v = empty_hash();
+        if (n <= 64) {
+            if (lane < n) v = p[lane];
+        } else {
+            const uint32_t nb = (n + 63) / 64;
+            for (uint32_t k = 0; k < nb; ++k) {
+                const uint32_t c = min(64u, n - 64 * k);
+                const uint64_t r = lane_word(wave_merkle<1, 6>(lane < c ? p[64 * k + lane] : 0, c), 0);
+                if (lane == k) v = r;
+            }
+            n = nb;
+        }
+        v = wave_merkle<1, 6>(v, n);
+        if (lane == 0) {
+            roots[b] = v;
+            if (tab.root[0]) ((g_u64 *)tab.root[0])[b] = v;
+            if (tab.root[1]) ((g_u64 *)tab.root[1])[b] = v;
+        }
+    }
+    __syncthreads();
+    if (wave == 0 && (tab.sroot[0] || tab.sroot[1])) {
+        const uint32_t n = tab.nbuf;
+        uint64_t v = n == 0 ? empty_hash() : wave_merkle<1, 6>(lane < n ? roots[lane] : 0, min(n, 64u));
+        if (n > 64) v = node_hash(v, wave_merkle<1, 6>(64 + lane < n ? roots[64 + lane] : 0, n - 64));
+        if (lane == 0) {
+            if (tab.sroot[0]) *(g_u64 *)tab.sroot[0] = v;
+            if (tab.sroot[1]) *(g_u64 *)tab.sroot[1] = v;
+        }
+    }
+    __syncthreads();
+}
+
+// Room for the items of any job: the most groups a job may have, their first
+// level done, in lists that each end in a partial item.
+constexpr int kMerkleItems = 4352;
+__global__ __launch_bounds__(1024) void k_merkle_args(const ArgTables tab, uint32_t tiles,
+                                                      const uint64_t *__restrict__ in, bool pre)
+{
+    merkle_args<1024, kMerkleItems>(tab, tiles, in, pre);
+}
+
+// Grid-wide first level of a job's lists: wavefront w reduces item w into
+// out[begin + block], where the list's values then start.
+__global__ __launch_bounds__(256) void k_merkle_items(const ArgTables tab, uint32_t tiles,
+                                                      const uint64_t *__restrict__ in, uint64_t *__restrict__ out)
+{
+    const ArgItems it(tab, tiles, false);
+    const uint32_t w = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    if (w >= it.total) return;
+    uint64_t at, list;
+    uint32_t n;
+    it.item(w, at, n, list);
+    const uint64_t r = wave_merkle<1, 6>(lane < n ? in[at + lane] : 0, n);
+    if (lane == 0) out[list + (at - list) / 64] = r;
 }
 
 // Grid-wide first level of long Merkle lists (LongLists): wavefront w
@@ -781,7 +1172,7 @@ __global__ __launch_bounds__(256) void k_merkle_blocks(const LongLists L, const 
     const uint64_t blk = w - L.block_begin[j];
     const uint32_t cnt = (uint32_t)umin(64, L.count[j] - 64 * blk);
     const uint64_t v = lane < cnt ? in[L.begin[j] + 64 * blk + lane] : 0;
-    const uint64_t r = wave_merkle(v, cnt);
+    const uint64_t r = wave_merkle<1, 6>(v, cnt);
     if (lane == 0) sa[L.begin[j] + blk] = r;
 }
 
@@ -793,10 +1184,10 @@ __global__ __launch_bounds__(256) void k_merkle_blocks(const LongLists L, const 
 // without the hash and the LDS staging, in a shape of its own (512 lanes and
 // 1 KiB slices for whole groups, measured faster for copies than the fused
 // kernel's 1024 lanes and 512-byte slices).
-//   PACK:    the buffer's runs -> the chunk slots of the snapshot; a partial
+//   PACK:    the buffer's bytes -> the chunk slots of the snapshot; a partial
 //            last chunk is zero-padded to the end of its slot.
 //   !PACK:   the chunk slots (contiguous, or per chunk through a manifest of
-//            arena offsets) -> the destination buffer's runs; only logical
+//            arena offsets) -> the destination buffer; only logical
 //            bytes are written.
 template <class Tab, bool PACK, int T, int SL, int CPW>
 __global__ __launch_bounds__(T) void k_copy(const Tab tab, uint64_t arena_base, bool wb)
@@ -805,46 +1196,44 @@ __global__ __launch_bounds__(T) void k_copy(const Tab tab, uint64_t arena_base, 
     constexpr int U = CPW * SL / 16 / T;
     constexpr uint32_t kTiles = kGroupChunks / CPW;
     static_assert(U >= 1 && T % LPS == 0 && kGroupChunks % CPW == 0, "tile shape");
-    __shared__ ChunkLoc cloc[kGroupChunks];
+    __shared__ ChunkLoc cloc[CPW];
+    __shared__ TileInfo info;
     const uint32_t tile_id = xcd_tile();
-    const uint64_t G = tile_id / kTiles;
-    const GroupRef gr = group_ref(tab, G);
-    const JobBuf &jb = tab.bufs[gr.buf];
-    const Run *runs = tab.runs;
     const uint32_t t = threadIdx.x;
-    const uint64_t c0 = (G - jb.group_begin) * kGroupChunks + (tile_id % kTiles) * CPW;
-    if (c0 >= jb.nchunks) return;  // a buffer's last group may end before this tile
-    const uint32_t nv = (uint32_t)umin(CPW, jb.nchunks - c0);
-    const uint32_t run_begin = jb.run_begin, run_count = jb.run_count;
-    const g_u64 *man = (const g_u64 *)jb.manifest;
-    chunk_table(jb, runs, gr.run, c0, nv, cloc);
-    __syncthreads();
-
+    tile_setup<PACK ? kModePack : kModeVerify, CPW>(tab, tile_id / kTiles, tile_id % kTiles, arena_base, &info, cloc);
+    if (__builtin_amdgcn_readfirstlane(info.nv) == 0) return;  // a buffer's last group may end before this tile
     const uint32_t slot = (t % LPS) * 16;
+    if (__builtin_amdgcn_readfirstlane(info.many)) {
+        // A tile with a chunk of more than two pieces, one granule at a time
+        // (see hash_tile).
+        const uint32_t nv = info.nv;
+        for (uint32_t g = t; g < nv * (kChunk / 16); g += T) {
+            const uint32_t c = g / (kChunk / 16), x = g % (kChunk / 16) * 16, clen = cloc[c].len;
+            const uint64_t at = x < clen ? locate(info.g, (info.c0 + c) * kChunk + x).addr : 0;
+            if (PACK) {
+                uint4 v = make_uint4(0, 0, 0, 0);
+                if (x < clen) v = x + 16 <= clen ? load16_nt(at) : load_partial(at, clen - x);
+                store16(cloc[c].slot + x, v);
+            } else if (x < clen) {
+                const uint4 v = load16_nt(cloc[c].slot + x);
+                if (x + 16 <= clen) store16_nt(at, v);
+                else store_partial(at, v, clen - x);
+            }
+        }
+        return;
+    }
     uint64_t ra[U], rb[U], sa[U];
     uint32_t rs[U], gl[U];
 #pragma unroll
     for (int k = 0; k < U; ++k) {
-        const uint32_t c = (k * T + t) / LPS;
-        const ChunkLoc l = c < nv ? cloc[c] : ChunkLoc{0, 0, 0, 0};
+        const ChunkLoc l = cloc[(k * T + t) / LPS];
         ra[k] = l.a1;
         rb[k] = l.a2;
         rs[k] = l.split;
         gl[k] = l.len;
-        sa[k] = c < nv ? (PACK || !man ? jb.payload + (c0 + c) * kChunk : arena_base + man[c0 + c]) : 0;
+        sa[k] = l.slot;
     }
-    auto runs_addr = [&](int k, uint32_t x) -> uint64_t {
-        const uint32_t c = (k * T + t) / LPS;
-        return ra[k] ? (x < rs[k] ? ra[k] : rb[k]) + x : phys_addr(runs, run_begin, run_count, (c0 + c) * kChunk + x);
-    };
-    auto load = [&](int k, uint32_t x) -> uint4 {
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (x < gl[k]) {
-            if (PACK) v = x + 16 <= gl[k] ? load16_nt(runs_addr(k, x)) : load_partial(runs_addr(k, x), gl[k] - x);
-            else v = load16_nt(sa[k] + x);  // slots are whole 4096-byte granules
-        }
-        return v;
-    };
+    auto piece_addr = [&](int k, uint32_t x) -> uint64_t { return (x < rs[k] ? ra[k] : rb[k]) + x; };
     // The lanes move the tile in lockstep steps (a barrier per step); the
     // next step's loads are issued before this step's stores.  Chunk c moves
     // its slices in an order rotated by c and the tile index, so that a
@@ -857,13 +1246,27 @@ __global__ __launch_bounds__(T) void k_copy(const Tab tab, uint64_t arena_base, 
         const uint32_t c = (k * T + t) / LPS;
         return ((step + c + tile_id) % kSteps) * SL + slot;
     };
+    const bool ragged = __builtin_amdgcn_readfirstlane(info.ragged);
+    // Whole granules first, as load_granules (each chunk at its own offset).
+    const auto load = [&](uint4 (&v)[U], uint32_t step) {
 #pragma unroll
-    for (int k = 0; k < U; ++k) v[k] = load(k, off(k, 0));
-    for (uint32_t step = 0; step < kSteps; ++step) {
-        if (step + 1 < kSteps) {
-#pragma unroll
-            for (int k = 0; k < U; ++k) n[k] = load(k, off(k, step + 1));
+        for (int k = 0; k < U; ++k) {
+            const uint32_t x = off(k, step);
+            v[k] = make_uint4(0, 0, 0, 0);
+            if (PACK ? x + 16 <= gl[k] : x < gl[k])  // slots are whole 4096-byte granules
+                v[k] = load16_nt(PACK ? piece_addr(k, x) : sa[k] + x);
         }
+        if (PACK && ragged) {
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const uint32_t x = off(k, step);
+                if (x < gl[k] && x + 16 > gl[k]) v[k] = load_partial(piece_addr(k, x), gl[k] - x);
+            }
+        }
+    };
+    load(v, 0);
+    for (uint32_t step = 0; step < kSteps; ++step) {
+        if (step + 1 < kSteps) load(n, step + 1);
 #pragma unroll
         for (int k = 0; k < U; ++k) {
             const uint32_t x = off(k, step);
@@ -873,8 +1276,8 @@ __global__ __launch_bounds__(T) void k_copy(const Tab tab, uint64_t arena_base, 
                     else store16_nt(sa[k] + x, v[k]);
                 }
             } else if (x < gl[k]) {
-                if (x + 16 <= gl[k]) store16_nt(runs_addr(k, x), v[k]);
-                else store_partial(runs_addr(k, x), v[k], gl[k] - x);
+                if (x + 16 <= gl[k]) store16_nt(piece_addr(k, x), v[k]);
+                else store_partial(piece_addr(k, x), v[k], gl[k] - x);
             }
         }
         __syncthreads();
@@ -884,23 +1287,6 @@ __global__ __launch_bounds__(T) void k_copy(const Tab tab, uint64_t arena_base, 
 }
 
 // ---------------------------------------------------------------- incremental
-
-// Inclusive prefix sum across the 64 lanes of a wavefront, in DPP moves (no
-// LDS round trips): shifts by 1, 2, 4 and 8 lanes within each row of 16
-// lanes, then row 0's total (lane 15) into row 1 and row 2's into row 3
-// (row_bcast:15), then rows 0-1's total (lane 31) into rows 2 and 3
-// (row_bcast:31).  A lane whose source lies outside its row, or a row the
-// row mask leaves out, adds 0 (the `old` operand).
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x)
-{
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);  // row_shr:1
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);  // row_shr:2
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);  // row_shr:4
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);  // row_shr:8
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);  // row_bcast:15
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);  // row_bcast:31
-    return x;
-}
 
 // A scan's entry j: the number of set bits of the 64-bit dirty mask of
 // group j of an incremental checkpoint.
@@ -979,7 +1365,7 @@ __global__ __launch_bounds__(1024) void k_scan(const Count counts, uint64_t n, u
 // wavefront scans, then one over the 16 wavefront totals (counts stay below
 // 2^32).  Writes offsets[] (LDS or global) and returns the total in every
 // thread.  Ends with a barrier.
-__device__ uint64_t scan_masks_small(const uint64_t (&mk)[4], uint64_t ngroups, uint64_t *offsets, uint32_t *wsum)
+__device__ __forceinline__ uint64_t scan_masks_small(const uint64_t (&mk)[4], uint64_t ngroups, uint64_t *offsets, uint32_t *wsum)
 {
     const uint32_t t = threadIdx.x, wave = t >> 6, lane = t & 63;
     uint32_t c[4], sum = 0;
@@ -1009,21 +1395,20 @@ __device__ uint64_t scan_masks_small(const uint64_t (&mk)[4], uint64_t ngroups, 
     return total;
 }
 
-// Moves chunk i of buffer jb (its logical bytes, zero-padded to 4096) to
+// Moves chunk i of a buffer (its logical bytes, zero-padded to 4096) to
 // device address dst: the 64 lanes of a wavefront, 64 bytes each, four
 // 16-byte loads in flight per lane.
-template <class Tab>
-__device__ __forceinline__ void copy_chunk(const Tab &tab, const JobBuf &jb, uint64_t i, uint64_t dst, uint32_t lane)
+__device__ __forceinline__ void copy_chunk(const Geom &g, uint64_t i, uint64_t dst, uint32_t lane)
 {
     const uint64_t cb = i * kChunk;
-    const uint64_t len = umin(kChunk, jb.nbytes - cb);
+    const uint64_t len = umin(kChunk, g.nbytes - cb);
     uint4 v[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const uint32_t x = (k * 64 + lane) * 16;
         v[k] = make_uint4(0, 0, 0, 0);
         if (x < len) {
-            const uint64_t a = phys_addr(tab.runs, jb.run_begin, jb.run_count, cb + x);
+            const uint64_t a = locate(g, cb + x).addr;
             v[k] = x + 16 <= len ? load16(a) : load_partial(a, (uint32_t)(len - x));
         }
     }
@@ -1047,20 +1432,16 @@ __device__ __forceinline__ void copy_chunk(const Tab &tab, const JobBuf &jb, uin
 // Slots therefore follow (buffer, chunk) order, as k_place_dirty assigns
 // them.  Lane 0 enters the slot in the manifest (clean chunks' entries
 // were written by the diff tiles) and the wavefront copies the chunk.
-__global__ __launch_bounds__(1024) void k_merkle_scan_place(const ArgLists L, const uint64_t *__restrict__ nodes,
-                                                            uint64_t *__restrict__ sa, uint64_t *__restrict__ sb,
-                                                            const ArgTables tab, uint64_t ngroups,
+__global__ __launch_bounds__(1024) void k_merkle_scan_place(const ArgTables tab, uint32_t tiles,
+                                                            const uint64_t *__restrict__ nodes, uint64_t ngroups,
                                                             const uint64_t *__restrict__ dirty_mask,
                                                             const SlotBump bump, uint64_t *__restrict__ total,
                                                             uint64_t arena_base)
 {
-    __shared__ uint64_t lds[4096];  // Merkle values (workgroup 0), then the groups' offsets
+    __shared__ uint64_t offs[kScanCompactMaxGroups];
     __shared__ uint64_t msk[kScanCompactMaxGroups];
-    __shared__ uint64_t lds2[64];
-    __shared__ uint64_t roots[kArgBufs];
     __shared__ uint32_t wsum[33];
-    static_assert(kScanCompactMaxGroups <= 4 * 1024 && kScanCompactMaxGroups <= 4096,
-                  "four dirty masks per thread, offsets in the Merkle LDS array");
+    static_assert(kScanCompactMaxGroups <= 4 * 1024, "four dirty masks per thread");
     const uint32_t t = threadIdx.x;
     uint64_t mk[4];
 #pragma unroll
@@ -1068,8 +1449,8 @@ __global__ __launch_bounds__(1024) void k_merkle_scan_place(const ArgLists L, co
     const uint64_t top = !bump.bump ? 0 : bump.reset ? bump.reset : *bump.bump;
     if (blockIdx.x == 0) {
         // The masks' round trip to memory overlaps the Merkle reduction.
-        merkle_lists<1024>(L, nodes, sa, sb, lds, lds2, roots);
-        const uint64_t count = scan_masks_small(mk, ngroups, lds, wsum);
+        merkle_args<1024, kScanCompactMaxGroups / 64 + kArgBufs>(tab, tiles, nodes, false);
+        const uint64_t count = scan_masks_small(mk, ngroups, offs, wsum);
         if (t == 0) *total = count;
         if (t == 1023) place_slots(bump, count, top);
         return;
@@ -1077,58 +1458,61 @@ __global__ __launch_bounds__(1024) void k_merkle_scan_place(const ArgLists L, co
 #pragma unroll
     for (int k = 0; k < 4; ++k)
         if (4 * t + k < ngroups) msk[4 * t + k] = mk[k];
-    const uint64_t count = scan_masks_small(mk, ngroups, lds, wsum);  // ends with a barrier: msk is visible
+    const ArgLanes lanes(tab);
+    const uint64_t count = scan_masks_small(mk, ngroups, offs, wsum);  // ends with a barrier: msk is visible
     const uint32_t lane = t & 63;
     const uint64_t stride = (uint64_t)(gridDim.x - 1) * 16;
-    for (uint64_t s = (uint64_t)(blockIdx.x - 1) * 16 + (t >> 6); s < count; s += stride) {
-        uint32_t lo = 0, hi = (uint32_t)ngroups;  // lds[lo] <= s (lds[0] = 0)
+    for (uint64_t s = (uint64_t)(blockIdx.x - 1) * 16 + __builtin_amdgcn_readfirstlane(t >> 6); s < count; s += stride) {
+        uint32_t lo = 0, hi = (uint32_t)ngroups;  // offs[lo] <= s (offs[0] = 0)
         while (hi - lo > 1) {
             const uint32_t mid = (lo + hi) >> 1;
-            if (lds[mid] <= s) lo = mid; else hi = mid;
+            if (offs[mid] <= s) lo = mid; else hi = mid;
         }
+        lo = __builtin_amdgcn_readfirstlane(lo);
         const uint64_t m = msk[lo];
-        const uint32_t k = (uint32_t)(s - lds[lo]);
+        const uint32_t k = (uint32_t)(s - offs[lo]);
         const uint32_t below = (uint32_t)__popcll(lane ? m & ((1ULL << lane) - 1) : 0);
         const uint32_t c = (uint32_t)__ffsll((unsigned long long)__ballot(((m >> lane) & 1) && below == k)) - 1;
-        const JobBuf &jb = tab.bufs[buf_index(tab, lo)];
-        const uint64_t i = (lo - jb.group_begin) * kGroupChunks + c;
+        const uint32_t b = lanes.find(lo);
+        const ArgBuf buf = lanes.buf(b);
+        const uint64_t i = (uint64_t)(lo - buf.group_begin) * kGroupChunks + c;
         const uint64_t slot_off = top - (s + 1) * kChunk;  // arena offset
-        if (lane == 0) ((g_u64 *)jb.manifest)[i] = slot_off;
-        copy_chunk(tab, jb, i, arena_base + slot_off, lane);
+        if (lane == 0) ((g_u64 *)tab.manifest)[buf.chunk_begin + i] = slot_off;
+        copy_chunk(lanes.geom(b, buf), i, arena_base + slot_off, lane);
     }
 }
 
 // Slot assignment and dirty copy in one launch (jobs with device tables,
 // or whose slots the host placed, after the scan of the dirty masks): one
-// wavefront per chunk, four per 256-lane workgroup, striding over the job's
-// chunk positions (64 per group) so that a large job launches no more than
-// kPlaceBlocks workgroups.  The wavefront of a dirty chunk takes its slot
-// (below the payload top in *top_word) from its group's scanned offset and
-// the set bits of the mask below it, as k_merkle_scan_place; lane 0 enters the
-// slot in the manifest and all 64 lanes copy the chunk into it, 64 bytes per
-// lane, zero-padding a partial chunk.  A clean chunk costs its wavefront one
-// (cached) mask load: the diff tiles entered it in the manifest.
-constexpr uint64_t kPlaceBlocks = 2048;  // 8192 wavefronts: eight workgroups per CU
+// 256-lane workgroup per group, striding over the job so that a large one
+// launches no more than kPlaceBlocks.  A clean group costs its workgroup one
+// (cached) mask load; the dirty chunks of a group are dealt to its four
+// wavefronts.  The r-th of them takes the group's scanned offset + r as its
+// slot (below the payload top in *top_word), as k_merkle_scan_place; lane 0
+// enters the slot in the manifest and all 64 lanes copy the chunk into it,
+// 64 bytes per lane, zero-padding a partial chunk.  (The diff tiles entered
+// the clean chunks.)  A wavefront per chunk position, dirty or not, took
+// 81 us for 131,072 positions of which 576 were dirty.
+constexpr uint64_t kPlaceBlocks = 2048;
 template <class Tab>
-__global__ __launch_bounds__(256) void k_place_dirty(const Tab tab, uint64_t npos, const uint64_t *__restrict__ dirty_mask,
+__global__ __launch_bounds__(256) void k_place_dirty(const Tab tab, uint64_t ngroups, const uint64_t *__restrict__ dirty_mask,
                                                      const uint64_t *__restrict__ offsets,
                                                      const uint64_t *__restrict__ top_word, uint64_t arena_base)
 {
-    const uint32_t lane = threadIdx.x & 63;
-    const uint64_t stride = (uint64_t)gridDim.x * 4;
-    for (uint64_t gc = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6); gc < npos; gc += stride) {
-        const uint64_t G = gc / kGroupChunks;
-        const uint32_t c = (uint32_t)(gc % kGroupChunks);
-        const uint64_t mask = dirty_mask[G];
-        if (!((mask >> c) & 1)) continue;
-        const JobBuf &jb = tab.bufs[buf_index(tab, G)];
-        const uint64_t i = (G - jb.group_begin) * kGroupChunks + c;
-        if (i >= jb.nchunks) continue;  // (a mask never sets such a bit)
-        g_u64 *man = (g_u64 *)jb.manifest;
-        const uint64_t slot = offsets[G] + (uint64_t)__popcll(c ? mask & ((1ULL << c) - 1) : 0);
+    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (uint64_t G = blockIdx.x; G < ngroups; G += gridDim.x) {
+        uint64_t mask = dirty_mask[G];
+        if (!mask) continue;
+        const TileBuf b = tile_buf<kModeDiff>(tab, G);
         const uint64_t top = *top_word;  // arena offset
-        if (lane == 0) man[i] = top - (slot + 1) * kChunk;
-        copy_chunk(tab, jb, i, arena_base + top - (slot + 1) * kChunk, lane);
+        uint64_t slot = offsets[G];
+        for (uint32_t r = 0; mask; mask &= mask - 1, ++r, ++slot) {
+            if ((r & 3) != wave) continue;
+            const uint64_t i = (G - b.group_begin) * kGroupChunks + (uint64_t)__builtin_ctzll(mask);
+            const uint64_t slot_off = top - (slot + 1) * kChunk;
+            if (lane == 0) ((g_u64 *)b.manifest)[i] = slot_off;
+            copy_chunk(b.g, i, arena_base + slot_off, lane);
+        }
     }
 }
 
@@ -1144,31 +1528,79 @@ __global__ __launch_bounds__(256) void k_reverse_slots(uint64_t top, uint64_t ds
 
 // ---------------------------------------------------------------- classify
 
-// Bitmap word G (= one 64-chunk group of one buffer), computed by one
-// wavefront: chunk i differs iff its K replay fingerprints are not all equal;
-// the wave's ballot is the word.
-template <class Tab>
-__device__ __forceinline__ uint64_t classify_word(const Tab &tab, uint64_t G, uint32_t lane,
-                                                  const uint64_t *hashes, uint32_t K, uint64_t total)
+// The chunks and groups of a buffer: group G's, and buffer b's.
+struct ChunkRange {
+    uint64_t nchunks, chunk_begin, group_begin;
+};
+__device__ __forceinline__ ChunkRange range_of(const JobBuf &b) { return ChunkRange{b.nchunks(), b.chunk_begin, b.group_begin}; }
+__device__ __forceinline__ ChunkRange range_of(const ArgBuf &b)
 {
-    const JobBuf &jb = tab.bufs[buf_index(tab, G)];
-    const uint64_t i = (G - jb.group_begin) * kGroupChunks + lane;
-    bool differs = false;
-    if (i < jb.nchunks) {
-        const uint64_t idx = jb.chunk_begin + i;
-        const uint64_t h0 = hashes[idx];
-        for (uint32_t k = 1; k < K; ++k) differs |= hashes[(uint64_t)k * total + idx] != h0;
+    return ChunkRange{chunks_of(b.nbytes), b.chunk_begin, b.group_begin};
+}
+struct DevRanges {
+    const DevTables &t;
+    __device__ __forceinline__ explicit DevRanges(const DevTables &tab) : t(tab) {}
+    __device__ __forceinline__ ChunkRange group(uint64_t G) const { return range_of(t.bufs[t.map[G]]); }
+};
+struct ArgRanges {
+    ArgLanes lanes;
+    __device__ __forceinline__ explicit ArgRanges(const ArgTables &tab) : lanes(tab) {}
+    __device__ __forceinline__ ChunkRange group(uint64_t G) const { return range_of(lanes.buf(lanes.find(G))); }
+};
+__device__ __forceinline__ DevRanges ranges_of(const DevTables &t) { return DevRanges(t); }
+__device__ __forceinline__ ArgRanges ranges_of(const ArgTables &t) { return ArgRanges(t); }
+
+// Bitmap words g[0..U) (each one 64-chunk group of one buffer; g >= ngroups:
+// none), computed by one wavefront: chunk i differs iff its K replay
+// fingerprints are not all equal; the wave's ballot is the word.  The first
+// kReplays fingerprints of every word are loaded before any is compared.
+constexpr int kReplays = 4;
+template <int U, class R>
+__device__ __forceinline__ void classify_words(const R &ranges, const uint64_t (&g)[U], uint64_t ngroups, uint32_t lane,
+                                               const uint64_t *hashes, uint32_t K, uint64_t total, uint64_t (&word)[U])
+{
+    const uint64_t *p[U];
+    uint64_t h[U][kReplays];
+    bool in[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        in[u] = false;
+        p[u] = hashes;
+        if (g[u] < ngroups) {
+            const ChunkRange r = ranges.group(g[u]);
+            const uint64_t i = (g[u] - r.group_begin) * kGroupChunks + lane;
+            in[u] = i < r.nchunks;
+            if (in[u]) p[u] = hashes + r.chunk_begin + i;
+        }
+#pragma unroll
+        for (int k = 0; k < kReplays; ++k) h[u][k] = p[u][in[u] && k < (int)K ? k * total : 0];
     }
-    return __ballot(differs);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        bool differs = false;
+#pragma unroll
+        for (int k = 1; k < kReplays; ++k) differs |= h[u][k] != h[u][0];
+        for (uint32_t k0 = kReplays; k0 < K; k0 += kReplays) {
+            uint64_t e[kReplays];
+#pragma unroll
+            for (int k = 0; k < kReplays; ++k) e[k] = p[u][in[u] ? min(k0 + k, K - 1) * total : 0];
+#pragma unroll
+            for (int k = 0; k < kReplays; ++k) differs |= e[k] != h[u][0];
+        }
+        word[u] = __ballot(in[u] && differs);
+    }
 }
 
 // One wavefront per bitmap word.
 template <class Tab>
-__global__ __launch_bounds__(64) void k_classify(const Tab tab, const uint64_t *__restrict__ hashes, uint32_t K,
-                                                 uint64_t total, uint64_t *__restrict__ bitmap)
+__global__ __launch_bounds__(256) void k_classify(const Tab tab, uint64_t ngroups, const uint64_t *__restrict__ hashes,
+                                                  uint32_t K, uint64_t total, uint64_t *__restrict__ bitmap)
 {
-    const uint64_t word = classify_word(tab, blockIdx.x, threadIdx.x, hashes, K, total);
-    if (threadIdx.x == 0) bitmap[blockIdx.x] = word;
+    const uint64_t g[1] = {(uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)};
+    if (g[0] >= ngroups) return;
+    uint64_t word[1];
+    classify_words<1>(ranges_of(tab), g, ngroups, threadIdx.x & 63, hashes, K, total, word);
+    if ((threadIdx.x & 63) == 0) bitmap[g[0]] = word[0];
 }
 
 // Per buffer: 1 iff any of its bitmap words is non-zero (one wavefront per
@@ -1178,38 +1610,44 @@ __global__ __launch_bounds__(64) void k_labels(const Tab tab, const uint64_t *__
                                                uint8_t *__restrict__ labels)
 {
     const uint32_t b = blockIdx.x;
-    const JobBuf &jb = tab.bufs[b];
-    const uint64_t nw = (jb.nchunks + kGroupChunks - 1) / kGroupChunks;
+    const ChunkRange r = range_of(tab.bufs[b]);
+    const uint64_t nw = (r.nchunks + kGroupChunks - 1) / kGroupChunks;
     uint64_t any = 0;
-    for (uint64_t w = threadIdx.x; w < nw; w += 64) any |= bitmap[jb.group_begin + w];
+    for (uint64_t w = threadIdx.x; w < nw; w += 64) any |= bitmap[r.group_begin + w];
     const bool set = __ballot(any != 0) != 0;
     if (threadIdx.x == 0) labels[b] = set ? 1 : 0;
 }
 
 // Small jobs (tables in the kernel arguments, at most kClassifyFusedGroups
 // groups): the bitmap and the labels in one workgroup and one launch.
-// Wavefront w computes words w, w + 16, ... (also kept in LDS); after a
-// barrier, one wavefront per buffer ORs its words into the buffer's label.
+// Wavefront w computes words w, w + 16, ..., four at a time (also kept in
+// LDS); after a barrier, one wavefront per buffer ORs its words into the
+// buffer's label.
 __global__ __launch_bounds__(1024) void k_classify_small(const ArgTables tab, uint64_t ngroups,
                                                          const uint64_t *__restrict__ hashes, uint32_t K,
                                                          uint64_t total, uint64_t *__restrict__ bitmap,
                                                          uint8_t *__restrict__ labels)
 {
     __shared__ uint64_t words[kClassifyFusedGroups];
-    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (uint64_t G = wave; G < ngroups; G += 16) {
-        const uint64_t word = classify_word(tab, G, lane, hashes, K, total);
-        if (lane == 0) {
-            bitmap[G] = word;
-            words[G] = word;
-        }
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const ArgRanges ranges(tab);
+    for (uint64_t G = wave; G < ngroups; G += 64) {
+        const uint64_t g[4] = {G, G + 16, G + 32, G + 48};
+        uint64_t word[4];
+        classify_words<4>(ranges, g, ngroups, lane, hashes, K, total, word);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (lane == 0 && g[u] < ngroups) {
+                bitmap[g[u]] = word[u];
+                words[g[u]] = word[u];
+            }
     }
     __syncthreads();
     for (uint32_t b = wave; b < tab.nbuf; b += 16) {
-        const JobBuf &jb = tab.bufs[b];
-        const uint64_t nw = (jb.nchunks + kGroupChunks - 1) / kGroupChunks;
+        const ChunkRange r = range_of(tab.bufs[b]);
+        const uint64_t nw = (r.nchunks + kGroupChunks - 1) / kGroupChunks;
         uint64_t any = 0;
-        for (uint64_t w = lane; w < nw; w += 64) any |= words[jb.group_begin + w];
+        for (uint64_t w = lane; w < nw; w += 64) any |= words[r.group_begin + w];
         const bool set = __ballot(any != 0) != 0;
         if (lane == 0) labels[b] = set ? 1 : 0;
     }
@@ -1236,6 +1674,7 @@ constexpr int kVerifyStaggerSlice = 1024;
 // nontemporal stores whatever the size (plain ones: the KV ring restore 177
 // -> 196 us, its verified restore 181 -> 196 us).
 constexpr uint32_t kPackWriteBackMaxRounds = kStaggerMaxRounds;
+constexpr uint32_t kPackSpareLds = 48 << 10;
 constexpr int kHashLanes = 256, kHashSlice = 512;
 constexpr int kCopyLanes = 512, kCopySlice = 1024;
 // Fingerprint and diff tiles of jobs whose tables travel in the kernel
@@ -1251,7 +1690,13 @@ constexpr int kCopyLanes = 512, kCopySlice = 1024;
 // 4096 groups is even and one of 8192 groups 19% slower; a fingerprint of
 // 2048 groups is 5% faster on a flat buffer and 1.5% slower on a 64-run KV
 // ring window.
+// A job of many buffers has many partial groups, and a 1024-lane tile of a few
+// chunks holds its CU as long as a full one: with more than 16 buffers wide
+// tiles need at least 32 groups a buffer (fingerprints of 53 buffers of 66 B to
+// 57 MB, 12 groups a buffer: 38 us with wide tiles, 33 with 256 lanes; a diff of
+// 64 buffers of 32 groups each: 94-96 us either way).
 constexpr uint64_t kWideDiffGroups = 2048, kWideHashGroups = 1024;
+inline bool wide_pays(uint32_t nbuf, uint64_t ngroups) { return nbuf <= 16 || ngroups >= 32ull * nbuf; }
 constexpr int kSmallLanes = 256;  // sub-tiles of small jobs: 8 chunks per workgroup
 // A sub-tile moves whole chunks in one step (8 granules per lane): a small
 // job's time is a tile's latency, one load round trip per step.
@@ -1851,7 +2296,7 @@ __global__ __launch_bounds__(1024) void k_sel_place(uint64_t scores, uint32_t n,
 // first store, and short entries are laid end to end: one 256-lane workgroup
 // per entry and one granule per lane left three lanes of four idle on a
 // 1 KiB row, with one load in flight on the fourth: 24,000 rows of 16 such
-// arrays (788 MB moved) 457 us, now 155 us.
+// arrays (788 MB moved) 457 us, now 130 us.
 template <int G>
 struct Granule {
     uint64_t v;
@@ -1972,12 +2417,15 @@ __global__ void k_flip_bit(uint64_t addr)
 
 // ---------------------------------------------------------------- launchers
 
-hipError_t launch_group_map(const JobBuf *bufs, const Run *runs, uint32_t nbuf, uint64_t ngroups, GroupRef *map,
-                            hipStream_t s)
+hipError_t launch_stage(uint64_t host, uint64_t dev, uint64_t bytes, const JobBuf *host_bufs, uint32_t nbuf,
+                        uint32_t *map, hipStream_t s)
 {
-    if (ngroups == 0) return hipSuccess;
-    const uint32_t blocks = (uint32_t)((ngroups + 255) / 256);
-    run_kernel(k_group_map, dim3(blocks), dim3(256), s, bufs, runs, nbuf, ngroups, map);
+    const uint64_t n16 = bytes / 16;
+    const uint32_t copy_blocks = (uint32_t)((n16 + kStageUnits - 1) / kStageUnits);
+    const uint32_t per = kStageLanes / 64, map_blocks = (nbuf + per - 1) / per;
+    if (copy_blocks + map_blocks == 0) return hipSuccess;
+    run_kernel(k_stage, dim3(copy_blocks + map_blocks), dim3(kStageLanes), s, host, dev, n16, copy_blocks, host_bufs,
+               nbuf, map);
     return hipGetLastError();
 }
 
@@ -2011,7 +2459,7 @@ hipError_t launch_tile(const Tab &tab, uint64_t ngroups, int mode, uint64_t *nod
     constexpr bool kArgTab = std::is_same<Tab, ArgTables>::value;
     switch (mode) {
     case kModeHash:
-        if (kArgTab && ngroups <= kWideHashGroups)
+        if (kArgTab && ngroups <= kWideHashGroups && wide_pays(tab.nbuf, ngroups))
             run_kernel((k_hash<Tab, kModeHash, kPackLanes, kHashSlice, kGroupChunks, false>), grid, dim3(kPackLanes), s,
                        tab, nodes, flag_mask, arena_base);
         else
@@ -2020,17 +2468,17 @@ hipError_t launch_tile(const Tab &tab, uint64_t ngroups, int mode, uint64_t *nod
         break;
     case kModePack:
         if (stg.ticks)
-            run_kernel((k_hash_staggered<Tab, kModePack, kPackLanes, kPackSlice, kGroupChunks>), grid, dim3(kPackLanes),
-                       s, tab, nodes, flag_mask, arena_base, stg);
+            run_kernel_lds((k_hash_staggered<Tab, kModePack, kPackLanes, kPackSlice, kGroupChunks>), grid, dim3(kPackLanes),
+                           kPackSpareLds, s, tab, nodes, flag_mask, arena_base, stg);
         else if (ngroups <= (uint64_t)kPackWriteBackMaxRounds * std::max<uint32_t>(dev.cus, 1))
-            run_kernel((k_hash<Tab, kModePack, kPackLanes, kPackSlice, kGroupChunks, true>), grid, dim3(kPackLanes), s,
-                       tab, nodes, flag_mask, arena_base);
+            run_kernel_lds((k_hash<Tab, kModePack, kPackLanes, kPackSlice, kGroupChunks, true>), grid, dim3(kPackLanes),
+                           kPackSpareLds, s, tab, nodes, flag_mask, arena_base);
         else
-            run_kernel((k_hash<Tab, kModePack, kPackLanes, kPackSlice, kGroupChunks, false>), grid, dim3(kPackLanes), s,
-                       tab, nodes, flag_mask, arena_base);
+            run_kernel_lds((k_hash<Tab, kModePack, kPackLanes, kPackSlice, kGroupChunks, false>), grid, dim3(kPackLanes),
+                           kPackSpareLds, s, tab, nodes, flag_mask, arena_base);
         break;
     case kModeDiff:
-        if (kArgTab && ngroups <= kWideDiffGroups)
+        if (kArgTab && ngroups <= kWideDiffGroups && wide_pays(tab.nbuf, ngroups))
             run_kernel((k_hash<Tab, kModeDiff, kPackLanes, kHashSlice, kGroupChunks, false>), grid, dim3(kPackLanes), s,
                        tab, nodes, flag_mask, arena_base);
         else
@@ -2082,9 +2530,8 @@ hipError_t launch_place_dirty(const Tab &tab, uint64_t ngroups, const uint64_t *
                               const uint64_t *top_word, uint64_t arena_base, hipStream_t s)
 {
     if (ngroups == 0) return hipSuccess;
-    const uint64_t npos = ngroups * kGroupChunks;
-    const uint32_t blocks = (uint32_t)std::min<uint64_t>((npos + 3) / 4, kPlaceBlocks);
-    run_kernel((k_place_dirty<Tab>), dim3(blocks), dim3(256), s, tab, npos, dirty_mask, offsets, top_word, arena_base);
+    const uint32_t blocks = (uint32_t)std::min<uint64_t>(ngroups, kPlaceBlocks);
+    run_kernel((k_place_dirty<Tab>), dim3(blocks), dim3(256), s, tab, ngroups, dirty_mask, offsets, top_word, arena_base);
     return hipGetLastError();
 }
 
@@ -2093,7 +2540,7 @@ hipError_t launch_classify(const Tab &tab, uint64_t ngroups, const uint64_t *has
                            uint64_t *bitmap, hipStream_t s)
 {
     if (ngroups == 0) return hipSuccess;
-    run_kernel((k_classify<Tab>), dim3((uint32_t)ngroups), dim3(64), s, tab, hashes, K, total, bitmap);
+    run_kernel((k_classify<Tab>), dim3((uint32_t)((ngroups + 3) / 4)), dim3(256), s, tab, ngroups, hashes, K, total, bitmap);
     return hipGetLastError();
 }
 
@@ -2135,11 +2582,17 @@ hipError_t launch_merkle_blocks(const LongLists &lists, const uint64_t *in, uint
     return hipGetLastError();
 }
 
-hipError_t launch_merkle_small(const ArgLists &lists, const uint64_t *in, uint64_t *scratch_a,
-                               uint64_t *scratch_b, bool pre, hipStream_t s)
+hipError_t launch_merkle_args(const ArgTables &tab, uint32_t tiles, uint64_t nodes, const uint64_t *in,
+                              uint64_t *scratch, bool first, hipStream_t s)
 {
-    if (lists.nlists == 0) return hipSuccess;
-    run_kernel(k_merkle_small, dim3(1), dim3(1024), s, lists, in, scratch_a, scratch_b, pre);
+    const bool pre = nodes > kMerkleArgValues;
+    if (first) {
+        if (!pre) return hipSuccess;
+        const uint64_t items = nodes / 64 + tab.nbuf;  // at least the lists' items
+        run_kernel(k_merkle_items, dim3((uint32_t)((items + 3) / 4)), dim3(256), s, tab, tiles, in, scratch);
+    } else {
+        run_kernel(k_merkle_args, dim3(1), dim3(1024), s, tab, tiles, pre ? (const uint64_t *)scratch : in, pre);
+    }
     return hipGetLastError();
 }
 
@@ -2150,8 +2603,7 @@ hipError_t launch_scan(const uint64_t *dirty_mask, uint64_t n, uint64_t *offsets
     return hipGetLastError();
 }
 
-hipError_t launch_merkle_scan_place(const ArgLists &lists, const uint64_t *nodes, uint64_t *scratch_a,
-                                    uint64_t *scratch_b, const ArgTables &tab, uint64_t ngroups,
+hipError_t launch_merkle_scan_place(const ArgTables &tab, uint32_t tiles, const uint64_t *nodes, uint64_t ngroups,
                                     const uint64_t *dirty_mask, const SlotBump &bump, uint64_t *total,
                                     uint64_t arena_base, hipStream_t s)
 {
@@ -2161,8 +2613,8 @@ hipError_t launch_merkle_scan_place(const ArgLists &lists, const uint64_t *nodes
     // per wavefront if every chunk is stored (at most kPlaceBlocks / 4).
     const uint64_t npos = ngroups * kGroupChunks;
     const uint32_t blocks = 1 + (uint32_t)std::min<uint64_t>((npos + 15) / 16, kPlaceBlocks / 4);
-    run_kernel(k_merkle_scan_place, dim3(blocks), dim3(1024), s, lists, nodes, scratch_a, scratch_b, tab, ngroups,
-               dirty_mask, bump, total, arena_base);
+    run_kernel(k_merkle_scan_place, dim3(blocks), dim3(1024), s, tab, tiles, nodes, ngroups, dirty_mask, bump, total,
+               arena_base);
     return hipGetLastError();
 }
 

@@ -14,19 +14,87 @@ constexpr uint32_t kGroupChunks = 64;   // chunks per work group and per bitmap 
 // A maximal physically contiguous piece of a buffer's logical byte stream:
 // logical bytes [lstart, next run's lstart) live at addr onwards.  A flat
 // buffer is one run; a ring window is at most two runs per ring (before and
-// after the wrap), merged where physically adjacent.
+// after the wrap), merged where physically adjacent.  (Kernels compute these
+// pieces, see Geom; the list is what that is checked against.)
 struct Run {
     uint64_t lstart;
     uint64_t addr;
 };
 
+constexpr uint64_t chunks_of(uint64_t nbytes) { return nbytes / kChunk + (nbytes % kChunk != 0); }
+
+// Where a buffer's logical bytes lie.  Flat (win == 0): at addr onwards.
+// Ring: `win` logical bytes per ring, ring o at addr + o * stride; the first
+// `first` bytes of a ring's window start `head` bytes into it, the rest at
+// its beginning.  inv_win = 1 / win.
+struct Geom {
+    uint64_t addr;
+    uint64_t nbytes;
+    uint64_t win, first, head, stride;
+    double inv_win;
+};
+// Physical address of logical byte L < nbytes, and the bytes from L to the
+// end of its physically contiguous piece.
+struct Where {
+    uint64_t addr, left;
+};
+// The ring number comes from a multiplication by inv_win: it is below 2^30
+// (a descriptor's limit on rings), so the product is off by less than 2^-20
+// and its floor by at most one, which the remainder shows.  Kernels compute
+// addresses this way instead of searching a table of pieces: a search costs a
+// dependent load a step, and a table of many rings does not fit the kernel
+// arguments.
+constexpr Where locate(const Geom &g, uint64_t L)
+{
+    if (g.win == 0) return Where{g.addr + L, g.nbytes - L};
+    uint64_t o = (uint64_t)((double)L * g.inv_win);
+    int64_t rem = (int64_t)(L - o * g.win);
+    if (rem < 0) {
+        --o;
+        rem += (int64_t)g.win;
+    } else if ((uint64_t)rem >= g.win) {
+        ++o;
+        rem -= (int64_t)g.win;
+    }
+    const uint64_t r = (uint64_t)rem, base = g.addr + o * g.stride;
+    return r < g.first ? Where{base + g.head + r, g.first - r} : Where{base + (r - g.first), g.win - r};
+}
+
+// Where one chunk's bytes lie: byte x (x < len) is at (x < split ? a1 : a2)
+// + x when the chunk spans at most two pieces (it straddles a ring's wrap, or
+// the end of one ring's window and the start of the next); a1 = 0 marks a
+// chunk of more pieces (rows shorter than a chunk), located per access.
+// Piece boundaries are 16-byte aligned, so no 16-byte granule crosses one.
+// slot: the chunk's 4096-byte snapshot slot (pack, restore; the kernels' own).
+struct ChunkLoc {
+    uint64_t a1, a2, slot;
+    uint32_t split, len;
+};
+constexpr ChunkLoc chunk_loc(const Geom &g, uint64_t chunk)
+{
+    const uint64_t cb = chunk * kChunk, rest = g.nbytes - cb;
+    ChunkLoc l{0, 0, 0, 0, (uint32_t)(rest < kChunk ? rest : kChunk)};
+    const Where w = locate(g, cb);
+    if (l.len <= w.left) {
+        l.a1 = l.a2 = w.addr;
+        l.split = l.len;
+    } else {  // the buffer goes on after this piece
+        const Where w2 = locate(g, cb + w.left);
+        if (l.len - w.left <= w2.left) {
+            l.a1 = w.addr;
+            l.split = (uint32_t)w.left;
+            l.a2 = w2.addr - w.left;  // byte `split` of the chunk is the second piece's first byte
+        }
+    }
+    return l;
+}
+
 // One buffer of a job.  Every kernel grids over 64-chunk groups of one
 // buffer; group_begin is this buffer's first group in the job.
 struct JobBuf {
-    uint64_t nbytes;          // logical bytes
-    uint64_t nchunks;         // ceil(nbytes / 4096)
-    uint64_t chunk_begin;     // first chunk of this buffer in job-wide chunk order
-    uint64_t group_begin;     // first 64-chunk group of this buffer in the job
+    Geom g;
+    uint32_t chunk_begin;     // first chunk of this buffer in job-wide chunk order
+    uint32_t group_begin;     // first 64-chunk group of this buffer in the job
     uint64_t payload;         // device address of chunk 0's 4096-byte slot (pack dst, restore src)
     uint64_t manifest;        // restore: device address of uint64 arena offsets, one per chunk
                               // incremental pack: where this buffer's new manifest entries go
@@ -37,11 +105,8 @@ struct JobBuf {
     uint64_t parent_chunks;   // incremental: chunks the parent held for this buffer
     uint64_t parent_manifest; // incremental: parent's manifest entries (0 if the parent is full)
     uint64_t parent_slot0;    // incremental, full parent: arena offset of the parent's chunk-0 slot
-    uint32_t run_begin;       // this buffer's runs in the job's run table
-    uint32_t run_count;
-    uint32_t pad[2];
+    constexpr uint64_t nchunks() const { return chunks_of(g.nbytes); }
 };
-static_assert(sizeof(JobBuf) == 128, "JobBuf layout");
 
 // A list reduced by the Merkle kernel: values [begin, begin + count) of the
 // input array; the root goes to dst[0] / dst[1] (0 = none) and scratch[idx].
@@ -51,14 +116,15 @@ struct MerkleList {
     uint64_t dst[2];
 };
 
-// Where a launch finds its buffer and run tables.
-//   DevTables: in device memory (uploaded per call), with a group map
-//              written by k_group_map that gives each group its buffer and
-//              the run holding its first byte; any job size.
-//   ArgTables: carried in the kernel arguments themselves (no upload, no map
-//              kernel: a workgroup finds its buffer and first run with short
-//              searches); jobs of at most kArgBufs buffers and kArgRuns runs.
-constexpr uint32_t kArgBufs = 16, kArgRuns = 64;
+// Where a launch finds its buffer table.
+//   DevTables: in device memory (staged per call), with a group map that
+//              gives each group its buffer; any job.
+//   ArgTables: carried in the kernel arguments themselves (nothing staged);
+//              jobs of at most kArgBufs buffers, kArgRings of them rings, and
+//              one session where fingerprints are written.  A workgroup reads
+//              the whole table with a few vector loads, one round trip to
+//              memory, and finds its buffer with a ballot.
+constexpr uint32_t kArgBufs = 96, kArgRings = 8;
 // Small jobs (at most kSmallJobGroups groups) are cut into kSmallTiles
 // sub-tiles per group, so that a few groups still spread over many CUs.
 // Fingerprint and pack tiles then write one Merkle node per sub-tile (an
@@ -69,10 +135,6 @@ constexpr uint32_t kArgBufs = 16, kArgRuns = 64;
 constexpr uint64_t kSmallJobGroups = 128;
 constexpr uint32_t kSmallTiles = 8;
 inline uint32_t tile_split(uint64_t ngroups) { return ngroups <= kSmallJobGroups ? kSmallTiles : 1; }
-struct GroupRef {
-    uint32_t buf;
-    uint32_t run;
-};
 
 // Tile order of the tile kernels: the tile workgroup b of a launch of nb
 // workgroups takes.  The dispatcher deals a launch's workgroups to the eight
@@ -103,31 +165,45 @@ constexpr uint32_t xcd_tile_of(uint32_t b, uint32_t nb)
 
 struct DevTables {
     const JobBuf *bufs;
-    const Run *runs;
-    const GroupRef *map;
+    const uint32_t *map;  // each group's buffer
     uint32_t nbuf;
     uint32_t pad;
 };
+
+// JobBuf packed for the kernel arguments.  What a job lays out linearly
+// (fingerprints, manifests, roots) is a base plus an index; aux depends on
+// what the job does:
+//   pack:            device address of chunk 0's slot
+//   restore, verify: the same, or the address of the buffer's manifest
+//                    entries with kAuxManifest set
+//   diff:            parent's first chunk | parent's chunks << 32
+struct ArgBuf {
+    uint64_t addr;
+    uint64_t nbytes;
+    uint32_t chunk_begin, group_begin;
+    uint64_t aux;
+};
+constexpr uint64_t kAuxManifest = 1;
+struct ArgRing {
+    uint64_t win, first, head, stride;
+    double inv_win;
+    uint32_t buf, pad;
+};
 struct ArgTables {
-    uint32_t nbuf;
-    uint32_t pad;
-    JobBuf bufs[kArgBufs];
-    Run runs[kArgRuns];
+    uint32_t nbuf, nring;
+    uint64_t hash[2];          // chunk fingerprints of chunk i: hash + 8 i (0 = none)
+    uint64_t root[2];          // root of buffer b: root + 8 b (0 = none)
+    uint64_t sroot[2];         // session root (0 = none)
+    uint64_t manifest;         // diff: new manifest entry of chunk i: manifest + 8 i
+    uint64_t parent_hash;      // diff: parent's chunk i; verify: stored fingerprint of chunk i
+    uint64_t parent_manifest;  // diff: parent's manifest (0 if the parent is full)
+    uint64_t parent_slot0;     // diff, full parent: arena offset of its chunk 0's slot
+    ArgRing rings[kArgRings];
+    ArgBuf bufs[kArgBufs];
 };
 // Kernel arguments are limited to 4 KiB; a launch passes one ArgTables and at
 // most a few pointers and sizes besides.
 static_assert(sizeof(ArgTables) + 256 <= 4096, "argument tables must fit in the kernel arguments");
-// Merkle lists carried in the kernel arguments: the first nbuf_lists reduce
-// group nodes to buffer roots, the rest reduce those roots to session roots
-// (their begin/count index the buffer lists).
-struct ArgLists {
-    uint32_t nbuf_lists;
-    uint32_t nlists;
-    MerkleList lists[kArgBufs + 1];
-};
-static_assert(sizeof(ArgLists) + 256 <= 4096, "Merkle lists must fit in the kernel arguments");
-// The small incremental launch passes both, with a few pointers and sizes.
-static_assert(sizeof(ArgLists) + sizeof(ArgTables) + 128 <= 4096, "Merkle lists and tables must fit together");
 
 // Buffer lists of a Merkle launch that hold more than kMerkleLdsValues
 // values (a buffer of more than 1 GiB): when at most kLongLists of them, a

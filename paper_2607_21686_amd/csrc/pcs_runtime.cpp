@@ -3,7 +3,7 @@
 // Owns: the arena sub-allocator (first fit over a caller-owned device
 // arena), the snapshot table (handle -> immutable snapshot record, shared by
 // forks, kept alive by incremental children), the descriptor builder (plan
-// buffers -> logical/physical runs and 64-chunk groups), pinned staging for
+// buffers -> geometry and 64-chunk groups), pinned staging for
 // descriptor uploads, and stream ordering.  Every byte of state moves in the
 // kernels of pcs_kernels.hip; nothing here touches snapshot data on the host.
 #include <algorithm>
@@ -81,7 +81,7 @@ struct pcs_ctx {
     std::string err;
 
     struct Slot {
-        void *host = nullptr;
+        void *host = nullptr, *dev = nullptr;  // the same memory as the device addresses it
         size_t cap = 0;
         hipEvent_t ev = nullptr;
         bool pending = false;
@@ -111,7 +111,7 @@ struct pcs_ctx {
     // pcs_fingerprint_noalloc: the device's static scratch array (its address
     // on the arena's device) and a fixed pinned staging buffer for tables.
     uint64_t scratch_dev = 0;
-    void *na_host = nullptr;
+    void *na_host = nullptr, *na_dev = nullptr;
     hipEvent_t na_ev = nullptr;
     bool na_pending = false;
 };
@@ -168,38 +168,39 @@ int hip_fail(pcs_ctx *c, hipError_t e, const char *what)
         if (e_ != hipSuccess) return hip_fail((ctx), e_, #expr);        \
     } while (0)
 
-// Validates one descriptor and appends its runs (see pcs::describe); the
-// reason for a rejection becomes the context's last error.
-int check_buf(pcs_ctx *c, const pcs_buf &b, uint32_t idx, Layout *lay, std::vector<Run> *runs)
+// Validates one descriptor (see pcs::describe); the reason for a rejection
+// becomes the context's last error.
+int check_buf(pcs_ctx *c, const pcs_buf &b, uint32_t idx, Layout *lay)
 {
     std::string why;
-    const int st = describe(b, idx, lay, runs, &why);
+    const int st = describe(b, idx, lay, nullptr, &why);
     return st ? fail(c, st, "%s", why.c_str()) : PCS_OK;
 }
 
-// A job under construction: buffer table, run table, and group totals.
+// A job under construction: buffer table and totals.
 struct Job {
     std::vector<JobBuf> bufs;
-    std::vector<Run> runs;
     std::vector<Layout> lays;
     uint64_t ngroups = 0, nchunks = 0;
+    uint64_t nruns = 0;   // physically contiguous pieces
+    uint32_t nrings = 0;  // buffers that are not one piece
 };
 
 int add_buffers(pcs_ctx *c, Job &job, const pcs_buf *bufs, uint32_t n, uint32_t idx0)
 {
+    job.bufs.reserve(job.bufs.size() + n);
+    job.lays.reserve(job.lays.size() + n);
     for (uint32_t i = 0; i < n; ++i) {
         Layout lay;
-        const size_t r0 = job.runs.size();
-        const int st = check_buf(c, bufs[i], idx0 + i, &lay, &job.runs);
+        const int st = check_buf(c, bufs[i], idx0 + i, &lay);
         if (st) return st;
-        if (job.runs.size() > (1ULL << 31)) return fail(c, PCS_E_INVAL, "too many runs");
+        job.nruns += lay.nruns;
+        if (job.nruns > (1ULL << 31)) return fail(c, PCS_E_INVAL, "too many runs");
         JobBuf jb{};
-        jb.nbytes = lay.nbytes;
-        jb.nchunks = lay.nchunks;
-        jb.chunk_begin = job.nchunks;
-        jb.group_begin = job.ngroups;
-        jb.run_begin = (uint32_t)r0;
-        jb.run_count = (uint32_t)(job.runs.size() - r0);
+        jb.g = lay.geom;
+        jb.chunk_begin = (uint32_t)job.nchunks;
+        jb.group_begin = (uint32_t)job.ngroups;
+        job.nrings += lay.geom.win != 0;
         job.nchunks += lay.nchunks;
         job.ngroups += lay.ngroups;
         if (job.ngroups > kMaxGroups) return fail(c, PCS_E_INVAL, "job too large (%llu groups)", (unsigned long long)job.ngroups);
@@ -242,10 +243,10 @@ int temp_alloc(pcs_ctx *c, Temp &t, uint64_t bytes)
     return PCS_OK;
 }
 
-// Copies host bytes to device memory through a pinned staging slot.
-int upload(pcs_ctx *c, uint64_t dev, const void *src, size_t bytes)
+// A pinned staging slot of at least `bytes` whose last use has finished, and
+// the address the device reads it at.
+int staging_slot(pcs_ctx *c, size_t bytes, pcs_ctx::Slot **out)
 {
-    if (bytes == 0) return PCS_OK;
     pcs_ctx::Slot &s = c->staging[c->next_slot];
     c->next_slot = (c->next_slot + 1) % kStagingSlots;
     if (s.pending) {
@@ -255,14 +256,13 @@ int upload(pcs_ctx *c, uint64_t dev, const void *src, size_t bytes)
     if (s.cap < bytes) {
         if (s.host) HIP_TRY(c, hipHostFree(s.host));
         s.host = nullptr;
+        s.cap = 0;
         const size_t cap = round_up(bytes, 1 << 20);
-        HIP_TRY(c, hipHostMalloc(&s.host, cap, hipHostMallocDefault));
+        HIP_TRY(c, hipHostMalloc(&s.host, cap, hipHostMallocMapped));
+        HIP_TRY(c, hipHostGetDevicePointer(&s.dev, s.host, 0));
         s.cap = cap;
     }
-    memcpy(s.host, src, bytes);
-    HIP_TRY(c, hipMemcpyAsync((void *)dev, s.host, bytes, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(c, hipEventRecord(s.ev, c->stream));
-    s.pending = true;
+    *out = &s;
     return PCS_OK;
 }
 
@@ -443,7 +443,56 @@ struct RootDst {
     uint64_t d[2];
 };
 
-bool is_small(const Job &job) { return job.bufs.size() <= kArgBufs && job.runs.size() <= kArgRuns; }
+bool is_small(const Job &job) { return job.bufs.size() <= kArgBufs && job.nrings <= kArgRings; }
+
+// What a job does with its buffers, as far as the argument tables need it
+// (see ArgBuf).
+enum class Use { kHash, kPack, kRestore, kDiff };
+
+// Packs a small job into the argument tables.  Fingerprints, roots and
+// manifests are linear in the chunk (or buffer) number over a whole job of
+// one session, so the first buffer's addresses are the bases.
+void fill_args(const Job &job, Use use, ArgTables *t)
+{
+    const uint32_t n = (uint32_t)job.bufs.size();
+    memset(t, 0, offsetof(ArgTables, bufs));
+    memset((void *)(t->bufs + n), 0, sizeof(ArgBuf) * (kArgBufs - n));
+    t->nbuf = n;
+    if (n) {
+        const JobBuf &f = job.bufs[0];
+        for (int k = 0; k < 2; ++k) {
+            t->hash[k] = f.hash_dst[k];
+            t->root[k] = f.root_dst[k];
+        }
+        t->parent_hash = f.parent_hash;
+        if (use == Use::kDiff) {
+            t->manifest = f.manifest;
+            t->parent_manifest = f.parent_manifest;
+            t->parent_slot0 = f.parent_slot0;
+        }
+    }
+    for (uint32_t b = 0; b < n; ++b) {
+        const JobBuf &jb = job.bufs[b];
+        ArgBuf &a = t->bufs[b];
+        a.addr = jb.g.addr;
+        a.nbytes = jb.g.nbytes;
+        a.chunk_begin = jb.chunk_begin;
+        a.group_begin = jb.group_begin;
+        a.aux = use == Use::kPack      ? jb.payload
+                : use == Use::kRestore ? (jb.manifest ? jb.manifest | kAuxManifest : jb.payload)
+                : use == Use::kDiff    ? (jb.parent_hash - t->parent_hash) / 8 | jb.parent_chunks << 32
+                                       : 0;
+        if (jb.g.win) {
+            ArgRing &r = t->rings[t->nring++];
+            r.win = jb.g.win;
+            r.first = jb.g.first;
+            r.head = jb.g.head;
+            r.stride = jb.g.stride;
+            r.inv_win = jb.g.inv_win;
+            r.buf = b;
+        }
+    }
+}
 
 // The descriptor tables of a job as the kernels see them: in the kernel
 // arguments for a small job, else uploaded into per-call scratch with a
@@ -454,26 +503,23 @@ struct Staged {
     DevTables dev;
 };
 
-// Lays out per-call scratch as [tables (big jobs)][extra host bytes] (one
-// upload) then [group map (big jobs)][dev_bytes of device-only scratch],
-// uploads, and launches the group map for a big job.
-int stage(pcs_ctx *c, const Job &job, bool small, Temp &t, const std::vector<uint8_t> &extra, uint64_t dev_bytes,
-          Staged &sg, uint64_t &extra_dev, uint64_t &scratch_dev)
+// Lays out per-call scratch as [tables (big jobs)][extra host bytes] (staged
+// in one launch) then [group map (big jobs)][dev_bytes of device-only
+// scratch].
+int stage(pcs_ctx *c, const Job &job, bool small, Use use, Temp &t, const std::vector<uint8_t> &extra,
+          uint64_t dev_bytes, Staged &sg, uint64_t &extra_dev, uint64_t &scratch_dev)
 {
     const uint32_t n = (uint32_t)job.bufs.size();
     const uint64_t G = job.ngroups;
     Carver cv;
-    uint64_t o_bufs = 0, o_runs = 0, o_extra = 0, o_map = 0, o_scr = 0;
-    if (!small) {
-        cv.add(&o_bufs, sizeof(JobBuf) * n);
-        cv.add(&o_runs, sizeof(Run) * job.runs.size());
-    }
+    uint64_t o_bufs = 0, o_extra = 0, o_map = 0, o_scr = 0;
+    if (!small) cv.add(&o_bufs, sizeof(JobBuf) * n);
     if (!extra.empty()) cv.add(&o_extra, extra.size());
     const uint64_t hb = cv.total;
-    if (!small) cv.add(&o_map, sizeof(GroupRef) * G);
+    if (!small) cv.add(&o_map, sizeof(uint32_t) * G);
     if (dev_bytes) cv.add(&o_scr, dev_bytes);
-    // A small job with nothing to upload and no device scratch (a restore,
-    // a plain pack, classify) takes no arena space at all.
+    // A small job with no device scratch (a restore, a plain pack, classify)
+    // takes no arena space at all.
     uint64_t base = 0;
     if (cv.total) {
         if (int e = temp_alloc(c, t, cv.total)) return e;
@@ -483,27 +529,23 @@ int stage(pcs_ctx *c, const Job &job, bool small, Temp &t, const std::vector<uin
     scratch_dev = dev_bytes ? base + o_scr : 0;
     sg.small = small;
     if (small) {
-        memset(&sg.arg, 0, sizeof sg.arg);
-        sg.arg.nbuf = n;
-        if (n) memcpy(sg.arg.bufs, job.bufs.data(), sizeof(JobBuf) * n);
-        if (!job.runs.empty()) memcpy(sg.arg.runs, job.runs.data(), sizeof(Run) * job.runs.size());
+        fill_args(job, use, &sg.arg);
     } else {
-        sg.dev = DevTables{(const JobBuf *)(base + o_bufs), (const Run *)(base + o_runs),
-                           (const GroupRef *)(base + o_map), n, 0};
+        sg.dev = DevTables{(const JobBuf *)(base + o_bufs), (const uint32_t *)(base + o_map), n, 0};
     }
-    if (hb) {
-        std::vector<uint8_t> host(hb, 0);
-        if (!small) {
-            if (n) memcpy(host.data() + o_bufs, job.bufs.data(), sizeof(JobBuf) * n);
-            if (!job.runs.empty()) memcpy(host.data() + o_runs, job.runs.data(), sizeof(Run) * job.runs.size());
-        }
-        if (!extra.empty()) memcpy(host.data() + o_extra, extra.data(), extra.size());
-        if (int e = upload(c, base, host.data(), hb)) return e;
-    }
-    if (!small && G)
-        return launch(c, "map", [&] {
-            return launch_group_map(sg.dev.bufs, sg.dev.runs, n, G, (GroupRef *)sg.dev.map, c->stream);
-        });
+    if (!hb) return PCS_OK;
+    pcs_ctx::Slot *slot;
+    if (int e = staging_slot(c, hb, &slot)) return e;
+    uint8_t *host = (uint8_t *)slot->host;
+    if (!small && n) memcpy(host + o_bufs, job.bufs.data(), sizeof(JobBuf) * n);
+    if (!extra.empty()) memcpy(host + o_extra, extra.data(), extra.size());
+    if (int e = launch(c, "map", [&] {
+            return launch_stage((uint64_t)slot->dev, base, hb, (const JobBuf *)((uint64_t)slot->dev + o_bufs),
+                                small ? 0 : n, (uint32_t *)(base + o_map), c->stream);
+        }))
+        return e;
+    HIP_TRY(c, hipEventRecord(slot->ev, c->stream));
+    slot->pending = true;
     return PCS_OK;
 }
 
@@ -520,22 +562,24 @@ std::vector<uint8_t> bytes_of(const std::vector<MerkleList> &lists)
     return v;
 }
 
-ArgLists arg_lists(const std::vector<MerkleList> &lists, uint32_t nbuf_lists)
+// The roots of a job in the argument tables (its outputs are in the tables).
+int run_merkle_args(pcs_ctx *c, const ArgTables &tab, uint64_t G, uint32_t tiles, uint64_t *d_nodes, uint64_t *d_sa)
 {
-    ArgLists al;
-    memset(&al, 0, sizeof al);
-    al.nbuf_lists = nbuf_lists;
-    al.nlists = (uint32_t)lists.size();
-    for (size_t j = 0; j < lists.size(); ++j) al.lists[j] = lists[j];
-    return al;
+    for (const bool first : {true, false})
+        if (!first || G * tiles > kMerkleArgValues)
+            if (int st = launch(c, "merkle", [&] {
+                    return launch_merkle_args(tab, tiles, G * tiles, d_nodes, d_sa, first, c->stream);
+                }))
+                return st;
+    return PCS_OK;
 }
 
-// Buffer roots then session roots: one single-workgroup launch for a small
-// job, else one workgroup per list in two launches.  Buffer lists of more
+// Buffer roots then session roots of a job with device tables: one workgroup
+// per list in two launches.  Buffer lists of more
 // than kMerkleLdsValues values (up to kLongLists of them) first have their
 // 64-value blocks reduced by every CU (one more launch), which a single
 // workgroup would otherwise do a block per wavefront at a time.
-int run_merkle(pcs_ctx *c, bool small, const std::vector<MerkleList> &lists, uint32_t nbuf_lists,
+int run_merkle(pcs_ctx *c, const std::vector<MerkleList> &lists, uint32_t nbuf_lists,
                uint64_t lists_dev, uint64_t *d_nodes, uint64_t *d_sa, uint64_t *d_sb, uint64_t *d_roots)
 {
     hipStream_t s = c->stream;
@@ -555,10 +599,6 @@ int run_merkle(pcs_ctx *c, bool small, const std::vector<MerkleList> &lists, uin
         ll.n = nlong;
         if (int st = launch(c, "merkle", [&] { return launch_merkle_blocks(ll, d_nodes, d_sa, s); })) return st;
     }
-    if (small) {
-        const ArgLists al = arg_lists(lists, nbuf_lists);
-        return launch(c, "merkle", [&] { return launch_merkle_small(al, d_nodes, d_sa, d_sb, pre, s); });
-    }
     const MerkleList *d_lists = (const MerkleList *)lists_dev;
     const uint32_t nsess = (uint32_t)lists.size() - nbuf_lists;
     uint64_t max_buf = 0, max_sess = 0;  // the longest list of each launch picks its workgroup size
@@ -575,9 +615,26 @@ int run_merkle(pcs_ctx *c, bool small, const std::vector<MerkleList> &lists, uin
     });
 }
 
+// The Merkle lists of a job with device tables: one per buffer (its root
+// destinations are in the job), then one per session over the buffer roots.
+std::vector<MerkleList> merkle_lists(const Job &job, uint32_t tiles, const std::vector<uint32_t> &sess_nbufs,
+                                     const std::vector<RootDst> &sroot_dst)
+{
+    const uint64_t per_tile = kGroupChunks / tiles;
+    std::vector<MerkleList> lists;
+    lists.reserve(job.bufs.size() + sess_nbufs.size());
+    for (const JobBuf &b : job.bufs)
+        lists.push_back({(uint64_t)b.group_begin * tiles, div_up(b.nchunks(), per_tile), {b.root_dst[0], b.root_dst[1]}});
+    uint64_t first = 0;
+    for (size_t s = 0; s < sess_nbufs.size(); ++s) {
+        lists.push_back({first, sess_nbufs[s], {sroot_dst[s].d[0], sroot_dst[s].d[1]}});
+        first += sess_nbufs[s];
+    }
+    return lists;
+}
+
 int run_hash_job(pcs_ctx *c, Job &job, bool copy, const std::vector<uint32_t> &sess_nbufs,
-                 const std::vector<RootDst> &root_dst, const std::vector<RootDst> &sroot_dst,
-                 bool want_roots)
+                 const std::vector<RootDst> &sroot_dst, bool want_roots)
 {
     const uint32_t n = (uint32_t)job.bufs.size();
     const uint32_t S = (uint32_t)sess_nbufs.size();
@@ -586,40 +643,40 @@ int run_hash_job(pcs_ctx *c, Job &job, bool copy, const std::vector<uint32_t> &s
     // A small job runs as sub-tiles: one Merkle node per sub-tile, and each
     // buffer's list covers its sub-tiles (aligned subtrees of the same tree).
     const uint32_t tiles = tile_split(G);
-    const uint64_t per_tile = kGroupChunks / tiles;
+    std::vector<uint8_t> lists_bytes;
     std::vector<MerkleList> lists;
-    if (want_roots) {
-        for (uint32_t b = 0; b < n; ++b)
-            lists.push_back({job.bufs[b].group_begin * tiles, div_up(job.bufs[b].nchunks, per_tile),
-                             {root_dst[b].d[0], root_dst[b].d[1]}});
-        uint64_t first = 0;
-        for (uint32_t s = 0; s < S; ++s) {
-            lists.push_back({first, sess_nbufs[s], {sroot_dst[s].d[0], sroot_dst[s].d[1]}});
-            first += sess_nbufs[s];
-        }
+    if (want_roots && !small) {
+        lists = merkle_lists(job, tiles, sess_nbufs, sroot_dst);
+        lists_bytes = bytes_of(lists);
     }
     Carver cv;
-    uint64_t o_nodes, o_sa, o_sb, o_roots;
+    uint64_t o_nodes, o_sa, o_sb = 0, o_roots = 0;
     cv.add(&o_nodes, 8 * G * tiles);
     cv.add(&o_sa, 8 * std::max<uint64_t>(G * tiles, n));
-    cv.add(&o_sb, 8 * std::max<uint64_t>(G * tiles, n));
-    cv.add(&o_roots, 8 * n);
+    if (!small) {
+        cv.add(&o_sb, 8 * std::max<uint64_t>(G * tiles, n));
+        cv.add(&o_roots, 8 * n);
+    }
     Temp t(c);
     Staged sg;
     uint64_t lists_dev, scr;
-    if (int st = stage(c, job, small, t, small ? std::vector<uint8_t>() : bytes_of(lists), cv.total, sg, lists_dev, scr))
+    if (int st = stage(c, job, small, copy ? Use::kPack : Use::kHash, t, lists_bytes, cv.total, sg, lists_dev, scr))
         return st;
-    uint64_t *d_nodes = (uint64_t *)(scr + o_nodes);
-    uint64_t *d_sa = (uint64_t *)(scr + o_sa), *d_sb = (uint64_t *)(scr + o_sb);
-    uint64_t *d_roots = (uint64_t *)(scr + o_roots);
+    if (small && S) {
+        sg.arg.sroot[0] = sroot_dst[0].d[0];
+        sg.arg.sroot[1] = sroot_dst[0].d[1];
+    }
+    uint64_t *d_nodes = (uint64_t *)(scr + o_nodes), *d_sa = (uint64_t *)(scr + o_sa);
     hipStream_t s = c->stream;
     int st = with_tables(sg, [&](const auto &tab) {
         return launch(c, copy ? "pack_hash" : "hash", [&] {
-            return launch_tile(tab, G, copy ? kModePack : kModeHash, d_nodes, nullptr, 0, s, tiles, c->dev);
+            return launch_tile(tab, G, copy ? kModePack : kModeHash, want_roots ? d_nodes : nullptr, nullptr, 0, s, tiles,
+                               c->dev);
         });
     });
     if (st || !want_roots) return st;
-    return run_merkle(c, small, lists, n, lists_dev, d_nodes, d_sa, d_sb, d_roots);
+    if (small) return run_merkle_args(c, sg.arg, G, tiles, d_nodes, d_sa);
+    return run_merkle(c, lists, n, lists_dev, d_nodes, d_sa, (uint64_t *)(scr + o_sb), (uint64_t *)(scr + o_roots));
 }
 
 struct FullPlan {
@@ -707,9 +764,8 @@ int checkpoint_full(pcs_ctx *c, const pcs_buf *plans, const uint32_t *nbufs, uin
     }
 
     // Wire destinations.
-    std::vector<RootDst> rdst(nb_total), sdst(sessions);
+    std::vector<RootDst> sdst(sessions);
     b0 = 0;
-    uint64_t chunk0 = 0;
     for (uint32_t s = 0; s < sessions; ++s) {
         const auto &nd = nodes[s];
         for (uint32_t k = 0; k < nbufs[s]; ++k) {
@@ -718,26 +774,24 @@ int checkpoint_full(pcs_ctx *c, const pcs_buf *plans, const uint32_t *nbufs, uin
             if (hash) {
                 jb.hash_dst[0] = c->arena_dev + nd->hashes_off + 8 * nd->chunk_begin[k];
                 jb.hash_dst[1] = d_hashes ? (uint64_t)(d_hashes + jb.chunk_begin) : 0;
-                rdst[b0 + k].d[0] = c->arena_dev + nd->roots_off + 8 * k;
-                rdst[b0 + k].d[1] = d_roots ? (uint64_t)(d_roots + b0 + k) : 0;
+                jb.root_dst[0] = c->arena_dev + nd->roots_off + 8 * k;
+                jb.root_dst[1] = d_roots ? (uint64_t)(d_roots + b0 + k) : 0;
             }
         }
         sdst[s].d[0] = c->arena_dev + nd->roots_off + 8 * nbufs[s];
         sdst[s].d[1] = d_sroots ? (uint64_t)(d_sroots + s) : 0;
         b0 += nbufs[s];
-        chunk0 += nd->total_chunks;
     }
-    (void)chunk0;
 
     int st;
     if (hash) {
         std::vector<uint32_t> sn(nbufs, nbufs + sessions);
-        st = run_hash_job(c, job, true, sn, rdst, sdst, true);
+        st = run_hash_job(c, job, true, sn, sdst, true);
     } else {
         Temp t(c);
         Staged sg;
         uint64_t xd, scr;
-        st = stage(c, job, is_small(job), t, {}, 0, sg, xd, scr);
+        st = stage(c, job, is_small(job), Use::kPack, t, {}, 0, sg, xd, scr);
         const uint64_t G = job.ngroups;
         if (!st)
             st = with_tables(sg, [&](const auto &tab) {
@@ -793,7 +847,7 @@ int restore_impl(pcs_ctx *c, const pcs_snap *snaps, uint32_t m, const pcs_buf *d
     Temp t(c);
     Staged sg;
     uint64_t xd, scr;
-    if (int st = stage(c, job, is_small(job), t, {}, 0, sg, xd, scr)) return st;
+    if (int st = stage(c, job, is_small(job), Use::kRestore, t, {}, 0, sg, xd, scr)) return st;
     const uint64_t G = job.ngroups;
     return with_tables(sg, [&](const auto &tab) {
         return launch(c, "copy", [&] { return launch_copy(tab, G, false, c->arena_dev, c->stream); });
@@ -816,13 +870,13 @@ int fingerprint_regions(pcs_ctx *c, const std::vector<uint64_t> &addr, const std
     }
     Job job;
     if (int st = add_buffers(c, job, bufs.data(), n, 0)) return st;
-    std::vector<RootDst> rdst(n), sdst(1);
+    std::vector<RootDst> sdst(1);
     for (uint32_t b = 0; b < n; ++b) {
         job.bufs[b].hash_dst[0] = (uint64_t)(d_hashes + job.bufs[b].chunk_begin);
-        rdst[b].d[0] = (uint64_t)(d_roots + b);
+        job.bufs[b].root_dst[0] = (uint64_t)(d_roots + b);
     }
     sdst[0].d[0] = (uint64_t)d_sroot;
-    return run_hash_job(c, job, false, {n}, rdst, sdst, true);
+    return run_hash_job(c, job, false, {n}, sdst, true);
 }
 
 // The static scratch array's address on the device that holds `dev_ptr`,
@@ -851,6 +905,25 @@ hipError_t scratch_for(const void *dev_ptr, uint64_t *addr)
     }
     *addr = cached[dev];
     return hipSuccess;
+}
+
+// The scratch an allocation-free job is refused by: what the entry point
+// documents per buffer, run and group, so that the limit does not move with
+// the layout of the tables (which takes no more than this).
+uint64_t noalloc_need(uint64_t n, uint64_t runs, uint64_t G, uint32_t tiles, bool want_roots)
+{
+    Carver cv;
+    uint64_t off;
+    if (n > 16 || runs > 64) {
+        cv.add(&off, 128 * n);
+        cv.add(&off, 16 * runs);
+        if (want_roots) cv.add(&off, 32 * (n + 1));
+        cv.add(&off, 8 * G);
+    }
+    cv.add(&off, 8 * G * tiles);
+    for (int k = 0; k < 2; ++k) cv.add(&off, 8 * std::max(G * tiles, n));
+    cv.add(&off, 8 * std::max<uint64_t>(n, 1));
+    return cv.total;
 }
 
 // Clears c->no_events when the call that set it returns.
@@ -915,7 +988,8 @@ int pcs_ctx_create(void *d_arena, uint64_t arena_bytes, void *hip_stream, pcs_ct
         pcs_ctx_destroy(c);
         return PCS_E_HIP;
     }
-    if (hipHostMalloc(&c->na_host, kNoAllocStagingBytes, hipHostMallocDefault) != hipSuccess ||
+    if (hipHostMalloc(&c->na_host, kNoAllocStagingBytes, hipHostMallocMapped) != hipSuccess ||
+        hipHostGetDevicePointer(&c->na_dev, c->na_host, 0) != hipSuccess ||
         hipEventCreateWithFlags(&c->na_ev, hipEventDisableTiming) != hipSuccess ||
         scratch_for(d_arena, &c->scratch_dev) != hipSuccess) {
         pcs_ctx_destroy(c);
@@ -959,8 +1033,7 @@ int pcs_chunk_counts(const pcs_buf *bufs, uint32_t n, uint64_t *chunks, uint64_t
     uint64_t t = 0;
     for (uint32_t i = 0; i < n; ++i) {
         Layout lay;
-        std::vector<Run> rs;
-        if (int st = check_buf(nullptr, bufs[i], i, &lay, &rs)) return st;
+        if (int st = check_buf(nullptr, bufs[i], i, &lay)) return st;
         if (chunks) chunks[i] = lay.nchunks;
         t += lay.nchunks;
     }
@@ -976,14 +1049,14 @@ int pcs_fingerprint(pcs_ctx *c, const pcs_buf *bufs, uint32_t n, uint64_t *d_has
     if (n > (1u << 24)) return fail(c, PCS_E_INVAL, "too many buffers");
     Job job;
     if (int st = add_buffers(c, job, bufs, n, 0)) return st;
-    std::vector<RootDst> rdst(n), sdst(1);
+    std::vector<RootDst> sdst(1);
     for (uint32_t b = 0; b < n; ++b) {
         job.bufs[b].hash_dst[0] = d_hashes ? (uint64_t)(d_hashes + job.bufs[b].chunk_begin) : 0;
-        rdst[b].d[0] = d_roots ? (uint64_t)(d_roots + b) : 0;
+        job.bufs[b].root_dst[0] = d_roots ? (uint64_t)(d_roots + b) : 0;
     }
     sdst[0].d[0] = (uint64_t)d_sroot;
     settle(c, false);
-    return run_hash_job(c, job, false, {n}, rdst, sdst, d_roots || d_sroot);
+    return run_hash_job(c, job, false, {n}, sdst, d_roots || d_sroot);
 }
 
 int pcs_fingerprint_noalloc(pcs_ctx *c, const pcs_buf *bufs, uint32_t n, uint64_t *d_hashes, uint64_t *d_roots,
@@ -995,35 +1068,37 @@ int pcs_fingerprint_noalloc(pcs_ctx *c, const pcs_buf *bufs, uint32_t n, uint64_
     if (!c->scratch_dev) return fail(c, PCS_E_HIP, "no static scratch on this device");
     Job job;
     if (int st = add_buffers(c, job, bufs, n, 0)) return st;
-    if (job.runs.size() > kNoAllocMaxRuns)
-        return fail(c, PCS_E_INVAL, "at most %u physical runs without allocation (%zu given)", kNoAllocMaxRuns,
-                    job.runs.size());
+    if (job.nruns > kNoAllocMaxRuns)
+        return fail(c, PCS_E_INVAL, "at most %u physical runs without allocation (%llu given)", kNoAllocMaxRuns,
+                    (unsigned long long)job.nruns);
     const uint64_t G = job.ngroups;
     const bool want_roots = d_roots || d_sroot;
-    for (uint32_t b = 0; b < n; ++b) job.bufs[b].hash_dst[0] = d_hashes ? (uint64_t)(d_hashes + job.bufs[b].chunk_begin) : 0;
+    for (uint32_t b = 0; b < n; ++b) {
+        job.bufs[b].hash_dst[0] = d_hashes ? (uint64_t)(d_hashes + job.bufs[b].chunk_begin) : 0;
+        job.bufs[b].root_dst[0] = d_roots ? (uint64_t)(d_roots + b) : 0;
+    }
     const bool small = is_small(job);
     const uint32_t tiles = tile_split(G);
-    const uint64_t per_tile = kGroupChunks / tiles;
 
     // Scratch layout: [job tables][Merkle lists] (uploaded; large jobs only),
     // [group map (large jobs)][tile nodes][two Merkle levels][buffer roots].
     std::vector<MerkleList> lists;
     Carver cv;
-    uint64_t o_bufs = 0, o_runs = 0, o_lists = 0, o_map = 0, o_nodes, o_sa, o_sb, o_roots;
+    uint64_t o_bufs = 0, o_lists = 0, o_map = 0, o_nodes, o_sa, o_sb, o_roots;
     if (!small) {
         cv.add(&o_bufs, sizeof(JobBuf) * n);
-        cv.add(&o_runs, sizeof(Run) * job.runs.size());
         if (want_roots) cv.add(&o_lists, sizeof(MerkleList) * (n + 1));
     }
     const uint64_t hb = cv.total;
-    if (!small) cv.add(&o_map, sizeof(GroupRef) * G);
+    if (!small) cv.add(&o_map, sizeof(uint32_t) * G);
     cv.add(&o_nodes, 8 * G * tiles);
     cv.add(&o_sa, 8 * std::max<uint64_t>(G * tiles, n));
     cv.add(&o_sb, 8 * std::max<uint64_t>(G * tiles, n));
     cv.add(&o_roots, 8 * std::max<uint32_t>(n, 1));
-    if (cv.total > kStaticScratchBytes)
+    const uint64_t need = std::max(cv.total, noalloc_need(n, job.nruns, G, tiles, want_roots));
+    if (need > kStaticScratchBytes)
         return fail(c, PCS_E_INVAL, "job needs %llu bytes of scratch, more than the %llu bytes available without "
-                    "allocation", (unsigned long long)cv.total, (unsigned long long)kStaticScratchBytes);
+                    "allocation", (unsigned long long)need, (unsigned long long)kStaticScratchBytes);
     if (hb > kNoAllocStagingBytes)
         return fail(c, PCS_E_INVAL, "job tables need %llu bytes, more than the %llu bytes of staging",
                     (unsigned long long)hb, (unsigned long long)kNoAllocStagingBytes);
@@ -1031,49 +1106,40 @@ int pcs_fingerprint_noalloc(pcs_ctx *c, const pcs_buf *bufs, uint32_t n, uint64_
     uint64_t *d_nodes = (uint64_t *)(base + o_nodes);
     uint64_t *d_sa = (uint64_t *)(base + o_sa), *d_sb = (uint64_t *)(base + o_sb);
     uint64_t *d_rt = (uint64_t *)(base + o_roots);
-    if (want_roots) {
-        for (uint32_t b = 0; b < n; ++b)
-            lists.push_back({job.bufs[b].group_begin * tiles, div_up(job.bufs[b].nchunks, per_tile),
-                             {d_roots ? (uint64_t)(d_roots + b) : 0, 0}});
-        lists.push_back({0, n, {(uint64_t)d_sroot, 0}});
-    }
+    if (want_roots && !small) lists = merkle_lists(job, tiles, {n}, {RootDst{{(uint64_t)d_sroot, 0}}});
     NoEvents guard(c);
     hipStream_t s = c->stream;
     Staged sg;
     sg.small = small;
     if (small) {
-        memset(&sg.arg, 0, sizeof sg.arg);
-        sg.arg.nbuf = n;
-        if (n) memcpy(sg.arg.bufs, job.bufs.data(), sizeof(JobBuf) * n);
-        if (!job.runs.empty()) memcpy(sg.arg.runs, job.runs.data(), sizeof(Run) * job.runs.size());
+        fill_args(job, Use::kHash, &sg.arg);
+        sg.arg.sroot[0] = (uint64_t)d_sroot;
     } else {
-        sg.dev = DevTables{(const JobBuf *)(base + o_bufs), (const Run *)(base + o_runs),
-                           (const GroupRef *)(base + o_map), n, 0};
+        sg.dev = DevTables{(const JobBuf *)(base + o_bufs), (const uint32_t *)(base + o_map), n, 0};
         // The staging buffer is reused once the previous call's copy out of it has run.
         if (c->na_pending) {
             HIP_TRY(c, hipEventSynchronize(c->na_ev));
             c->na_pending = false;
         }
         uint8_t *h = (uint8_t *)c->na_host;
-        memset(h, 0, hb);
         if (n) memcpy(h + o_bufs, job.bufs.data(), sizeof(JobBuf) * n);
-        if (!job.runs.empty()) memcpy(h + o_runs, job.runs.data(), sizeof(Run) * job.runs.size());
         if (want_roots) memcpy(h + o_lists, lists.data(), sizeof(MerkleList) * lists.size());
-        HIP_TRY(c, hipMemcpyAsync((void *)base, h, hb, hipMemcpyHostToDevice, s));
+        if (int st = launch(c, "map", [&] {
+                return launch_stage((uint64_t)c->na_dev, base, hb, (const JobBuf *)((uint64_t)c->na_dev + o_bufs), n,
+                                    (uint32_t *)(base + o_map), s);
+            }))
+            return st;
         HIP_TRY(c, hipEventRecord(c->na_ev, s));
         c->na_pending = true;
-        if (G) {
-            if (int st = launch(c, "map", [&] {
-                    return launch_group_map(sg.dev.bufs, sg.dev.runs, n, G, (GroupRef *)sg.dev.map, s);
-                }))
-                return st;
-        }
     }
     int st = with_tables(sg, [&](const auto &tab) {
-        return launch(c, "hash", [&] { return launch_tile(tab, G, kModeHash, d_nodes, nullptr, 0, s, tiles); });
+        return launch(c, "hash", [&] {
+            return launch_tile(tab, G, kModeHash, want_roots ? d_nodes : nullptr, nullptr, 0, s, tiles);
+        });
     });
     if (st || !want_roots) return st;
-    return run_merkle(c, small, lists, n, base + o_lists, d_nodes, d_sa, d_sb, d_rt);
+    if (small) return run_merkle_args(c, sg.arg, G, tiles, d_nodes, d_sa);
+    return run_merkle(c, lists, n, base + o_lists, d_nodes, d_sa, d_sb, d_rt);
 }
 
 int pcs_classify(pcs_ctx *c, const uint64_t *d_hashes, uint32_t K, const uint64_t *h_chunks, uint32_t n,
@@ -1086,12 +1152,12 @@ int pcs_classify(pcs_ctx *c, const uint64_t *d_hashes, uint32_t K, const uint64_
     Job job;
     for (uint32_t b = 0; b < n; ++b) {
         JobBuf jb{};
-        jb.nchunks = h_chunks[b];
-        jb.chunk_begin = job.nchunks;
-        jb.group_begin = job.ngroups;
+        jb.chunk_begin = (uint32_t)job.nchunks;
+        jb.group_begin = (uint32_t)job.ngroups;
         job.nchunks += h_chunks[b];
         job.ngroups += div_up(h_chunks[b], kGroupChunks);
         if (job.ngroups > kMaxGroups) return fail(c, PCS_E_INVAL, "too many chunks");
+        jb.g.nbytes = h_chunks[b] * kChunk;  // (the groups' limit bounds it)
         job.bufs.push_back(jb);
     }
     if (job.nchunks && !d_hashes) return fail(c, PCS_E_INVAL, "null hashes");
@@ -1101,7 +1167,7 @@ int pcs_classify(pcs_ctx *c, const uint64_t *d_hashes, uint32_t K, const uint64_
     Temp t(c);
     Staged sg;
     uint64_t xd, scr;
-    if (int st = stage(c, job, is_small(job), t, {}, 0, sg, xd, scr)) return st;
+    if (int st = stage(c, job, is_small(job), Use::kHash, t, {}, 0, sg, xd, scr)) return st;
     const uint64_t G = job.ngroups, T = job.nchunks;
     if (sg.small && G <= kClassifyFusedGroups)
         return launch(c, "classify", [&] {
@@ -1151,7 +1217,7 @@ int pcs_distance(pcs_ctx *c, const pcs_buf *bufs, uint32_t n, const uint64_t *d_
         // mask word per group; the scan's total is the number of set bits.
         for (auto &jb : job.bufs) {
             jb.parent_hash = (uint64_t)(d_ref + jb.chunk_begin);
-            jb.parent_chunks = jb.nchunks;
+            jb.parent_chunks = jb.nchunks();
         }
         const uint32_t tiles = tile_split(G);
         Carver cv;
@@ -1163,7 +1229,7 @@ int pcs_distance(pcs_ctx *c, const pcs_buf *bufs, uint32_t n, const uint64_t *d_
         Staged sg;
         uint64_t xd, scr;
         settle(c, false);
-        if (int st = stage(c, job, is_small(job), t, {}, cv.total, sg, xd, scr)) return st;
+        if (int st = stage(c, job, is_small(job), Use::kDiff, t, {}, cv.total, sg, xd, scr)) return st;
         uint64_t *d_mask = (uint64_t *)(scr + o_mask), *d_offs = (uint64_t *)(scr + o_offs);
         uint64_t *d_total = (uint64_t *)(scr + o_total);
         hipStream_t s = c->stream;
@@ -1334,8 +1400,6 @@ int pcs_checkpoint(pcs_ctx *c, const pcs_buf *plan, uint32_t n, pcs_snap parent,
     // A small job fingerprints and diffs as sub-tiles; the Merkle lists then
     // reduce one node per sub-tile (an aligned 8-chunk subtree).
     const uint32_t tiles = tile_split(G);
-    const uint64_t per_tile = kGroupChunks / tiles;
-    std::vector<MerkleList> lists;
     for (uint32_t b = 0; b < n; ++b) {
         JobBuf &jb = job.bufs[b];
         jb.hash_dst[0] = c->arena_dev + node->hashes_off + 8 * jb.chunk_begin;
@@ -1348,10 +1412,10 @@ int pcs_checkpoint(pcs_ctx *c, const pcs_buf *plan, uint32_t n, pcs_snap parent,
         } else {
             jb.parent_slot0 = par->payload_off + par->comp_off[b];
         }
-        lists.push_back({jb.group_begin * tiles, div_up(jb.nchunks, per_tile),
-                         {c->arena_dev + node->roots_off + 8 * b, d_roots ? (uint64_t)(d_roots + b) : 0}});
+        jb.root_dst[0] = c->arena_dev + node->roots_off + 8 * b;
+        jb.root_dst[1] = d_roots ? (uint64_t)(d_roots + b) : 0;
     }
-    lists.push_back({0, n, {c->arena_dev + node->roots_off + 8 * n, (uint64_t)d_sroot}});
+    const RootDst sdst{{c->arena_dev + node->roots_off + 8 * n, (uint64_t)d_sroot}};
 
     // Where the scan places the slots: in the segment (pipelined), nowhere
     // (exact: the host places them once it has read the count from pair 0),
@@ -1397,7 +1461,9 @@ int pcs_checkpoint(pcs_ctx *c, const pcs_buf *plan, uint32_t n, pcs_snap parent,
     // A small job (tables in kernel arguments) on the pipelined path runs as
     // two launches: fingerprint+diff, then the Merkle lists, the scan, the
     // slot placement and the dirty copy.
-    const bool small = is_small(job) && !exact && G <= kScanCompactMaxGroups;
+    const bool small = is_small(job), two = small && !exact && G <= kScanCompactMaxGroups;
+    std::vector<MerkleList> lists;
+    if (!small) lists = merkle_lists(job, tiles, {n}, {sdst});
     Carver cv;
     uint64_t o_nodes, o_sa, o_sb, o_roots, o_mask, o_offs, o_total;
     cv.add(&o_nodes, 8 * G * tiles);
@@ -1410,8 +1476,11 @@ int pcs_checkpoint(pcs_ctx *c, const pcs_buf *plan, uint32_t n, pcs_snap parent,
     Temp t(c);
     Staged sg;
     uint64_t lists_dev, scr;
-    if (int st = stage(c, job, small, t, small ? std::vector<uint8_t>() : bytes_of(lists), cv.total, sg, lists_dev, scr))
-        return st;
+    if (int st = stage(c, job, small, Use::kDiff, t, bytes_of(lists), cv.total, sg, lists_dev, scr)) return st;
+    if (small) {
+        sg.arg.sroot[0] = sdst.d[0];
+        sg.arg.sroot[1] = sdst.d[1];
+    }
     uint64_t *d_nodes = (uint64_t *)(scr + o_nodes);
     uint64_t *d_sa = (uint64_t *)(scr + o_sa), *d_sb = (uint64_t *)(scr + o_sb);
     uint64_t *d_roots_tmp = (uint64_t *)(scr + o_roots);
@@ -1425,15 +1494,15 @@ int pcs_checkpoint(pcs_ctx *c, const pcs_buf *plan, uint32_t n, pcs_snap parent,
         });
     });
     if (st) return st;
-    if (small) {
-        const ArgLists al = arg_lists(lists, n);
+    if (two) {
         if ((st = launch(c, "incremental", [&] {
-                 return launch_merkle_scan_place(al, d_nodes, d_sa, d_sb, sg.arg, G, d_mask, bump, d_total,
-                                                 c->arena_dev, s);
+                 return launch_merkle_scan_place(sg.arg, tiles, d_nodes, G, d_mask, bump, d_total, c->arena_dev, s);
              })))
             return st;
     } else {
-        if ((st = run_merkle(c, small, lists, n, lists_dev, d_nodes, d_sa, d_sb, d_roots_tmp))) return st;
+        st = small ? run_merkle_args(c, sg.arg, G, tiles, d_nodes, d_sa)
+                   : run_merkle(c, lists, n, lists_dev, d_nodes, d_sa, d_sb, d_roots_tmp);
+        if (st) return st;
         if ((st = launch(c, "incremental", [&] { return launch_scan(d_mask, G, d_offs, d_total, bump, s); })))
             return st;
         if (exact) {
@@ -1523,7 +1592,7 @@ int pcs_restore_verify(pcs_ctx *c, pcs_snap snap, const pcs_buf *dst, uint32_t n
     Temp t(c);
     Staged sg;
     uint64_t xd, scr;
-    if (int st = stage(c, job, is_small(job), t, {}, 0, sg, xd, scr)) return st;
+    if (int st = stage(c, job, is_small(job), Use::kRestore, t, {}, 0, sg, xd, scr)) return st;
     const uint64_t G = job.ngroups;
     return with_tables(sg, [&](const auto &tab) {
         if (int st = launch(c, "verify", [&] {
@@ -1770,9 +1839,8 @@ int pcs_import(pcs_ctx *c, const void *h_src, uint64_t size, pcs_snap *out)
     uint64_t cb = 0;
     for (auto &y : lays) {
         JobBuf jb{};
-        jb.nbytes = y.nbytes;
-        jb.nchunks = y.nchunks;
-        jb.chunk_begin = cb;
+        jb.g.nbytes = y.nbytes;
+        jb.chunk_begin = (uint32_t)cb;
         cb += y.nchunks;
         job.bufs.push_back(jb);
     }
