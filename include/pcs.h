@@ -512,6 +512,8 @@ int pcs_arena_stats(pcs_ctx *ctx, uint64_t *used, uint64_t *free_bytes, uint64_t
  *     (what a kernel trace reports).  Measured on MI355X, it made the step
  *     times of the 1024-session batch (11 ms kernels back to back) more
  *     spread; it suits kernels for which the dispatch latency is not small.
+ * While timing is on, the roots of a small job are reduced in a launch of
+ * their own ("merkle"); otherwise its fingerprint launch finishes them.
  * Any other mode is PCS_E_INVAL.  pcs_kernel_time waits for the stream, then
  * reports the number of launches and their summed duration in milliseconds
  * for the kernel family `name` ("hash", "pack_hash", "pack", "copy",

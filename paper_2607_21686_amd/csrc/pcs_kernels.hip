@@ -302,6 +302,61 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x)
     return x;
 }
 
+// Values that pass between workgroups of one launch go through these, or
+// through agent-scope atomics, and nothing else does: an agent-scope access
+// goes to memory, past the eight XCDs' L2 caches, which are not coherent with
+// one another.  What orders them is the ticket: a wavefront waits until its own
+// stores have reached memory (vmcnt) before the ticket is taken for it, and
+// loads what the others left only after it has seen the last ticket.  So the
+// tickets need no release or acquire of their own, which would write back and
+// invalidate a whole L2 each time (1024 workgroups taking one: 24 us with,
+// 14 us without; at one ticket per eight workgroups 16 us against none
+// measurable).
+template <class V>
+__device__ __forceinline__ void agent_store(V *p, V v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class V>
+__device__ __forceinline__ V agent_load(const V *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Adds to a ticket word for one lane, after this wavefront's stores have
+// reached memory; the word's value before.
+template <class V>
+__device__ __forceinline__ V take_ticket(V *word, V add)
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const V n = __hip_atomic_fetch_add(word, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("" ::: "memory");
+    return n;
+}
+// True in every lane of the last of `of` wavefronts to get here; the ticket
+// is then back at zero.
+__device__ __forceinline__ bool last_wavefront(uint32_t *ticket, uint32_t of)
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    uint32_t last = 0;
+    if ((threadIdx.x & 63) == 0) {
+        last = take_ticket(ticket, 1u) + 1 == of;
+        if (last) agent_store(ticket, 0u);
+    }
+    return __builtin_amdgcn_readfirstlane(last) != 0;
+}
+// The same for whole workgroups (every thread calls it).
+__device__ __forceinline__ bool last_workgroup(uint32_t *ticket, uint32_t of, uint32_t *flag)
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        *flag = take_ticket(ticket, 1u) + 1 == of;
+        if (*flag) agent_store(ticket, 0u);
+    }
+    __syncthreads();
+    return *flag != 0;
+}
+
 // ---------------------------------------------------------------- job tables
 
 // Stages a job's tables for the kernels that follow on the stream: copies
@@ -345,14 +400,16 @@ struct TileBuf {
     uint64_t hash[2];      // addresses of chunk 0's fingerprint outputs
     uint64_t parent_hash;  // diff, verify: address of the fingerprint chunk 0 is compared with
     uint64_t parent_chunks, manifest, parent_manifest, parent_slot0;  // diff
+    uint32_t index;
 };
 
 // Group G's buffer, read by a whole wavefront.
 template <int MODE>
 __device__ __forceinline__ TileBuf tile_buf(const DevTables &tab, uint64_t G)
 {
-    const JobBuf &jb = tab.bufs[__builtin_amdgcn_readfirstlane(tab.map[G])];
     TileBuf b;
+    b.index = __builtin_amdgcn_readfirstlane(tab.map[G]);
+    const JobBuf &jb = tab.bufs[b.index];
     b.g = jb.g;
     b.nchunks = jb.nchunks();
     b.chunk_begin = jb.chunk_begin;
@@ -437,6 +494,7 @@ __device__ __forceinline__ TileBuf tile_buf(const ArgTables &tab, uint64_t G)
     const uint32_t i = lanes.find(G);
     const ArgBuf a = lanes.buf(i);
     TileBuf b;
+    b.index = i;
     b.g = lanes.geom(i, a);
     b.nchunks = chunks_of(a.nbytes);
     b.chunk_begin = a.chunk_begin;
@@ -466,6 +524,8 @@ struct TileInfo {
     uint32_t nv;  // its chunks (0: the buffer's last group ends before this tile)
     bool many;    // a chunk of it spans more than two pieces
     bool ragged;  // its last chunk ends inside a granule
+    uint32_t buf, group_begin;  // the buffer, its first group and its chunks
+    uint64_t nchunks;
     uint64_t hash[2], parent_hash, parent_chunks, manifest, parent_manifest, parent_slot0;
     Geom g;
 };
@@ -507,6 +567,9 @@ __device__ __forceinline__ void tile_setup(const Tab &tab, uint64_t G, uint32_t 
         const bool many = __any(pieces);
         if (t == 0) {
             info->many = many;
+            info->buf = b.index;
+            info->group_begin = (uint32_t)b.group_begin;
+            info->nchunks = b.nchunks;
             info->ragged = (b.g.nbytes & 15) != 0 && c0 + nv == b.nchunks;
         }
         if (many) {
@@ -600,6 +663,89 @@ __device__ __forceinline__ uint64_t chain(uint64_t va, const uint8_t *p)
     return va;
 }
 
+// What the 8-chunk tiles of a small job in the argument tables do at their
+// end, so that no launch has to follow them (tab.tail): the last tile of a
+// group to finish, then the last group of a buffer, then the last buffer of the
+// job, each by the first wavefront of its workgroup.  A step up costs a
+// round trip or two to memory (about 1.5 us); the launch it saves took 4 us and
+// the gap before it.  Needs every buffer non-empty: an empty one has no tile.
+//
+// Roots: `node`, in lane 0, is the tile's.
+__device__ __forceinline__ void tail_roots(const ArgTables &tab, const TileInfo &info, uint64_t *nodes, uint32_t tile_id,
+                                           uint64_t node)
+{
+    TailWords *w = (TailWords *)tab.tail;
+    uint64_t *group_nodes = (uint64_t *)tab.tail_scratch, *buf_roots = group_nodes + gridDim.x / kSmallTiles;
+    const uint32_t lane = threadIdx.x & 63, G = tile_id / kSmallTiles, b = info.buf;
+    const uint64_t left = info.nchunks - (uint64_t)(G - info.group_begin) * kGroupChunks;
+    const uint32_t nt = ((uint32_t)umin(left, kGroupChunks) + 7) / 8;
+    const uint32_t ng = (uint32_t)((info.nchunks + kGroupChunks - 1) / kGroupChunks);
+    // n values of a list of at most 128, as the wavefront's root.
+    const auto reduce = [&](const uint64_t *p, uint32_t n) {
+        uint64_t v = wave_merkle<1, 6>(lane < n ? agent_load(p + lane) : 0, min(n, 64u));
+        if (n > 64) v = node_hash(v, wave_merkle<1, 6>(64 + lane < n ? agent_load(p + 64 + lane) : 0, n - 64));
+        return v;
+    };
+    if (nt > 1) {
+        if (lane == 0) agent_store(nodes + tile_id, node);
+        if (!last_wavefront(w->group[G], nt)) return;
+        node = wave_merkle<1, 3>(lane < nt ? agent_load(nodes + G * kSmallTiles + lane) : 0, nt);
+    }
+    if (ng > 1) {
+        if (lane == 0) agent_store(group_nodes + G, node);
+        if (!last_wavefront(&w->buf[b], ng)) return;
+        node = reduce(group_nodes + info.group_begin, ng);
+    }
+    if (lane == 0) {
+        if (tab.root[0]) ((g_u64 *)tab.root[0])[b] = node;
+        if (tab.root[1]) ((g_u64 *)tab.root[1])[b] = node;
+    }
+    if (!tab.sroot[0] && !tab.sroot[1]) return;
+    if (tab.nbuf > 1) {
+        if (lane == 0) agent_store(buf_roots + b, node);
+        if (!last_wavefront((uint32_t *)&w->job, tab.nbuf)) return;
+        node = reduce(buf_roots, tab.nbuf);
+    }
+    if (lane == 0) {
+        if (tab.sroot[0]) *(g_u64 *)tab.sroot[0] = node;
+        if (tab.sroot[1]) *(g_u64 *)tab.sroot[1] = node;
+    }
+}
+
+// Flags set by a diff or verify (n of them in this tile): the job's number of
+// them to tab.tail_count (diff), or each buffer's label to tab.tail_labels
+// (verify).  The tickets carry the counts; lane 0 alone.
+template <int MODE>
+__device__ __forceinline__ void tail_flags(const ArgTables &tab, const TileInfo &info, uint32_t tile_id, uint32_t n)
+{
+    TailWords *w = (TailWords *)tab.tail;
+    const uint32_t G = tile_id / kSmallTiles;
+    const uint64_t left = info.nchunks - (uint64_t)(G - info.group_begin) * kGroupChunks;
+    const uint32_t nt = ((uint32_t)umin(left, kGroupChunks) + 7) / 8;
+    if (nt > 1) {
+        const uint32_t old = take_ticket(w->group[G], (1u << 16) + n);
+        if ((old >> 16) + 1 != nt) return;
+        agent_store(w->group[G], 0u);
+        n += old & 0xFFFF;
+    }
+    if (MODE == kModeDiff) {
+        const uint64_t old = take_ticket(&w->job, ((uint64_t)1 << 32) + n);
+        if ((old >> 32) + 1 != gridDim.x / kSmallTiles) return;
+        agent_store(&w->job, (uint64_t)0);
+        *(volatile uint64_t *)tab.tail_count = (uint32_t)old + n;
+        __threadfence_system();
+    } else {
+        const uint32_t ng = (uint32_t)((info.nchunks + kGroupChunks - 1) / kGroupChunks);
+        if (ng > 1) {
+            const uint32_t old = take_ticket(&w->buf[info.buf], (1u << 16) + (n ? 1u : 0u));
+            if ((old >> 16) + 1 != ng) return;
+            agent_store(&w->buf[info.buf], 0u);
+            n += old & 0xFFFF;
+        }
+        ((g_u8 *)tab.tail_labels)[info.buf] = n ? 1 : 0;
+    }
+}
+
 // Fingerprint tile kernels (k_hash, k_hash_staggered; the body is
 // hash_tile).  One workgroup = one tile of CPW chunks of one
 // buffer: a whole 64-chunk group, or for small jobs an eighth of one, so
@@ -640,9 +786,9 @@ __device__ __forceinline__ void hash_tile(const Tab &tab, uint64_t *__restrict__
     constexpr bool kFromSlots = MODE == kModeVerify;    // source is the snapshot, destination the pieces
     static_assert(U >= 1 && T % LPS == 0 && kGroupChunks % CPW == 0, "tile shape");
     static_assert(T >= 4 * CPW, "one lane per accumulator");
-    static_assert(CPW == kGroupChunks || MODE != kModeVerify, "verify flags need whole groups");
-    static_assert(kSteps > 1 || (MODE != kModeVerify && (MODE != kModePack || WB)), "one-step tiles store write-back");
-    static_assert(CPW == kGroupChunks || CPW == 8, "a sub-tile is hashed by one wavefront; diff writes one mask byte");
+    constexpr bool kFlags = MODE == kModeDiff || MODE == kModeVerify;
+    static_assert(kSteps > 1 || MODE != kModePack || WB, "one-step tiles store write-back");
+    static_assert(CPW == kGroupChunks || CPW == 8, "a sub-tile is hashed by one wavefront and writes one mask byte");
     __shared__ __attribute__((aligned(16))) uint8_t tile[CPW * kRow];
     __shared__ ChunkLoc cloc[CPW];
     __shared__ TileInfo info;
@@ -656,9 +802,9 @@ __device__ __forceinline__ void hash_tile(const Tab &tab, uint64_t *__restrict__
     tile_setup<MODE, CPW>(tab, G, tile_id % kTiles, arena_base, &info, cloc);
     const uint32_t nv = __builtin_amdgcn_readfirstlane(info.nv);
     if (nv == 0) {
-        // A diff sub-tile owns byte (tile % 8) of its group's dirty mask:
-        // an empty one writes it as 0 so every byte of the mask is defined.
-        if (MODE == kModeDiff && kTiles > 1 && t == 0 && flag_mask)
+        // A sub-tile owns byte (tile % 8) of its group's mask: an empty one
+        // writes it as 0 so every byte of the mask is defined.
+        if (kFlags && kTiles > 1 && t == 0 && flag_mask)
             ((g_u8 *)flag_mask)[G * kTiles + tile_id % kTiles] = 0;
         return;
     }
@@ -766,17 +912,24 @@ __device__ __forceinline__ void hash_tile(const Tab &tab, uint64_t *__restrict__
 #pragma unroll
         for (int k = 0; k < U; ++k) {
             const ChunkLoc &l = cloc[(k * T + t) / LPS];
-            at[k] = (slot < l.split ? l.a1 : l.a2) + slot;
-            clen[k] = l.len;
+            at[k] = (kFromSlots ? l.slot : slot < l.split ? l.a1 : l.a2) + slot;
+            // (slots are whole 4096-byte granules, zero padded)
+            clen[k] = kFromSlots ? (l.len + 15) & ~15u : l.len;
         }
-        load_granules<U>(at, clen, slot, ragged, r);
+        load_granules<U>(at, clen, slot, ragged && !kFromSlots, r);
         asm volatile("" ::: "memory");
 #pragma unroll
         for (int k = 0; k < U; ++k) {
             const uint32_t c = (k * T + t) / LPS;
             if (c < nv) {
-                if (MODE == kModePack) store16(cloc[c].slot + slot, r[k]);
-                stage(c, slot, cloc[c].len, r[k]);
+                const ChunkLoc &l = cloc[c];
+                if (MODE == kModePack) store16(l.slot + slot, r[k]);
+                if (kFromSlots && slot < l.len) {
+                    const uint64_t to = (slot < l.split ? l.a1 : l.a2) + slot;
+                    if (slot + 16 <= l.len) store16_nt(to, r[k]);
+                    else store_partial(to, r[k], l.len - slot);
+                }
+                stage(c, slot, l.len, r[k]);
             }
         }
         __syncthreads();
@@ -883,20 +1036,25 @@ __device__ __forceinline__ void hash_tile(const Tab &tab, uint64_t *__restrict__
             const uint32_t wave = t >> 6, mine = nv > 16 * wave ? (uint32_t)umin(16, nv - 16 * wave) : 0;
             const uint64_t root = wave_merkle<4, CPW == 8 ? 3 : 4>(h, mine);
             if (CPW == 8) {
-                if (t == 0) nodes[tile_id] = root;
+                bool finished = false;
+                if constexpr (std::is_same<Tab, ArgTables>::value && !kFlags) {
+                    finished = tab.tail != 0;
+                    if (finished) tail_roots(tab, info, nodes, tile_id, root);
+                }
+                if (!finished && t == 0) nodes[tile_id] = root;
             } else if ((t & 63) == 0) {
                 partial[wave] = root;
             }
         }
     }
-    if (CPW == 8 && MODE != kModeDiff) return;
+    if (CPW == 8 && !kFlags) return;
     __syncthreads();
     if (t < 64) {
         if (CPW != 8 && nodes) {
             const uint64_t root = wave_merkle<1, 2>(partial[t & 3], (nv + 15) / 16);
             if (t == 0) nodes[tile_id] = root;
         }
-        if (MODE == kModeDiff || MODE == kModeVerify) {
+        if (kFlags) {
             // Bit c of group G's mask = chunk c of the group; a sub-tile
             // writes its 8 bits as byte (tile % 8) of the little-endian word.
             const uint64_t mask = __ballot(t < nv && dflag[t & (CPW - 1)] != 0);
@@ -904,6 +1062,8 @@ __device__ __forceinline__ void hash_tile(const Tab &tab, uint64_t *__restrict__
                 if (kTiles == 1) flag_mask[G] = mask;
                 else ((g_u8 *)flag_mask)[G * kTiles + tile_id % kTiles] = (uint8_t)mask;
             }
+            if constexpr (CPW == 8 && std::is_same<Tab, ArgTables>::value)
+                if (t == 0 && tab.tail) tail_flags<MODE>(tab, info, tile_id, (uint32_t)__popcll(mask));
         }
     }
 }
@@ -2075,40 +2235,6 @@ __device__ __forceinline__ void sel_wave_range(const SelView &v, uint64_t gw, ui
     w1 = v.gf0 + umin(gw * per + per, nfull);
 }
 
-// Values that pass between workgroups of one launch: stored and loaded at
-// agent scope, since the eight XCDs' L2 caches are not coherent with one
-// another.
-template <class V>
-__device__ __forceinline__ void agent_store(V *p, V v)
-{
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <class V>
-__device__ __forceinline__ V agent_load(const V *p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// True in every thread of the last workgroup of the launch to get here (of
-// `of` that do); the ticket is then back at zero.  What the workgroups pass
-// to the last one goes through agent_store or agent-scope atomics: each
-// wavefront waits until its own have reached memory, and thread 0 then takes
-// the ticket, with release and acquire, for the workgroup.  (A __threadfence
-// in every thread does the same and writes the L2 cache back once per
-// wavefront: the selection of 2^20 scores took 309 us with it, 70 us now.)
-__device__ __forceinline__ bool last_workgroup(uint32_t *ticket, uint32_t of, uint32_t *flag)
-{
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint32_t n = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1;
-        *flag = n == of;
-        if (n == of) agent_store(ticket, 0u);
-    }
-    __syncthreads();
-    return *flag != 0;
-}
-
 // Exclusive prefix of x over the 1024 threads of a workgroup (ws: 33 words).
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t *ws)
 {
@@ -2435,7 +2561,6 @@ hipError_t launch_tile(const Tab &tab, uint64_t ngroups, int mode, uint64_t *nod
 {
     if (ngroups == 0) return hipSuccess;
     const bool split = tiles_per_group != 1;
-    if (split && (mode != kModeHash && mode != kModePack && mode != kModeDiff)) return hipErrorInvalidValue;
     Stagger stg{0, 0};
     if (!split && (mode == kModePack || mode == kModeVerify) && dev.cus && dev.wall_khz &&
         ngroups >= (uint64_t)kStaggerMinRounds * dev.cus && ngroups <= (uint64_t)kStaggerMaxRounds * dev.cus)
@@ -2443,15 +2568,18 @@ hipError_t launch_tile(const Tab &tab, uint64_t ngroups, int mode, uint64_t *nod
     const dim3 grid((uint32_t)(ngroups * tiles_per_group));
     if (tiles_per_group == kSmallTiles) {
         constexpr int kCPW = kGroupChunks / kSmallTiles;
-        static_assert(kCPW == 8, "a diff sub-tile writes one mask byte");
+        static_assert(kCPW == 8, "a sub-tile writes one mask byte");
         if (mode == kModeHash)
             run_kernel((k_hash<Tab, kModeHash, kSmallLanes, kSmallSlice, kCPW, false>), grid, dim3(kSmallLanes), s,
                        tab, nodes, flag_mask, arena_base);
         else if (mode == kModePack)  // sub-tile jobs are far within the write-back bound
             run_kernel((k_hash<Tab, kModePack, kSmallLanes, kSmallSlice, kCPW, true>), grid, dim3(kSmallLanes), s, tab,
                        nodes, flag_mask, arena_base);
-        else
+        else if (mode == kModeDiff)
             run_kernel((k_hash<Tab, kModeDiff, kSmallLanes, kSmallSlice, kCPW, false>), grid, dim3(kSmallLanes), s,
+                       tab, nodes, flag_mask, arena_base);
+        else
+            run_kernel((k_hash<Tab, kModeVerify, kSmallLanes, kSmallSlice, kCPW, false>), grid, dim3(kSmallLanes), s,
                        tab, nodes, flag_mask, arena_base);
         return hipGetLastError();
     }

@@ -163,6 +163,28 @@ constexpr uint32_t xcd_tile_of(uint32_t b, uint32_t nb)
     return x * per + (x < rem ? x : rem) + (i + x * (n / kXcds)) % n;
 }
 
+// Words of the arena's first unit, which the library keeps (byte offsets).
+// Bump: two bump words of incremental slot placement and a call's payload
+// top.  Select: tickets and the first histogram of a large bank's selection,
+// zero between calls (the launch that uses them clears them again).
+constexpr uint64_t kUnitBump = 0;
+constexpr uint64_t kUnitSelect = 64;
+constexpr uint32_t kSelectTickets = 4, kSelectFirstBuckets = 256;
+constexpr uint64_t kUnitSelectBytes = 4 * (kSelectTickets + kSelectFirstBuckets);
+// Tail: tickets of the tile launches that finish their own job (TailWords),
+// zero between calls too.
+constexpr uint64_t kUnitTail = 2048 - 8 * 64;
+
+// Tickets of a small job whose 8-chunk tiles finish it (all zero between
+// launches): one per group, 16 bytes apart, one per buffer, one for the job.
+struct TailWords {
+    uint64_t job;
+    uint32_t pad[30];
+    uint32_t buf[96];
+    uint32_t group[kSmallJobGroups][4];
+};
+static_assert(kUnitTail + sizeof(TailWords) <= 4096 && kUnitTail % 128 == 0, "the tickets lie in the arena's first unit");
+
 struct DevTables {
     const JobBuf *bufs;
     const uint32_t *map;  // each group's buffer
@@ -198,12 +220,16 @@ struct ArgTables {
     uint64_t parent_hash;      // diff: parent's chunk i; verify: stored fingerprint of chunk i
     uint64_t parent_manifest;  // diff: parent's manifest (0 if the parent is full)
     uint64_t parent_slot0;     // diff, full parent: arena offset of its chunk 0's slot
+    uint64_t tail;             // sub-tiles that finish their job: device address of the TailWords (0: they do not)
+    uint64_t tail_scratch;     // roots: a value per group, then one per buffer
+    uint64_t tail_count;       // diff: where the number of set mask bits goes (mapped host memory)
+    uint64_t tail_labels;      // verify: a byte per buffer
     ArgRing rings[kArgRings];
     ArgBuf bufs[kArgBufs];
 };
 // Kernel arguments are limited to 4 KiB; a launch passes one ArgTables and at
 // most a few pointers and sizes besides.
-static_assert(sizeof(ArgTables) + 256 <= 4096, "argument tables must fit in the kernel arguments");
+static_assert(sizeof(ArgTables) + 224 <= 4096, "argument tables must fit in the kernel arguments");
 
 // Buffer lists of a Merkle launch that hold more than kMerkleLdsValues
 // values (a buffer of more than 1 GiB): when at most kLongLists of them, a
@@ -220,15 +246,6 @@ struct LongLists {
     uint64_t count[kLongLists];
     uint64_t block_begin[kLongLists + 1];
 };
-
-// Words of the arena's first unit, which the library keeps (byte offsets).
-// Bump: two bump words of incremental slot placement and a call's payload
-// top.  Select: tickets and the first histogram of a large bank's selection,
-// zero between calls (the launch that uses them clears them again).
-constexpr uint64_t kUnitBump = 0;
-constexpr uint64_t kUnitSelect = 64;
-constexpr uint32_t kSelectTickets = 4, kSelectFirstBuckets = 256;
-constexpr uint64_t kUnitSelectBytes = 4 * (kSelectTickets + kSelectFirstBuckets);
 
 // The entry moves of a bank shrink, every part in one launch.  Part p moves
 // the kept entries of entry_bytes eb from src to dst (stage: in place, the
