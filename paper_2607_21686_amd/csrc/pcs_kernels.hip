@@ -1966,36 +1966,6 @@ __device__ __forceinline__ SelSingle sel_single(const SelView &v, uint64_t score
     return s;
 }
 
-// One radix-select pass's choice, in wavefront 0: lane l holds buckets
-// 4l..4l+3 of the histogram, and the bucket where the running count first
-// reaches `need` is the one.  True in the one lane that finds it, with the
-// bucket and the rank of the keep-th key among that bucket's keys.
-__device__ __forceinline__ bool pick_bucket(const uint32_t *hist, uint32_t need, uint32_t lane, uint32_t &bucket,
-                                            uint32_t &rest)
-{
-    const uint32_t h0 = hist[4 * lane], h1 = hist[4 * lane + 1], h2 = hist[4 * lane + 2], h3 = hist[4 * lane + 3];
-    const uint32_t sum = h0 + h1 + h2 + h3;
-    const uint32_t incl = wave_incl_scan(sum);
-    uint32_t cum = incl - sum;
-    if (!(cum < need && incl >= need)) return false;
-    uint32_t d = 4 * lane;
-    if (cum + h0 < need) {
-        cum += h0;
-        ++d;
-        if (cum + h1 < need) {
-            cum += h1;
-            ++d;
-            if (cum + h2 < need) {
-                cum += h2;
-                ++d;
-            }
-        }
-    }
-    bucket = d;
-    rest = need - cum;
-    return true;
-}
-
 // Counts of keys below and equal to K* among the single scores (head pair,
 // tail pair); every lane of wavefront 0 gets them.
 __device__ __forceinline__ void count_singles(const SelSingle &s, uint32_t key, uint32_t prefix, uint32_t (&c)[4])
@@ -2058,99 +2028,123 @@ __device__ __forceinline__ void place_group(const uint32_t (&k)[4], bool ok, uin
     }
 }
 
+// Exclusive prefix of x over the 1024 threads of a workgroup (ws: 33 words).
+__device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t *ws)
+{
+    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const uint32_t incl = wave_incl_scan(x);
+    if (lane == 63) ws[wave] = incl;
+    __syncthreads();
+    if (wave == 0) {
+        const uint32_t w = lane < 16 ? ws[lane] : 0;
+        const uint32_t wi = wave_incl_scan(w);
+        if (lane < 16) ws[16 + lane] = wi - w;
+    }
+    __syncthreads();
+    return incl - x + ws[16 + wave];
+}
+
 // Selection of a bank of at most kSelectOneWorkgroupEntries scores in one
 // workgroup of 1024 lanes: the `keep` best-ranked entries (a smaller key, or
 // an equal key at a lower index, ranks first) in increasing index order.
-//   1. Radix select, most significant byte first: four passes histogram the
-//      candidates' next byte (LDS atomics) and narrow to the bucket that holds
-//      the keep-th smallest key (wavefront 0 finds it with a prefix sum over
-//      the 256 buckets), which ends as K*, with `need` = how many entries
-//      with key K* are kept (those with the lowest indices).
-//   2. Sixteen ranges of a multiple of 64 whole groups, one per wavefront
-//      (up to 1024 groups each lane holds its one group, read once for every
-//      pass), count their keys below K* and equal to K*; the counts of the ranges before a range give the rank
-//      of its first K* key, hence how many entries it keeps, and where its
-//      kept indices go.  The single scores before and after the whole groups
+//   0. Sixteen ranges of a multiple of 64 whole groups, one per wavefront;
+//      each lane holds its R groups of its wavefront's range (the smallest R
+//      of 1, 2, 4 and 8 that does), read once, all loads in flight.
+//      The single scores before and after the whole groups
 //      are ranges of their own, first and last, held by wavefront 0.
+//   1. Radix select, most significant bits first: passes over the next 11, 11
+//      and 10 bits histogram the candidates (LDS atomics, two copies of the
+//      histogram beyond 4096 scores so that fewer wavefronts meet in one) and narrow to the
+//      bucket that holds the keep-th smallest key (a prefix sum over the
+//      buckets finds it), which ends as K*, with `need` = how many entries
+//      with key K* are kept (those with the lowest indices).  Eight-bit
+//      digits put most keys of a pass into a few buckets, whose LDS atomics
+//      serialise.
+//   2. Each range counts its keys below K* and equal to K*; the counts of the
+//      ranges before a range give the rank
+//      of its first K* key, hence how many entries it keeps, and where its
+//      kept indices go.
 //   3. Each wavefront compacts its kept indices with ballots.
 // Larger banks take the multi-workgroup selection (k_sel_*), which follows
 // the same steps with a launch per pass.
-// Up to here one workgroup is as fast (23 us at 16384 scores, 38-41 us at
-// 32768) as the five launches of the multi-workgroup selection (40 us at
-// 32769 to 131072, 70 us at 2^20, 0.14 ms at 2^24, 1.3 ms at 2^28).
+// Measured (us, up to 32768 scores): 5.6 at 512, 6.4 at 4096, 8.4 at 8192, 12.8
+// at 16384, 22 at 32768; reading the scores anew in each of four 8-bit passes,
+// one load in flight, took 13 at 8192 and 38 at 32768.  At 65536 (16 groups a
+// lane) one workgroup takes 42, the five launches 40.
 constexpr uint32_t kSelectOneWorkgroupEntries = 32768;
+constexpr uint32_t kSelDigits = 2048;
+template <int R>
 __global__ __launch_bounds__(1024) void k_shrink_select(uint64_t scores, uint32_t n, uint32_t keep,
                                                         uint32_t *__restrict__ kept)
 {
     // Per range: keys below K* (cnt[r]) and equal to K* (cnt[18 + r]); range 0
     // = the single scores before the whole groups, 1 + w = wavefront w's
     // groups, 17 = the single scores after.
-    __shared__ uint32_t hist[256];
+    constexpr int kSelCopies = R > 1 ? 2 : 1;
+    __shared__ uint32_t hist[kSelCopies][kSelDigits];
     __shared__ uint32_t cnt[36];
+    __shared__ uint32_t ws[33];
     __shared__ uint32_t pick[2];
     const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const SelView v = sel_view(scores, n);
-    const uint64_t nfull = v.gf1 - v.gf0, per = (nfull + 1023) / 1024 * 64;
+    const uint64_t nfull = v.gf1 - v.gf0, per = (nfull + 1023) / 1024 * 64;  // at most 64 R
     const uint64_t w0 = v.gf0 + umin(wave * per, nfull), w1 = v.gf0 + umin(wave * per + per, nfull);
-    const bool resident = nfull <= 1024;  // each lane holds its one group for every pass
     const SelSingle es = sel_single(v, scores, n, lane, wave == 0);
-    uint32_t rk[1][4] = {{0, 0, 0, 0}};
-    bool rok[1] = {false};
-    if (resident && w0 < w1) load_keys<1>(v, w0 + lane, 64, w1, rk, rok);
+    uint32_t rk[R][4];
+    bool rok[R];
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+        rok[u] = false;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) rk[u][j] = 0;
+    }
+    if (w0 < w1) load_keys<R>(v, w0 + lane, 64, w1, rk, rok);
     const uint32_t ek = score_key(es.raw);
+    uint32_t *const mine = hist[wave % kSelCopies];
 
     uint32_t prefix = 0, pmask = 0, need = keep;  // need: 1-based rank of K* among the candidates
-    for (int p = 0; p < 4; ++p) {
-        const uint32_t shift = 24 - 8 * p;
-        if (t < 256) hist[t] = 0;
+#pragma unroll 1
+    for (int p = 0; p < 3; ++p) {
+        const uint32_t shift = p == 0 ? 21 : p == 1 ? 10 : 0, digits = p == 2 ? kSelDigits / 2 : kSelDigits;
+#pragma unroll
+        for (int c = 0; c < kSelCopies; ++c)
+#pragma unroll
+            for (uint32_t i = 0; i < kSelDigits; i += 1024) hist[c][i + t] = 0;
         __syncthreads();
-        if (resident) {
+#pragma unroll
+        for (int u = 0; u < R; ++u)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                hist_add<false>(hist, (rk[0][j] >> shift) & 255u, rok[0] && (rk[0][j] & pmask) == prefix);
-        } else {
-            for (uint64_t g0 = w0; g0 < w1; g0 += 64) {
-                uint32_t k[1][4];
-                bool ok[1];
-                load_keys<1>(v, g0 + lane, 64, w1, k, ok);
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    hist_add<false>(hist, (k[0][j] >> shift) & 255u, ok[0] && (k[0][j] & pmask) == prefix);
-            }
-        }
-        if (wave == 0) hist_add<false>(hist, (ek >> shift) & 255u, es.in && (ek & pmask) == prefix);
+                if (rok[u] && (rk[u][j] & pmask) == prefix) atomicAdd(&mine[(rk[u][j] >> shift) & (digits - 1)], 1u);
+        if (es.in && (ek & pmask) == prefix) atomicAdd(&mine[(ek >> shift) & (digits - 1)], 1u);
         __syncthreads();
-        uint32_t bucket, rest;
-        if (t < 64 && pick_bucket(hist, need, lane, bucket, rest)) {
-            pick[0] = bucket;
-            pick[1] = rest;
+        uint32_t h0 = 0, h1 = 0;  // buckets 2t and 2t + 1
+#pragma unroll
+        for (int c = 0; c < kSelCopies; ++c) {
+            h0 += hist[c][2 * t];
+            h1 += hist[c][2 * t + 1];
+        }
+        const uint32_t before = block_excl_scan(h0 + h1, ws);
+        if (before < need && before + h0 + h1 >= need) {
+            const bool second = before + h0 < need;
+            pick[0] = 2 * t + (second ? 1 : 0);
+            pick[1] = need - before - (second ? h0 : 0);
         }
         __syncthreads();
         prefix |= pick[0] << shift;
-        pmask |= 255u << shift;
+        pmask |= (digits - 1) << shift;
         need = pick[1];
-        __syncthreads();
     }
 
     // 2. Counts per range (wavefront totals, the same in every lane).
     uint32_t lt = 0, eq = 0;
-    const auto count = [&](const uint32_t(&k)[4], bool ok) {
+#pragma unroll
+    for (int u = 0; u < R; ++u)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            lt += (uint32_t)__popcll(__ballot(ok && k[j] < prefix));
-            eq += (uint32_t)__popcll(__ballot(ok && k[j] == prefix));
+            lt += (uint32_t)__popcll(__ballot(rok[u] && rk[u][j] < prefix));
+            eq += (uint32_t)__popcll(__ballot(rok[u] && rk[u][j] == prefix));
         }
-    };
-    if (resident) {
-        count(rk[0], rok[0]);
-    } else {
-        for (uint64_t g0 = w0; g0 < w1; g0 += 64) {
-            uint32_t k[1][4];
-            bool ok[1];
-            load_keys<1>(v, g0 + lane, 64, w1, k, ok);
-            count(k[0], ok[0]);
-        }
-    }
     if (lane == 0) {
         cnt[1 + wave] = lt;
         cnt[19 + wave] = eq;
@@ -2185,17 +2179,8 @@ __global__ __launch_bounds__(1024) void k_shrink_select(uint64_t scores, uint32_
     }
     uint32_t pos, rank;
     range_start(1 + wave, pos, rank);
-    const uint32_t pos_end = pos + lt + (need > rank ? min(need - rank, eq) : 0u);
-    if (resident) {
-        if (pos < pos_end) place_group(rk[0], rok[0], w0 + lane, v.head, prefix, need, pos, rank, kept);
-    } else {
-        for (uint64_t g0 = w0; g0 < w1 && pos < pos_end; g0 += 64) {
-            uint32_t k[1][4];
-            bool ok[1];
-            load_keys<1>(v, g0 + lane, 64, w1, k, ok);
-            place_group(k[0], ok[0], g0 + lane, v.head, prefix, need, pos, rank, kept);
-        }
-    }
+#pragma unroll
+    for (int u = 0; u < R; ++u) place_group(rk[u], rok[u], w0 + 64 * u + lane, v.head, prefix, need, pos, rank, kept);
 }
 
 // ---- multi-workgroup selection (banks of more than kSelectOneWorkgroupEntries
@@ -2233,22 +2218,6 @@ __device__ __forceinline__ void sel_wave_range(const SelView &v, uint64_t gw, ui
     const uint64_t per = (nfull + 64 * nwaves - 1) / (64 * nwaves) * 64;
     w0 = v.gf0 + umin(gw * per, nfull);
     w1 = v.gf0 + umin(gw * per + per, nfull);
-}
-
-// Exclusive prefix of x over the 1024 threads of a workgroup (ws: 33 words).
-__device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t *ws)
-{
-    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const uint32_t incl = wave_incl_scan(x);
-    if (lane == 63) ws[wave] = incl;
-    __syncthreads();
-    if (wave == 0) {
-        const uint32_t w = lane < 16 ? ws[lane] : 0;
-        const uint32_t wi = wave_incl_scan(w);
-        if (lane < 16) ws[16 + lane] = wi - w;
-    }
-    __syncthreads();
-    return incl - x + ws[16 + wave];
 }
 
 // Pass P narrows K* by its bits [kShift, kShift + log2(kBuckets)).
@@ -2772,7 +2741,11 @@ hipError_t launch_shrink_select(const float *scores, uint32_t n, uint32_t keep, 
     if ((uint64_t)scores & 3) return hipErrorInvalidValue;
     const uint64_t sc = (uint64_t)scores;
     if (n <= kSelectOneWorkgroupEntries) {
-        run_kernel(k_shrink_select, dim3(1), dim3(1024), s, sc, n, keep, kept);
+        // R groups of four scores a lane.
+        if (n <= 4096) run_kernel(k_shrink_select<1>, dim3(1), dim3(1024), s, sc, n, keep, kept);
+        else if (n <= 8192) run_kernel(k_shrink_select<2>, dim3(1), dim3(1024), s, sc, n, keep, kept);
+        else if (n <= 16384) run_kernel(k_shrink_select<4>, dim3(1), dim3(1024), s, sc, n, keep, kept);
+        else run_kernel(k_shrink_select<8>, dim3(1), dim3(1024), s, sc, n, keep, kept);
         return hipGetLastError();
     }
     if (!scratch || (scratch & 255) || !unit) return hipErrorInvalidValue;

@@ -87,3 +87,21 @@ def test_large_selection_buckets(pcs, n, kind):
         ctx.bank_shrink([], sd, keep, kept)
         assert np.array_equal(host(kept).view(np.uint32), want), (kind, keep)
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [4095, 4097, 8192, 8193, 16384, 16385, 32767, 32768])
+def test_one_workgroup_selection(pcs, n):
+    """Both sides of the sizes where a lane holds 1, 2, 4 and 8 groups of
+    scores, at every alignment of the first one, with many ties."""
+    rng = np.random.default_rng(n)
+    s = np.round(rng.standard_normal(n + 3) * 50).astype(np.float32)
+    ctx = pcs.Context(arena(4 << 20))
+    sd = torch.from_numpy(s).cuda()
+    for off in range(4):
+        view = sd[off:off + n]
+        for keep in (1, n // 2, n - 1):
+            want, _ = oracle.bank_shrink([], s[off:off + n], keep)
+            kept = torch.zeros(keep, dtype=torch.int32, device="cuda")
+            ctx.bank_shrink([], view, keep, kept)
+            assert np.array_equal(host(kept).view(np.uint32), want), (off, keep)
+    ctx.close()
