@@ -44,9 +44,11 @@ struct Where {
 // addresses this way instead of searching a table of pieces: a search costs a
 // dependent load a step, and a table of many rings does not fit the kernel
 // arguments.
-constexpr Where locate(const Geom &g, uint64_t L)
+struct RingAt {
+    uint64_t base, r;  // the ring's address; the byte's place in its window
+};
+constexpr RingAt ring_at(const Geom &g, uint64_t L)
 {
-    if (g.win == 0) return Where{g.addr + L, g.nbytes - L};
     uint64_t o = (uint64_t)((double)L * g.inv_win);
     int64_t rem = (int64_t)(L - o * g.win);
     if (rem < 0) {
@@ -56,8 +58,13 @@ constexpr Where locate(const Geom &g, uint64_t L)
         ++o;
         rem -= (int64_t)g.win;
     }
-    const uint64_t r = (uint64_t)rem, base = g.addr + o * g.stride;
-    return r < g.first ? Where{base + g.head + r, g.first - r} : Where{base + (r - g.first), g.win - r};
+    return RingAt{g.addr + o * g.stride, (uint64_t)rem};
+}
+constexpr Where locate(const Geom &g, uint64_t L)
+{
+    if (g.win == 0) return Where{g.addr + L, g.nbytes - L};
+    const RingAt p = ring_at(g, L);
+    return p.r < g.first ? Where{p.base + g.head + p.r, g.first - p.r} : Where{p.base + (p.r - g.first), g.win - p.r};
 }
 
 // Where one chunk's bytes lie: byte x (x < len) is at (x < split ? a1 : a2)
@@ -74,17 +81,28 @@ constexpr ChunkLoc chunk_loc(const Geom &g, uint64_t chunk)
 {
     const uint64_t cb = chunk * kChunk, rest = g.nbytes - cb;
     ChunkLoc l{0, 0, 0, 0, (uint32_t)(rest < kChunk ? rest : kChunk)};
-    const Where w = locate(g, cb);
-    if (l.len <= w.left) {
-        l.a1 = l.a2 = w.addr;
+    if (g.win == 0) {
+        l.a1 = l.a2 = g.addr + cb;
         l.split = l.len;
-    } else {  // the buffer goes on after this piece
-        const Where w2 = locate(g, cb + w.left);
-        if (l.len - w.left <= w2.left) {
-            l.a1 = w.addr;
-            l.split = (uint32_t)w.left;
-            l.a2 = w2.addr - w.left;  // byte `split` of the chunk is the second piece's first byte
-        }
+        return l;
+    }
+    const RingAt p = ring_at(g, cb);
+    const bool before = p.r < g.first;  // in the part of the window before the wrap
+    const uint64_t a1 = before ? p.base + g.head + p.r : p.base + (p.r - g.first);
+    const uint64_t left = before ? g.first - p.r : g.win - p.r;
+    if (l.len <= left) {
+        l.a1 = l.a2 = a1;
+        l.split = l.len;
+        return l;
+    }
+    // The buffer goes on after this piece: past the wrap, or in the next ring
+    // (derived, not located anew, which every lane of a tile would wait for).
+    const bool wraps = before && g.first < g.win;
+    const uint64_t next = wraps ? p.base : p.base + g.stride + g.head, left2 = wraps ? g.win - g.first : g.first;
+    if (l.len - left <= left2) {
+        l.a1 = a1;
+        l.split = (uint32_t)left;
+        l.a2 = next - left;  // byte `split` of the chunk is the second piece's first byte
     }
     return l;
 }
