@@ -6,10 +6,11 @@
 // each cut into 4096-byte chunks, and the chunks of one buffer into aligned
 // groups of 64.  One workgroup handles one group (in a job of at most 128
 // groups, an eighth of one); it finds its buffer through a group-to-buffer
-// map (k_group_map) when the tables live in device memory,
-// or by a short search when a small job carries its tables in the kernel
-// arguments (no upload and no map launch).  Groups never straddle
-// buffers, so a group's 64 chunk fingerprints reduce to one Merkle node
+// map (written by k_stage with the tables) when the tables live in device
+// memory, or with one vector load and a ballot when a job carries its tables
+// in the kernel arguments (nothing staged).  Where a ring buffer's bytes lie
+// follows from its shape, head and row by arithmetic; no table of runs is
+// stored.  Groups never straddle buffers, so a group's 64 chunk fingerprints reduce to one Merkle node
 // inside the workgroup (a promote-odd tree over n leaves splits into aligned
 // 64-leaf subtrees), and a group is exactly one word of the classification
 // bitmap.
@@ -1851,6 +1852,9 @@ constexpr int kVerifyStaggerSlice = 1024;
 // nontemporal stores whatever the size (plain ones: the KV ring restore 177
 // -> 196 us, its verified restore 181 -> 196 us).
 constexpr uint32_t kPackWriteBackMaxRounds = kStaggerMaxRounds;
+// LDS no pack tile uses, so that a CU holds one of them: their 64 registers
+// would admit two, and two tiles' interleaved stores are slower (KV ring step
+// 529 -> 536 us, the 1024-session batch 4293 -> 4438 us a pass).
 constexpr uint32_t kPackSpareLds = 48 << 10;
 constexpr int kHashLanes = 256, kHashSlice = 512;
 constexpr int kCopyLanes = 512, kCopySlice = 1024;
@@ -1868,12 +1872,12 @@ constexpr int kCopyLanes = 512, kCopySlice = 1024;
 // 2048 groups is 5% faster on a flat buffer and 1.5% slower on a 64-run KV
 // ring window.
 // A job of many buffers has many partial groups, and a 1024-lane tile of a few
-// chunks holds its CU as long as a full one: with more than 16 buffers wide
-// tiles need at least 32 groups a buffer (fingerprints of 53 buffers of 66 B to
-// 57 MB, 12 groups a buffer: 38 us with wide tiles, 33 with 256 lanes; a diff of
-// 64 buffers of 32 groups each: 94-96 us either way).
+// chunks holds its CU as long as a full one, so wide tiles are for at most 16
+// buffers (fingerprints of 53 buffers of 66 B to 57 MB, 12 groups a buffer: 38
+// us with wide tiles, 33 with 256 lanes; a diff of 64 ring buffers of 32
+// groups each: 98 us with wide tiles, 93.5 with 256 lanes).
 constexpr uint64_t kWideDiffGroups = 2048, kWideHashGroups = 1024;
-inline bool wide_pays(uint32_t nbuf, uint64_t ngroups) { return nbuf <= 16 || ngroups >= 32ull * nbuf; }
+inline bool wide_pays(uint32_t nbuf) { return nbuf <= 16; }
 constexpr int kSmallLanes = 256;  // sub-tiles of small jobs: 8 chunks per workgroup
 // A sub-tile moves whole chunks in one step (8 granules per lane): a small
 // job's time is a tile's latency, one load round trip per step.
@@ -1890,17 +1894,11 @@ __device__ __forceinline__ uint32_t score_key(uint32_t bits)
     return (bits & 0x80000000u) ? ~bits : (bits | 0x80000000u);
 }
 
-// hist[b] += 1 for every lane of the wavefront with m set.  AGG: lanes that
-// share the first such lane's bucket are added with one atomic (ties, the
-// common conflict, cost one LDS atomic per wavefront, not 64 serialised
-// ones); worth its extra steps on long streams only.
-template <bool AGG>
+// hist[b] += 1 for every lane of the wavefront with m set.  Lanes that share
+// the first such lane's bucket are added with one atomic: ties, the common
+// conflict, cost one LDS atomic per wavefront, not 64 serialised ones.
 __device__ __forceinline__ void hist_add(uint32_t *hist, uint32_t b, bool m)
 {
-    if constexpr (!AGG) {
-        if (m) atomicAdd(&hist[b], 1u);
-        return;
-    }
     const uint64_t act = __ballot(m);
     if (!act) return;
     const int leader = __builtin_ctzll(act);
@@ -2263,12 +2261,12 @@ __global__ __launch_bounds__(1024) void k_sel_hist(uint64_t scores, uint32_t n, 
         for (int u = 0; u < kSelU; ++u)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                hist_add<true>(hist, (k[u][j] >> kShift) & (kBuckets - 1), ok[u] && (k[u][j] & kAbove) == prefix);
+                hist_add(hist, (k[u][j] >> kShift) & (kBuckets - 1), ok[u] && (k[u][j] & kAbove) == prefix);
     }
     if (blockIdx.x == 0 && wave == 0) {
         const SelSingle es = sel_single(v, scores, n, lane, true);
         const uint32_t ek = score_key(es.raw);
-        hist_add<true>(hist, (ek >> kShift) & (kBuckets - 1), es.in && (ek & kAbove) == prefix);
+        hist_add(hist, (ek >> kShift) & (kBuckets - 1), es.in && (ek & kAbove) == prefix);
     }
     __syncthreads();
     uint32_t *global = P == 0 ? unit->hist : st->hist;
@@ -2573,7 +2571,7 @@ hipError_t launch_tile(const Tab &tab, uint64_t ngroups, int mode, uint64_t *nod
     constexpr bool kArgTab = std::is_same<Tab, ArgTables>::value;
     switch (mode) {
     case kModeHash:
-        if (kArgTab && ngroups <= kWideHashGroups && wide_pays(tab.nbuf, ngroups))
+        if (kArgTab && ngroups <= kWideHashGroups && wide_pays(tab.nbuf))
             run_kernel((k_hash<Tab, kModeHash, kPackLanes, kHashSlice, kGroupChunks, false>), grid, dim3(kPackLanes), s,
                        tab, nodes, flag_mask, arena_base);
         else
@@ -2592,7 +2590,7 @@ hipError_t launch_tile(const Tab &tab, uint64_t ngroups, int mode, uint64_t *nod
                            kPackSpareLds, s, tab, nodes, flag_mask, arena_base);
         break;
     case kModeDiff:
-        if (kArgTab && ngroups <= kWideDiffGroups && wide_pays(tab.nbuf, ngroups))
+        if (kArgTab && ngroups <= kWideDiffGroups && wide_pays(tab.nbuf))
             run_kernel((k_hash<Tab, kModeDiff, kPackLanes, kHashSlice, kGroupChunks, false>), grid, dim3(kPackLanes), s,
                        tab, nodes, flag_mask, arena_base);
         else
