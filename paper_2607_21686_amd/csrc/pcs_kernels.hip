@@ -1874,7 +1874,7 @@ constexpr int kCopyLanes = 512, kCopySlice = 1024;
 // A job of many buffers has many partial groups, and a 1024-lane tile of a few
 // chunks holds its CU as long as a full one, so wide tiles are for at most 16
 // buffers (fingerprints of 53 buffers of 66 B to 57 MB, 12 groups a buffer: 38
-// us with wide tiles, 33 with 256 lanes; a diff of 64 ring buffers of 32
+// us with wide tiles, 33 with 256 lanes; a diff of 64 buffers of 32
 // groups each: 98 us with wide tiles, 93.5 with 256 lanes).
 constexpr uint64_t kWideDiffGroups = 2048, kWideHashGroups = 1024;
 inline bool wide_pays(uint32_t nbuf) { return nbuf <= 16; }
