@@ -2074,7 +2074,8 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t *ws)
 //      buckets finds it), which ends as K*, with `need` = how many entries
 //      with key K* are kept (those with the lowest indices).  Eight-bit
 //      digits put most keys of a pass into a few buckets, whose LDS atomics
-//      serialise.
+//      serialise.  A bucket that is kept whole ends the search: K* is then the
+//      bucket's largest possible key, and every key equal to it is kept.
 //   2. Each range counts its keys below K* and equal to K*; the counts of the
 //      ranges before a range give the rank
 //      of its first K* key, hence how many entries it keeps, and where its
@@ -2082,8 +2083,9 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t *ws)
 //   3. Each wavefront compacts its kept indices with ballots.
 // Larger banks take the multi-workgroup selection (k_sel_*), which follows
 // the same steps with a launch per pass.
-// Measured (us, up to 32768 scores): 5.6 at 512, 6.4 at 4096, 8.4 at 8192, 12.8
-// at 16384, 22 at 32768; reading the scores anew in each of four 8-bit passes,
+// Measured (us, up to 32768 scores): 5.2 at 512, 5.8 at 4096, 7.5 at 8192, 11.5
+// at 16384, 20 at 32768 (distinct scores; with every pass run, as many ties make
+// it, 5.7, 6.4, 8.4, 12.8 and 22); reading the scores anew in each of four 8-bit passes,
 // one load in flight, took 13 at 8192 and 38 at 32768.  At 65536 (16 groups a
 // lane) one workgroup takes 42, the five launches 40.
 constexpr uint32_t kSelectOneWorkgroupEntries = 32768;
@@ -2099,7 +2101,7 @@ __global__ __launch_bounds__(1024) void k_shrink_select(uint64_t scores, uint32_
     __shared__ uint32_t hist[kSelCopies][kSelDigits];
     __shared__ uint32_t cnt[36];
     __shared__ uint32_t ws[33];
-    __shared__ uint32_t pick[2];
+    __shared__ uint32_t pick[3];
     const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const SelView v = sel_view(scores, n);
     const uint64_t nfull = v.gf1 - v.gf0, per = (nfull + 1023) / 1024 * 64;  // at most 64 R
@@ -2144,11 +2146,17 @@ __global__ __launch_bounds__(1024) void k_shrink_select(uint64_t scores, uint32_
             const bool second = before + h0 < need;
             pick[0] = 2 * t + (second ? 1 : 0);
             pick[1] = need - before - (second ? h0 : 0);
+            pick[2] = second ? h1 : h0;
         }
         __syncthreads();
         prefix |= pick[0] << shift;
         pmask |= (digits - 1) << shift;
         need = pick[1];
+        if (need == pick[2]) {
+            prefix |= ~pmask;
+            need = n;
+            break;
+        }
     }
 
     // 2. Counts per range (wavefront totals, the same in every lane).

@@ -974,7 +974,11 @@ int pcs_ctx_create(void *d_arena, uint64_t arena_bytes, void *hip_stream, pcs_ct
             return PCS_E_HIP;
         }
     }
-    if (hipHostMalloc((void **)&c->counts, 16 * kCountPairs, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
+    // The mapped words and the staging of the allocation-free call in one
+    // pinned block: making one costs a context more than its other parts.
+    const uint64_t words = round_up(16 * kCountPairs, kAlign);
+    if (hipHostMalloc((void **)&c->counts, words + kNoAllocStagingBytes, hipHostMallocMapped | hipHostMallocCoherent) !=
+            hipSuccess ||
         hipHostGetDevicePointer((void **)&c->counts_dev, c->counts, 0) != hipSuccess ||
         hipEventCreateWithFlags(&c->exact_ev, hipEventDisableTiming) != hipSuccess) {
         pcs_ctx_destroy(c);
@@ -1004,9 +1008,9 @@ int pcs_ctx_create(void *d_arena, uint64_t arena_bytes, void *hip_stream, pcs_ct
         pcs_ctx_destroy(c);
         return PCS_E_HIP;
     }
-    if (hipHostMalloc(&c->na_host, kNoAllocStagingBytes, hipHostMallocMapped) != hipSuccess ||
-        hipHostGetDevicePointer(&c->na_dev, c->na_host, 0) != hipSuccess ||
-        hipEventCreateWithFlags(&c->na_ev, hipEventDisableTiming) != hipSuccess ||
+    c->na_host = (uint8_t *)c->counts + words;
+    c->na_dev = (uint8_t *)c->counts_dev + words;
+    if (hipEventCreateWithFlags(&c->na_ev, hipEventDisableTiming) != hipSuccess ||
         scratch_for(d_arena, &c->scratch_dev) != hipSuccess) {
         pcs_ctx_destroy(c);
         return PCS_E_HIP;
@@ -1036,7 +1040,6 @@ int pcs_ctx_destroy(pcs_ctx *c)
     }
     if (c->counts) (void)hipHostFree(c->counts);
     if (c->na_ev) (void)hipEventDestroy(c->na_ev);
-    if (c->na_host) (void)hipHostFree(c->na_host);
     delete c;
     return PCS_OK;
 }
