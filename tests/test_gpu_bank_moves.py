@@ -105,3 +105,27 @@ def test_one_workgroup_selection(pcs, n):
             ctx.bank_shrink([], view, keep, kept)
             assert np.array_equal(host(kept).view(np.uint32), want), (off, keep)
     ctx.close()
+
+
+@pytest.mark.parametrize("low_bits", [0, 9, 20], ids=["ties", "10-bit buckets", "21-bit buckets"])
+@pytest.mark.parametrize("n", [1, 5, 512, 4097, 32768])
+def test_selection_of_whole_buckets(pcs, n, low_bits):
+    """Runs of up to 32 scores that share every key bit above `low_bits`, so
+    that a run is kept whole, all but one, or with one more: the search ends
+    after its first, second or last pass, and the ranges before and after the
+    whole groups take part."""
+    rng = np.random.default_rng([n, low_bits])
+    run = min(32, n)
+    top = (np.arange(n) // run).astype(np.uint32) << np.uint32(max(low_bits, 11))
+    key = (np.uint32(0x3F800000) + top) | rng.integers(0, 1 << low_bits, n).astype(np.uint32)
+    s = np.concatenate([np.zeros(3, np.float32), rng.permutation(key).astype(np.uint32).view(np.float32)])
+    ctx = pcs.Context(arena(4 << 20))
+    sd = torch.from_numpy(s).cuda()
+    for off in range(4):
+        m = min(n, s.size - off)
+        for keep in sorted({min(max(k, 1), m) for k in (run - 1, run, run + 1, m // 2 // run * run, m)}):
+            want, _ = oracle.bank_shrink([], s[off:off + m], keep)
+            kept = torch.zeros(keep, dtype=torch.int32, device="cuda")
+            ctx.bank_shrink([], sd[off:off + m], keep, kept)
+            assert np.array_equal(host(kept).view(np.uint32), want), (off, keep)
+    ctx.close()
