@@ -146,6 +146,9 @@ typedef struct pcs_snap_info {
  * 4096-byte boundary on, in whole 4096-byte units, keeps the first unit for
  * its own bookkeeping words, and PCS_E_INVAL results if fewer than two units
  * remain.  Small pinned host buffers are allocated for descriptor uploads.
+ * Creation enqueues no device work and does not depend on what the arena holds:
+ * other work may still write there until the context's first call.  From that
+ * call on the arena is the context's alone.
  */
 int pcs_ctx_create(void *d_arena, uint64_t arena_bytes, void *hip_stream, pcs_ctx **out);
 

@@ -2518,7 +2518,8 @@ __global__ __launch_bounds__(kMoveLanes) void k_move_entries(const ShrinkParts P
     }
 }
 
-// Clears n words (the arena's first unit, when its context is created).
+// Clears n words (the tickets in the arena's first unit, before a context's
+// first launch that takes any).
 __global__ __launch_bounds__(256) void k_clear(uint64_t addr, uint32_t n)
 {
     for (uint32_t i = threadIdx.x; i < n; i += 256) ((g_u32 *)addr)[i] = 0;

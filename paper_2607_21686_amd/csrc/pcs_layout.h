@@ -184,13 +184,14 @@ constexpr uint32_t xcd_tile_of(uint32_t b, uint32_t nb)
 // Words of the arena's first unit, which the library keeps (byte offsets).
 // Bump: two bump words of incremental slot placement and a call's payload
 // top.  Select: tickets and the first histogram of a large bank's selection,
-// zero between calls (the launch that uses them clears them again).
+// cleared by the context's first call that takes tickets and zero between calls
+// from then on (the launch that uses them clears them again).
 constexpr uint64_t kUnitBump = 0;
 constexpr uint64_t kUnitSelect = 64;
 constexpr uint32_t kSelectTickets = 4, kSelectFirstBuckets = 256;
 constexpr uint64_t kUnitSelectBytes = 4 * (kSelectTickets + kSelectFirstBuckets);
 // Tail: tickets of the tile launches that finish their own job (TailWords),
-// zero between calls too.
+// the same.
 constexpr uint64_t kUnitTail = 2048 - 8 * 64;
 
 // Tickets of a small job whose 8-chunk tiles finish it (all zero between

@@ -101,6 +101,7 @@ struct pcs_ctx {
     // word 1 a call's payload top.
     uint64_t unit_dev = 0, bump_dev = 0, top_dev = 0;
     uint32_t bump_par = 0;
+    bool tickets_clear = false;  // the unit's tickets have been cleared (use_tickets)
 
     pcs::TileDevice dev{0, 0};  // CU count and real-time counter rate of the arena's device (0: unknown)
 
@@ -242,6 +243,25 @@ int temp_alloc(pcs_ctx *c, Temp &t, uint64_t bytes)
     if (!c->arena.alloc(bytes, &t.off))
         return fail(c, PCS_E_NOMEM, "arena cannot hold %llu bytes of scratch", (unsigned long long)bytes);
     t.bytes = bytes;
+    return PCS_OK;
+}
+
+// Before a launch that takes tickets (kUnitSelect, kUnitTail): they must be
+// zero and every launch leaves them so, hence the context's first such call
+// clears them, on its stream like any other work.  Not pcs_ctx_create: creation
+// enqueues nothing, may run while another device is current, and neither
+// depends on what the arena holds nor on who still writes to it.  A clear that
+// is being captured runs at each replay of the graph and not now.
+int use_tickets(pcs_ctx *c)
+{
+    if (c->tickets_clear) return PCS_OK;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusActive;
+    if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess) {
+        capture = hipStreamCaptureStatusActive;
+        (void)hipGetLastError();
+    }
+    HIP_TRY(c, launch_clear(c->unit_dev + kUnitSelect, (uint32_t)(kAlign - kUnitSelect), c->stream));
+    c->tickets_clear = capture == hipStreamCaptureStatusNone;
     return PCS_OK;
 }
 
@@ -681,6 +701,7 @@ int run_hash_job(pcs_ctx *c, Job &job, bool copy, const std::vector<uint32_t> &s
     // families a caller asks for stay apart.)
     const bool finishes = want_roots && small && tail_pays(job) && c->timing == PCS_TIMING_OFF;
     if (finishes) {
+        if (int e = use_tickets(c)) return e;
         sg.arg.tail = c->unit_dev + kUnitTail;
         sg.arg.tail_scratch = (uint64_t)d_sa;
     }
@@ -1003,11 +1024,6 @@ int pcs_ctx_create(void *d_arena, uint64_t arena_bytes, void *hip_stream, pcs_ct
             khz > 0)
             c->dev = TileDevice{(uint32_t)cus, (uint32_t)khz};
     }
-    // Tickets and counters in the unit start at zero and are left at zero.
-    if (launch_clear(c->unit_dev, (uint32_t)kAlign, c->stream) != hipSuccess) {
-        pcs_ctx_destroy(c);
-        return PCS_E_HIP;
-    }
     c->na_host = (uint8_t *)c->counts + words;
     c->na_dev = (uint8_t *)c->counts_dev + words;
     if (hipEventCreateWithFlags(&c->na_ev, hipEventDisableTiming) != hipSuccess ||
@@ -1256,6 +1272,7 @@ int pcs_distance(pcs_ctx *c, const pcs_buf *bufs, uint32_t n, const uint64_t *d_
         settle(c, false);
         if (int st = stage(c, job, small, Use::kDiff, t, {}, cv.total, sg, xd, scr)) return st;
         if (finishes) {
+            if (int e = use_tickets(c)) return e;
             sg.arg.tail = c->unit_dev + kUnitTail;
             sg.arg.tail_count = (uint64_t)c->counts_dev;
         }
@@ -1359,6 +1376,8 @@ int pcs_bank_shrink(pcs_ctx *c, const pcs_bank_part *parts, uint32_t nparts, uin
         any_in_place = any_in_place || sp.stage != 0;
     }
     for (uint32_t p = nparts; p < kShrinkParts; ++p) P.item_begin[p] = P.items;
+    if (select_steps((uint32_t)n_entries) > 1)
+        if (int st = use_tickets(c)) return st;
     for (uint32_t step = 0; step < select_steps((uint32_t)n_entries); ++step)
         if (int st = launch(c, "shrink", [&] {
                 return launch_shrink_select(d_scores, (uint32_t)n_entries, (uint32_t)keep, kept,
@@ -1628,6 +1647,7 @@ int pcs_restore_verify(pcs_ctx *c, pcs_snap snap, const pcs_buf *dst, uint32_t n
     const uint64_t G = job.ngroups;
     const bool finishes = d_bad_labels && sg.small && tail_pays(job);
     if (finishes) {
+        if (int e = use_tickets(c)) return e;
         sg.arg.tail = c->unit_dev + kUnitTail;
         sg.arg.tail_labels = (uint64_t)d_bad_labels;
     }
