@@ -180,7 +180,7 @@ int pcs_fingerprint(pcs_ctx *ctx, const pcs_buf *h_bufs, uint32_t n, uint64_t *d
  * live in a static device array of 16 MiB that every GPU the library runs on
  * holds until the process ends (its address is looked up once per device when
  * the first context on that device is created); the tables of a job of more
- * than 96 buffers, or 8 rings that are not one piece, reach it through a 2 MiB
+ * than 96 buffers, or 16 rings that are not one piece, reach it through a 2 MiB
  * pinned host buffer made by pcs_ctx_create.  The call itself makes no device, pinned or
  * HIP allocation, creates no HIP event (kernel timing skips it) and takes no
  * arena space.
@@ -272,7 +272,7 @@ int pcs_checkpoint_batch(pcs_ctx *ctx, const pcs_buf *h_plans, const uint32_t *h
  * be restored at a new head).  Only window rows are written.  Destinations
  * must not overlap each other.  Returns PCS_E_SHAPE on a layout mismatch.
  * Restores copy out of the snapshot, so two restores of one snapshot (or of
- * a fork) are independent (I3).  A restore of at most 96 buffers, at most 8 of
+ * a fork) are independent (I3).  A restore of at most 96 buffers, at most 16 of
  * them rings in more than one piece, carries its tables in the kernel
  * arguments and takes no arena space; a larger one stages them in arena
  * scratch and returns PCS_E_NOMEM if the arena cannot hold that.

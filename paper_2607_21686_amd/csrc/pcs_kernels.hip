@@ -428,21 +428,23 @@ __device__ __forceinline__ TileBuf tile_buf(const DevTables &tab, uint64_t G)
 }
 
 // The argument tables in a wavefront's registers: lane l holds buffers l and
-// 64 + l % 32 and ring l % 8.  Every load is issued before any is used, so a
+// 64 + l % 32 and ring l % 16.  Every load is issued before any is used, so a
 // workgroup learns its buffer in one round trip to memory; a search, one
 // dependent load a step and several more for the chosen entry, took
 // 5,700 cycles of an 8-chunk tile's 20,000.
-static_assert(kArgBufs == 96 && kArgRings == 8, "lanes of ArgLanes");
+static_assert(kArgBufs == 96 && kArgRings == 16, "lanes of ArgLanes");
 struct ArgLanes {
     ArgBuf lo, hi;
     ArgRing ring;
+    uint32_t ring_buf;
     uint64_t valid_lo, valid_hi, rings;  // ballots
     __device__ __forceinline__ explicit ArgLanes(const ArgTables &t)
     {
         const uint32_t lane = threadIdx.x & 63;
         lo = t.bufs[lane];
         hi = t.bufs[64 + (lane & 31)];
-        ring = t.rings[lane & 7];
+        ring = t.rings[lane & 15];
+        ring_buf = t.ring_buf[lane & 15];
         valid_lo = __ballot(lane < t.nbuf);
         valid_hi = __ballot(lane < 32 && 64 + lane < t.nbuf);
         rings = __ballot(lane < t.nring);
@@ -476,7 +478,7 @@ struct ArgLanes {
     __device__ __forceinline__ Geom geom(uint32_t i, const ArgBuf &b) const
     {
         Geom g{b.addr, b.nbytes, 0, 0, 0, 0, 0};
-        const uint64_t m = __ballot(ring.buf == i) & rings;
+        const uint64_t m = __ballot(ring_buf == i) & rings;
         if (m) {
             const uint32_t l = (uint32_t)__builtin_ctzll(m);
             g.win = lane_word(ring.win, l);

@@ -142,7 +142,7 @@ struct MerkleList {
 //              one session where fingerprints are written.  A workgroup reads
 //              the whole table with a few vector loads, one round trip to
 //              memory, and finds its buffer with a ballot.
-constexpr uint32_t kArgBufs = 96, kArgRings = 8;
+constexpr uint32_t kArgBufs = 96, kArgRings = 16;
 // Small jobs (at most kSmallJobGroups groups) are cut into kSmallTiles
 // sub-tiles per group, so that a few groups still spread over many CUs.
 // Fingerprint and pack tiles then write one Merkle node per sub-tile (an
@@ -228,7 +228,6 @@ constexpr uint64_t kAuxManifest = 1;
 struct ArgRing {
     uint64_t win, first, head, stride;
     double inv_win;
-    uint32_t buf, pad;
 };
 struct ArgTables {
     uint32_t nbuf, nring;
@@ -243,11 +242,13 @@ struct ArgTables {
     uint64_t tail_scratch;     // roots: a value per group, then one per buffer
     uint64_t tail_count;       // diff: where the number of set mask bits goes (mapped host memory)
     uint64_t tail_labels;      // verify: a byte per buffer
+    uint8_t ring_buf[kArgRings];  // the buffer of each ring
     ArgRing rings[kArgRings];
     ArgBuf bufs[kArgBufs];
 };
 // Kernel arguments are limited to 4 KiB; a launch passes one ArgTables and at
 // most a few pointers and sizes besides.
+static_assert(kArgBufs <= 256, "a buffer number fits in ring_buf");
 static_assert(sizeof(ArgTables) + 224 <= 4096, "argument tables must fit in the kernel arguments");
 
 // Buffer lists of a Merkle launch that hold more than kMerkleLdsValues

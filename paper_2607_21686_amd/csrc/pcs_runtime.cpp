@@ -512,13 +512,13 @@ void fill_args(const Job &job, Use use, ArgTables *t)
                 : use == Use::kDiff    ? (jb.parent_hash - t->parent_hash) / 8 | jb.parent_chunks << 32
                                        : 0;
         if (jb.g.win) {
+            t->ring_buf[t->nring] = (uint8_t)b;
             ArgRing &r = t->rings[t->nring++];
             r.win = jb.g.win;
             r.first = jb.g.first;
             r.head = jb.g.head;
             r.stride = jb.g.stride;
             r.inv_win = jb.g.inv_win;
-            r.buf = b;
         }
     }
 }

@@ -1,4 +1,4 @@
-"""Both sides of what a job's argument tables hold (96 buffers, 8 rings in
+"""Both sides of what a job's argument tables hold (96 buffers, 16 rings in
 more than one piece) through every call that reads them: fingerprints, a
 fingerprinted checkpoint, plain and verified restores, an incremental
 checkpoint with a few dirty chunks, classification and distance; buffers are
@@ -136,14 +136,15 @@ def rings_case(pcs, geoms, heads2):
                     lambda: [host(flat_back)] + windows(back, to) + [host(tail_back)])
 
 
-@pytest.mark.parametrize("nring", [1, 7, 8, 9])
+@pytest.mark.parametrize("nring", [1, 7, 8, 9, 15, 16, 17])
 def test_rings(pcs, nring):
     log("tables rings", nring)
+    # (every window wraps, so that each ring is one of the rings the tables count)
     shapes = [(3, 700, 2048, 500), (2, 100, 48, 99), (1, 9, 4096, 5), (64, 40, 256, 33), (5, 64, 1008, 64)]
     geoms, heads2 = [], []
     for i in range(nring):
         outer, cap, row, win = shapes[i % len(shapes)]
-        geoms.append(W.Ring(outer, cap, row, win, cap - 1 - i, cap * row + 16 * (i % 2)))
+        geoms.append(W.Ring(outer, cap, row, win, cap - 1 - i % 3, cap * row + 16 * (i % 2)))
         heads2.append((3 + 5 * i) % cap)
     rings_case(pcs, geoms, heads2)
 
@@ -154,3 +155,59 @@ def test_many_pieces_in_whole_group_tiles(pcs, outer, cap, row, win):
     (16-byte rows: up to eight pieces a chunk; 1 KiB rows wrapping after one)."""
     log("tables many pieces", outer, cap, row, win)
     rings_case(pcs, [W.Ring(outer, cap, row, win, cap - 1)], [cap - 2])
+
+
+@pytest.mark.parametrize("nring", [9, 16])
+def test_rings_take_no_arena_space(pcs, nring):
+    """Up to 16 wrapped rings (one per layer and K or V, say) travel in the
+    kernel arguments: they restore, plain and verified, from an arena with no
+    free unit, and their allocation-free fingerprint stages nothing, so it
+    can be captured."""
+    log("tables rings, full arena", nring)
+    rng = np.random.default_rng(nring)
+    g = W.Ring(1, 70, 1008, 64, 60)
+    side = torch.cuda.Stream()
+    ctx = pcs.Context(arena(8 << 20), stream=side)
+    live = [dev(rng.integers(0, 256, size=g.ring_bytes, dtype=np.uint8)) for _ in range(nring)]
+    back = [torch.zeros_like(t) for t in live]
+    torch.cuda.synchronize()
+
+    def descs(ts):
+        return [pcs.ring(t, g.outer, g.capacity, g.row_bytes, g.head, g.window) for t in ts]
+
+    def windows(ts):
+        return [oracle.ring_window(host(t), g.outer, g.outer_stride, g.capacity, g.row_bytes, g.head, g.window) for t in ts]
+
+    want = windows(live)
+    h, r, s = oracle.fingerprint(want)
+    words = oracle.bitmap_words([oracle.chunk_count(b.size) for b in want])
+    snap = ctx.checkpoint(descs(live), hash=True)
+    one = [pcs.flat(live[0], 16)]
+    with pytest.raises(pcs.PcsError):
+        while True:
+            ctx.checkpoint(one)
+    assert ctx.arena_stats()["free"] == 0
+    ctx.restore(snap, descs(back))
+    assert all(np.array_equal(a, b) for a, b in zip(windows(back), want))
+    for t in back:
+        t.zero_()
+    torch.cuda.synchronize()
+    bad, lab = zeros_u64(words), torch.full((nring,), 7, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    ctx.restore_verify(snap, descs(back), bad, lab)
+    assert all(np.array_equal(a, b) for a, b in zip(windows(back), want))
+    assert not u64(bad)[:words].any() and not host(lab).any()
+    H, R, S = zeros_u64(h.size), zeros_u64(nring), zeros_u64(1)
+    torch.cuda.synchronize()
+    plan = pcs.BufArray(descs(live))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        ctx.fingerprint_noalloc(plan, H, R, S)
+    for _ in range(3):
+        for t in (H, R, S):
+            t.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        assert np.array_equal(u64(H)[:h.size], h) and np.array_equal(u64(R), r) and int(u64(S)[0]) == s
+        ctx.restore(snap, descs(back))  # eager work of the context between replays
+    ctx.close()
