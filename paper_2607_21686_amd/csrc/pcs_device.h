@@ -90,11 +90,11 @@ struct SlotBump {
     uint64_t *host;
 };
 // Slot assignment + dirty copy of an incremental checkpoint in one launch
-// (from the scanned per-group offsets and the dirty masks); writes the whole
-// new manifest.
+// (from the scanned per-group offsets and total and the dirty masks); enters
+// the dirty chunks in the new manifest.
 template <class Tab>
 hipError_t launch_place_dirty(const Tab &tab, uint64_t ngroups, const uint64_t *dirty_mask, const uint64_t *offsets,
-                              const uint64_t *top_word, uint64_t arena_base, hipStream_t s);
+                              const uint64_t *total, const uint64_t *top_word, uint64_t arena_base, hipStream_t s);
 template <class Tab>
 hipError_t launch_classify(const Tab &tab, uint64_t ngroups, const uint64_t *hashes, uint32_t K, uint64_t total,
                            uint64_t *bitmap, hipStream_t s);

@@ -1662,34 +1662,71 @@ __global__ __launch_bounds__(1024) void k_merkle_scan_place(const ArgTables tab,
     }
 }
 
+// The last group whose exclusive offset is at most s, for a whole wavefront
+// (every lane gets it): 64 probes a step, so one to four steps.  Offsets do not
+// decrease and begin at 0; a group without a dirty chunk shares its offset with
+// the next group, so the group found holds slot s.
+__device__ __forceinline__ uint32_t group_of_slot(const uint64_t *offsets, uint32_t ngroups, uint32_t s)
+{
+    uint32_t lo = 0, n = ngroups;
+    while (n > 1) {
+        const uint32_t step = (n + 63) / 64, d = (threadIdx.x & 63) * step;
+        const uint64_t at_most = __ballot(d < n && offsets[lo + (d < n ? d : 0)] <= s);
+        const uint32_t skip = (63 - (uint32_t)__builtin_clzll(at_most)) * step;
+        lo += skip;
+        n = min(step, n - skip);
+    }
+    return __builtin_amdgcn_readfirstlane(lo);
+}
+
 // Slot assignment and dirty copy in one launch (jobs with device tables,
-// or whose slots the host placed, after the scan of the dirty masks): one
-// 256-lane workgroup per group, striding over the job so that a large one
-// launches no more than kPlaceBlocks.  A clean group costs its workgroup one
-// (cached) mask load; the dirty chunks of a group are dealt to its four
-// wavefronts.  The r-th of them takes the group's scanned offset + r as its
-// slot (below the payload top in *top_word), as k_merkle_scan_place; lane 0
-// enters the slot in the manifest and all 64 lanes copy the chunk into it,
-// 64 bytes per lane, zero-padding a partial chunk.  (The diff tiles entered
-// the clean chunks.)  A wavefront per chunk position, dirty or not, took
-// 81 us for 131,072 positions of which 576 were dirty.
+// or whose slots the host placed, after the scan of the dirty masks).  The
+// *total slots are dealt to the wavefronts in equal shares of consecutive
+// slots, at most kPlaceShare at a time; a wavefront finds its share's first
+// group by search and then walks the set bits from there (a clean group in
+// between makes it search again).  Slots follow (buffer, chunk) order below the
+// payload top in *top_word, as k_merkle_scan_place; lane 0 enters the slot in
+// the manifest and all 64 lanes copy the chunk into it, 64 bytes per lane,
+// zero-padding a partial chunk.  (The diff tiles entered the clean chunks.)
+// Bound: the latency of a chunk's copy, about 2 us, times the chunks one
+// wavefront takes, so what matters is an even deal; for large counts HBM.  A
+// workgroup per group put appended state, whose dirty chunks fill a few groups,
+// on a few workgroups: 391 chunks in seven groups of 200 to 400 took 32 us,
+// now 8.7; a wavefront per chunk position, dirty or not, took 81 us for
+// 131,072 positions of which 576 were dirty.  Whole checkpoints of 2 GiB, every
+// chunk dirty, by share: 1 slot 1280 us (a search a chunk), 4 1157, 8 1144, an
+// equal part of the whole 1188 (every wavefront at the same offset of its own
+// 256 KiB), a workgroup per group 1199.
 constexpr uint64_t kPlaceBlocks = 2048;
+constexpr uint32_t kPlaceShare = 8;
 template <class Tab>
-__global__ __launch_bounds__(256) void k_place_dirty(const Tab tab, uint64_t ngroups, const uint64_t *__restrict__ dirty_mask,
+__global__ __launch_bounds__(256) void k_place_dirty(const Tab tab, uint32_t ngroups, const uint64_t *__restrict__ dirty_mask,
                                                      const uint64_t *__restrict__ offsets,
+                                                     const uint64_t *__restrict__ total,
                                                      const uint64_t *__restrict__ top_word, uint64_t arena_base)
 {
     const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    for (uint64_t G = blockIdx.x; G < ngroups; G += gridDim.x) {
+    const uint32_t waves = gridDim.x * 4, count = (uint32_t)*total;  // at most 2^30 chunks
+    const uint32_t share = min((count + waves - 1) / waves, kPlaceShare);
+    const uint64_t top = *top_word;  // arena offset
+    for (uint64_t first = (uint64_t)(blockIdx.x * 4 + wave) * share; first < count; first += (uint64_t)waves * share) {
+        const uint32_t end = (uint32_t)umin(first + share, count);
+        uint32_t s = (uint32_t)first, G = group_of_slot(offsets, ngroups, s);
         uint64_t mask = dirty_mask[G];
-        if (!mask) continue;
-        const TileBuf b = tile_buf<kModeDiff>(tab, G);
-        const uint64_t top = *top_word;  // arena offset
-        uint64_t slot = offsets[G];
-        for (uint32_t r = 0; mask; mask &= mask - 1, ++r, ++slot) {
-            if ((r & 3) != wave) continue;
+        for (uint32_t below = s - (uint32_t)offsets[G]; below; --below) mask &= mask - 1;
+        TileBuf b = tile_buf<kModeDiff>(tab, G);
+        for (; s < end; ++s) {
+            if (!mask) {
+                mask = dirty_mask[++G];  // (slot s lies in a later group)
+                if (!mask) {
+                    G = group_of_slot(offsets, ngroups, s);
+                    mask = dirty_mask[G];
+                }
+                b = tile_buf<kModeDiff>(tab, G);
+            }
             const uint64_t i = (G - b.group_begin) * kGroupChunks + (uint64_t)__builtin_ctzll(mask);
-            const uint64_t slot_off = top - (slot + 1) * kChunk;
+            mask &= mask - 1;
+            const uint64_t slot_off = top - ((uint64_t)s + 1) * kChunk;
             if (lane == 0) ((g_u64 *)b.manifest)[i] = slot_off;
             copy_chunk(b.g, i, arena_base + slot_off, lane);
         }
@@ -2650,11 +2687,14 @@ hipError_t launch_copy(const Tab &tab, uint64_t ngroups, bool pack, uint64_t are
 
 template <class Tab>
 hipError_t launch_place_dirty(const Tab &tab, uint64_t ngroups, const uint64_t *dirty_mask, const uint64_t *offsets,
-                              const uint64_t *top_word, uint64_t arena_base, hipStream_t s)
+                              const uint64_t *total, const uint64_t *top_word, uint64_t arena_base, hipStream_t s)
 {
     if (ngroups == 0) return hipSuccess;
-    const uint32_t blocks = (uint32_t)std::min<uint64_t>(ngroups, kPlaceBlocks);
-    run_kernel((k_place_dirty<Tab>), dim3(blocks), dim3(256), s, tab, ngroups, dirty_mask, offsets, top_word, arena_base);
+    // One wavefront a chunk if every chunk is dirty, up to kPlaceBlocks
+    // workgroups (what the chip holds at once).
+    const uint32_t blocks = (uint32_t)std::min<uint64_t>(ngroups * (kGroupChunks / 4), kPlaceBlocks);
+    run_kernel((k_place_dirty<Tab>), dim3(blocks), dim3(256), s, tab, (uint32_t)ngroups, dirty_mask, offsets, total,
+               top_word, arena_base);
     return hipGetLastError();
 }
 
@@ -2829,7 +2869,7 @@ hipError_t launch_reverse_slots(uint64_t top, uint64_t dst, uint64_t n, hipStrea
                                          uint32_t, TileDevice);                                                   \
     template hipError_t launch_copy<Tab>(const Tab &, uint64_t, bool, uint64_t, hipStream_t, uint32_t);           \
     template hipError_t launch_place_dirty<Tab>(const Tab &, uint64_t, const uint64_t *, const uint64_t *,        \
-                                                const uint64_t *, uint64_t, hipStream_t);                         \
+                                                const uint64_t *, const uint64_t *, uint64_t, hipStream_t);       \
     template hipError_t launch_classify<Tab>(const Tab &, uint64_t, const uint64_t *, uint32_t, uint64_t,         \
                                              uint64_t *, hipStream_t);                                            \
     template hipError_t launch_labels<Tab>(const Tab &, const uint64_t *, uint8_t *, hipStream_t);

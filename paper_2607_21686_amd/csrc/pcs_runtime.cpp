@@ -1572,7 +1572,7 @@ int pcs_checkpoint(pcs_ctx *c, const pcs_buf *plan, uint32_t n, pcs_snap parent,
         }
         st = with_tables(sg, [&](const auto &tab) {
             return launch(c, "incremental", [&] {
-                return launch_place_dirty(tab, G, d_mask, d_offs, top_word, c->arena_dev, s);
+                return launch_place_dirty(tab, G, d_mask, d_offs, d_total, top_word, c->arena_dev, s);
             });
         });
         if (st) return st;
