@@ -621,6 +621,16 @@ __device__ __forceinline__ void load_granules(const uint64_t (&at)[U], const uin
     }
 }
 
+// Where byte x (x < l.len, a multiple of 16) of a tile's chunk c lies, in a tile
+// that has a chunk of more than two pieces: from the chunk's description, or,
+// for such a chunk itself, from the geometry.
+__device__ __forceinline__ uint64_t granule_at(const TileInfo &info, const ChunkLoc &l, uint32_t c, uint32_t x)
+{
+    if (x >= l.len) return 0;
+    if (l.a1) return (x < l.split ? l.a1 : l.a2) + x;
+    return locate(info.g, (info.c0 + c) * kChunk + x).addr;
+}
+
 // Selects word i (0..3) of a 32-byte tail held in registers.
 __device__ __forceinline__ uint64_t sel4(uint64_t a, uint64_t b, uint64_t c, uint64_t d, uint32_t i)
 {
@@ -891,33 +901,56 @@ __device__ __forceinline__ void hash_tile(const Tab &tab, uint64_t *__restrict__
     };
 
     if (__builtin_amdgcn_readfirstlane(info.many)) {
-        // A tile with a chunk of more than two pieces: every granule's address
-        // from the geometry, one at a time (a loop of its own: its arithmetic
-        // beside the other loop's prefetched slice does not fit the registers).
+        // A tile with a chunk of more than two pieces: a granule's place is read
+        // from LDS, or located, each time (a loop of its own: the other one keeps
+        // its granules' places in registers).  The next slice is fetched ahead
+        // of the hashing where the registers of a second workgroup per CU
+        // are not at stake.  One granule at a time, located anew each, took for
+        // 2048 rings of 257 KiB, each with one such chunk, 193 us a
+        // fingerprint, 261 a pack with fingerprint, 299 a restore (k_copy) and
+        // 268 a verified one; so 107, 210, 186 and 200 (without such chunks
+        // 99, 205, 180 and 192).
+        constexpr bool kAhead = T != 1024 || MODE == kModePack || MODE == kModeVerify;
+        uint4 r[U];
+        const auto load_slice = [&](uint32_t x) {
+            uint64_t at[U];
+            uint32_t clen[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const uint32_t c = (k * T + t) / LPS;
+                const ChunkLoc &l = cloc[c];
+                // (slots are whole 4096-byte granules, zero padded)
+                at[k] = kFromSlots ? l.slot + x : granule_at(info, l, c, x);
+                clen[k] = kFromSlots ? (l.len + 15) & ~15u : l.len;
+            }
+            load_granules<U>(at, clen, x, ragged && !kFromSlots, r);
+        };
+        load_slice(slot);
         fetch_parent();
         for (uint32_t step = 0; step < kSteps; ++step) {
             const uint32_t x = step * SL + slot;
-#pragma unroll 1
+#pragma unroll
             for (int k = 0; k < U; ++k) {
                 const uint32_t c = (k * T + t) / LPS;
-                if (c >= nv) break;
-                const uint32_t clen = cloc[c].len;
-                const uint64_t at = x < clen ? locate(info.g, (c0 + c) * kChunk + x).addr : 0;
-                uint4 v = make_uint4(0, 0, 0, 0);
-                if (x < clen) {
-                    if (kFromSlots) v = load16_nt(cloc[c].slot + x);
-                    else v = x + 16 <= clen ? load16_nt(at) : load_partial(at, clen - x);
+                if (c < nv) {
+                    const ChunkLoc &l = cloc[c];
+                    if (MODE == kModePack) {
+                        if (WB) store16(l.slot + x, r[k]);
+                        else store16_nt(l.slot + x, r[k]);
+                    }
+                    if (kFromSlots && x < l.len) {
+                        const uint64_t to = granule_at(info, l, c, x);
+                        if (x + 16 <= l.len) store16_nt(to, r[k]);
+                        else store_partial(to, r[k], l.len - x);
+                    }
+                    stage(c, x, l.len, r[k]);
                 }
-                if (MODE == kModePack) store16(cloc[c].slot + x, v);
-                if (kFromSlots && x < clen) {
-                    if (x + 16 <= clen) store16_nt(at, v);
-                    else store_partial(at, v, clen - x);
-                }
-                stage(c, x, clen, v);
             }
             __syncthreads();
+            if (kAhead && step + 1 < kSteps) load_slice(x + SL);
             if (t < kHashers) hash_slice(step);
             __syncthreads();
+            if (!kAhead && step + 1 < kSteps) load_slice(x + SL);
         }
     } else if constexpr (kSteps == 1) {
         // Whole chunks in one step: nothing is prefetched, so a granule's
@@ -1383,20 +1416,37 @@ __global__ __launch_bounds__(T) void k_copy(const Tab tab, uint64_t arena_base, 
     if (__builtin_amdgcn_readfirstlane(info.nv) == 0) return;  // a buffer's last group may end before this tile
     const uint32_t slot = (t % LPS) * 16;
     if (__builtin_amdgcn_readfirstlane(info.many)) {
-        // A tile with a chunk of more than two pieces, one granule at a time
-        // (see hash_tile).
-        const uint32_t nv = info.nv;
-        for (uint32_t g = t; g < nv * (kChunk / 16); g += T) {
-            const uint32_t c = g / (kChunk / 16), x = g % (kChunk / 16) * 16, clen = cloc[c].len;
-            const uint64_t at = x < clen ? locate(info.g, (info.c0 + c) * kChunk + x).addr : 0;
-            if (PACK) {
-                uint4 v = make_uint4(0, 0, 0, 0);
-                if (x < clen) v = x + 16 <= clen ? load16_nt(at) : load_partial(at, clen - x);
-                store16(cloc[c].slot + x, v);
-            } else if (x < clen) {
-                const uint4 v = load16_nt(cloc[c].slot + x);
-                if (x + 16 <= clen) store16_nt(at, v);
-                else store_partial(at, v, clen - x);
+        // A tile with a chunk of more than two pieces (see hash_tile).
+        static_assert(T % (kChunk / 16) == 0, "a lane's granules lie at the same place of their chunks");
+        const uint32_t x = t % (kChunk / 16) * 16, nv = info.nv;
+        const bool ragged = __builtin_amdgcn_readfirstlane(info.ragged);
+#pragma unroll 1
+        for (uint32_t g = t; g < CPW * (kChunk / 16); g += U * T) {
+            uint64_t at[U];
+            uint32_t clen[U];
+            uint4 v[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const uint32_t c = (g + k * T) / (kChunk / 16);
+                const ChunkLoc &l = cloc[c];
+                at[k] = PACK ? granule_at(info, l, c, x) : l.slot + x;
+                clen[k] = PACK ? l.len : (l.len + 15) & ~15u;  // slots are whole 4096-byte granules
+            }
+            load_granules<U>(at, clen, x, PACK && ragged, v);
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const uint32_t c = (g + k * T) / (kChunk / 16);
+                const ChunkLoc &l = cloc[c];
+                if (PACK) {
+                    if (c >= nv) continue;
+                    if (wb) store16(l.slot + x, v[k]);
+                    else store16_nt(l.slot + x, v[k]);
+                } else if (x < l.len) {
+                    const uint64_t to = granule_at(info, l, c, x);
+                    if (x + 16 <= l.len) store16_nt(to, v[k]);
+                    else store_partial(to, v[k], l.len - x);
+                }
             }
         }
         return;

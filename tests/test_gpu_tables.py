@@ -149,10 +149,13 @@ def test_rings(pcs, nring):
     rings_case(pcs, geoms, heads2)
 
 
-@pytest.mark.parametrize("outer,cap,row,win", [(32000, 90, 16, 80), (700, 70, 1024, 48)])
+@pytest.mark.parametrize("outer,cap,row,win", [(32000, 90, 16, 80), (700, 70, 1024, 48), (9, 265, 1024, 257),
+                                               (150, 265, 1024, 257)])
 def test_many_pieces_in_whole_group_tiles(pcs, outer, cap, row, win):
     """More than 128 groups of windows whose pieces are shorter than a chunk
-    (16-byte rows: up to eight pieces a chunk; 1 KiB rows wrapping after one)."""
+    (16-byte rows: up to eight pieces a chunk; 1 KiB rows wrapping after one).
+    The last two: tiles in which one chunk of three pieces stands among whole
+    ones, in eighths of groups and in whole groups."""
     log("tables many pieces", outer, cap, row, win)
     rings_case(pcs, [W.Ring(outer, cap, row, win, cap - 1)], [cap - 2])
 
