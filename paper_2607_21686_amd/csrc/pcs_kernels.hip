@@ -631,12 +631,6 @@ __device__ __forceinline__ uint64_t granule_at(const TileInfo &info, const Chunk
     return locate(info.g, (info.c0 + c) * kChunk + x).addr;
 }
 
-// Selects word i (0..3) of a 32-byte tail held in registers.
-__device__ __forceinline__ uint64_t sel4(uint64_t a, uint64_t b, uint64_t c, uint64_t d, uint32_t i)
-{
-    return i == 0 ? a : i == 1 ? b : i == 2 ? c : d;
-}
-
 // First-round stagger.  The workgroups of a launch's first round (one per CU)
 // all start together and then move their slices in step: every CU reads the
 // same offsets within its chunks at the same moment.  In jobs of a few
@@ -818,6 +812,11 @@ __device__ __forceinline__ void hash_tile(const Tab &tab, uint64_t *__restrict__
     __shared__ TileInfo info;
     __shared__ uint64_t partial[4];
     __shared__ uint32_t dflag[CPW];
+    // A chunk's last bytes past its whole stripes, zero padded; written and
+    // read by the chunk's own lane quad.  (In registers, eight a lane for the
+    // rare chunk that has any, they put the 1024-lane diff tile over its 64:
+    // 12 bytes a lane of scratch memory.)
+    __shared__ uint64_t tail[CPW][4];
 
     const uint32_t tile_id = xcd_tile();
     if constexpr (STAGGER) stagger_start(stg);
@@ -861,7 +860,6 @@ __device__ __forceinline__ void hash_tile(const Tab &tab, uint64_t *__restrict__
     };
     // Accumulator q with seed 0: P1 + P2, P2, 0, -P1.
     uint64_t va = q == 0 ? P1 + P2 : q == 1 ? P2 : q == 2 ? 0 : 0 - P1;
-    uint64_t tw0 = 0, tw1 = 0, tw2 = 0, tw3 = 0;  // the chunk's tail (< 32 bytes), zero padded
 
     // A granule's words to the LDS tile.
     const auto stage = [&](uint32_t c, uint32_t x, uint32_t clen, uint4 v) {
@@ -890,12 +888,7 @@ __device__ __forceinline__ void hash_tile(const Tab &tab, uint64_t *__restrict__
             }
             const uint32_t tp = nst * 32;  // tail start, 32-aligned, inside this slice if here
             if (tp < len && tp >= step * SL && tp < (step + 1) * SL) {
-                const ulonglong2 x = *reinterpret_cast<const ulonglong2 *>(row + tp - step * SL);
-                const ulonglong2 y = *reinterpret_cast<const ulonglong2 *>(row + tp - step * SL + 16);
-                tw0 = x.x;
-                tw1 = x.y;
-                tw2 = y.x;
-                tw3 = y.y;
+                tail[ci][q] = *reinterpret_cast<const uint64_t *>(row + tp - step * SL + 8 * q);
             }
         }
     };
@@ -1058,16 +1051,16 @@ __device__ __forceinline__ void hash_tile(const Tab &tab, uint64_t *__restrict__
         uint32_t o = 0;
         const uint32_t rem = len - nst * 32;
         for (; rem - o >= 8; o += 8) {
-            acc ^= xround(0, sel4(tw0, tw1, tw2, tw3, o >> 3));
+            acc ^= xround(0, tail[ci][o >> 3]);
             acc = rotl(acc, 27) * P1 + P4;
         }
         if (rem - o >= 4) {
-            acc ^= (uint64_t)(uint32_t)sel4(tw0, tw1, tw2, tw3, o >> 3) * P1;
+            acc ^= (uint64_t)(uint32_t)tail[ci][o >> 3] * P1;
             acc = rotl(acc, 23) * P2 + P3;
             o += 4;
         }
         for (; o < rem; ++o) {
-            const uint64_t byte = (sel4(tw0, tw1, tw2, tw3, o >> 3) >> (8 * (o & 7))) & 0xFF;
+            const uint64_t byte = (tail[ci][o >> 3] >> (8 * (o & 7))) & 0xFF;
             acc ^= byte * P5;
             acc = rotl(acc, 11) * P1;
         }
