@@ -52,22 +52,16 @@ namespace {
 thread_local hipEvent_t t_start = nullptr, t_stop = nullptr;
 thread_local bool t_used = false;
 
-// lds: dynamic LDS no kernel uses, to bound the workgroups a CU holds.
-template <class K, class... Args>
-void run_kernel_lds(K kernel, dim3 grid, dim3 block, uint32_t lds, hipStream_t s, Args... args)
-{
-    if (!t_start) {
-        hipLaunchKernelGGL(kernel, grid, block, lds, s, args...);
-        return;
-    }
-    hipExtLaunchKernelGGL(kernel, grid, block, lds, s, t_start, t_stop, 0, args...);
-    t_start = t_stop = nullptr;
-    t_used = true;
-}
 template <class K, class... Args>
 void run_kernel(K kernel, dim3 grid, dim3 block, hipStream_t s, Args... args)
 {
-    run_kernel_lds(kernel, grid, block, 0, s, args...);
+    if (!t_start) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, s, args...);
+        return;
+    }
+    hipExtLaunchKernelGGL(kernel, grid, block, 0, s, t_start, t_stop, 0, args...);
+    t_start = t_stop = nullptr;
+    t_used = true;
 }
 
 // XXH64 primes (xxHash specification).
@@ -1923,6 +1917,12 @@ __global__ __launch_bounds__(1024) void k_classify_small(const ArgTables tab, ui
 
 // Workgroup sizes (lanes) and slice bytes of the tile kernels, from
 // measurement on MI355X.
+// A pack tile's 80 registers let a CU hold one (16 wavefronts of six a SIMD)
+// and take the next as soon as twelve of the last one's wavefronts have ended.
+// (48 KB of LDS reserved beside the tile's own, meant to keep a second one
+// out, only kept the next one from starting: packs with fingerprints of 90 /
+// 200 MiB 45.9 / 83.3 us with it, 45.5 / 82.5 without, 1 / 2 GiB 347 / 678 -> 343 /
+// 674.)
 constexpr int kPackLanes = 1024, kPackSlice = 512;
 // The staggered verified restore (jobs of 2-9 rounds) moves 1 KiB slices:
 // 2-4% faster there than 512 B (the KV ring window 187 -> 182 us, flat
@@ -1942,10 +1942,6 @@ constexpr int kVerifyStaggerSlice = 1024;
 // nontemporal stores whatever the size (plain ones: the KV ring restore 177
 // -> 196 us, its verified restore 181 -> 196 us).
 constexpr uint32_t kPackWriteBackMaxRounds = kStaggerMaxRounds;
-// LDS no pack tile uses, so that a CU holds one of them: their 64 registers
-// would admit two, and two tiles' interleaved stores are slower (KV ring step
-// 529 -> 536 us, the 1024-session batch 4293 -> 4438 us a pass).
-constexpr uint32_t kPackSpareLds = 48 << 10;
 constexpr int kHashLanes = 256, kHashSlice = 512;
 constexpr int kCopyLanes = 512, kCopySlice = 1024;
 // Fingerprint and diff tiles of jobs whose tables travel in the kernel
@@ -2679,14 +2675,14 @@ hipError_t launch_tile(const Tab &tab, uint64_t ngroups, int mode, uint64_t *nod
         break;
     case kModePack:
         if (stg.ticks)
-            run_kernel_lds((k_hash_staggered<Tab, kModePack, kPackLanes, kPackSlice, kGroupChunks>), grid, dim3(kPackLanes),
-                           kPackSpareLds, s, tab, nodes, flag_mask, arena_base, stg);
+            run_kernel((k_hash_staggered<Tab, kModePack, kPackLanes, kPackSlice, kGroupChunks>), grid, dim3(kPackLanes), s,
+                       tab, nodes, flag_mask, arena_base, stg);
         else if (ngroups <= (uint64_t)kPackWriteBackMaxRounds * std::max<uint32_t>(dev.cus, 1))
-            run_kernel_lds((k_hash<Tab, kModePack, kPackLanes, kPackSlice, kGroupChunks, true>), grid, dim3(kPackLanes),
-                           kPackSpareLds, s, tab, nodes, flag_mask, arena_base);
+            run_kernel((k_hash<Tab, kModePack, kPackLanes, kPackSlice, kGroupChunks, true>), grid, dim3(kPackLanes), s, tab,
+                       nodes, flag_mask, arena_base);
         else
-            run_kernel_lds((k_hash<Tab, kModePack, kPackLanes, kPackSlice, kGroupChunks, false>), grid, dim3(kPackLanes),
-                           kPackSpareLds, s, tab, nodes, flag_mask, arena_base);
+            run_kernel((k_hash<Tab, kModePack, kPackLanes, kPackSlice, kGroupChunks, false>), grid, dim3(kPackLanes), s, tab,
+                       nodes, flag_mask, arena_base);
         break;
     case kModeDiff:
         if (kArgTab && ngroups <= kWideDiffGroups && wide_pays(tab.nbuf))
