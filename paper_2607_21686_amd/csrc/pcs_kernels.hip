@@ -398,8 +398,9 @@ struct TileBuf {
     uint32_t index;
 };
 
-// Group G's buffer, read by a whole wavefront.
-template <int MODE>
+// Group G's buffer, read by a whole wavefront (CPW: the chunks of the
+// kernel's tiles).
+template <int MODE, int CPW>
 __device__ __forceinline__ TileBuf tile_buf(const DevTables &tab, uint64_t G)
 {
     TileBuf b;
@@ -484,15 +485,29 @@ struct ArgLanes {
         return g;
     }
 };
-template <int MODE>
+// A job of one buffer in whole-group tiles reads that entry alone, by scalar
+// loads: a launch of few rounds shows the difference (fingerprints of 128 / 200
+// MiB 31.2 / 48.4 -> 30.4 / 47.1 us, packs of 200 MiB 82.0 -> 81.0).  8-chunk tiles
+// gain nothing from it, and with several buffers the question costs 0.2 us or so.
+template <int MODE, int CPW>
 __device__ __forceinline__ TileBuf tile_buf(const ArgTables &tab, uint64_t G)
 {
-    const ArgLanes lanes(tab);
-    const uint32_t i = lanes.find(G);
-    const ArgBuf a = lanes.buf(i);
     TileBuf b;
-    b.index = i;
-    b.g = lanes.geom(i, a);
+    ArgBuf a;
+    if (CPW == kGroupChunks && tab.nbuf == 1) {
+        a = tab.bufs[0];
+        b.index = 0;
+        b.g = Geom{a.addr, a.nbytes, 0, 0, 0, 0, 0};
+        if (tab.nring) {
+            const ArgRing &r = tab.rings[0];
+            b.g = Geom{a.addr, a.nbytes, r.win, r.first, r.head, r.stride, r.inv_win};
+        }
+    } else {
+        const ArgLanes lanes(tab);
+        b.index = lanes.find(G);
+        a = lanes.buf(b.index);
+        b.g = lanes.geom(b.index, a);
+    }
     b.nchunks = chunks_of(a.nbytes);
     b.chunk_begin = a.chunk_begin;
     b.group_begin = a.group_begin;
@@ -532,7 +547,7 @@ __device__ __forceinline__ void tile_setup(const Tab &tab, uint64_t G, uint32_t 
 {
     const uint32_t t = threadIdx.x;
     if (t < 64) {
-        const TileBuf b = tile_buf<MODE>(tab, G);
+        const TileBuf b = tile_buf<MODE, CPW>(tab, G);
         const uint64_t c0 = (G - b.group_begin) * kGroupChunks + part * CPW;
         const uint32_t nv = c0 < b.nchunks ? (uint32_t)umin(CPW, b.nchunks - c0) : 0;
         bool pieces = false;
@@ -1762,7 +1777,7 @@ __global__ __launch_bounds__(256) void k_place_dirty(const Tab tab, uint32_t ngr
         uint32_t s = (uint32_t)first, G = group_of_slot(offsets, ngroups, s);
         uint64_t mask = dirty_mask[G];
         for (uint32_t below = s - (uint32_t)offsets[G]; below; --below) mask &= mask - 1;
-        TileBuf b = tile_buf<kModeDiff>(tab, G);
+        TileBuf b = tile_buf<kModeDiff, kGroupChunks>(tab, G);
         for (; s < end; ++s) {
             if (!mask) {
                 mask = dirty_mask[++G];  // (slot s lies in a later group)
@@ -1770,7 +1785,7 @@ __global__ __launch_bounds__(256) void k_place_dirty(const Tab tab, uint32_t ngr
                     G = group_of_slot(offsets, ngroups, s);
                     mask = dirty_mask[G];
                 }
-                b = tile_buf<kModeDiff>(tab, G);
+                b = tile_buf<kModeDiff, kGroupChunks>(tab, G);
             }
             const uint64_t i = (G - b.group_begin) * kGroupChunks + (uint64_t)__builtin_ctzll(mask);
             mask &= mask - 1;
@@ -1807,13 +1822,27 @@ struct DevRanges {
     __device__ __forceinline__ explicit DevRanges(const DevTables &tab) : t(tab) {}
     __device__ __forceinline__ ChunkRange group(uint64_t G) const { return range_of(t.bufs[t.map[G]]); }
 };
+// (One buffer: its entry alone.  A wavefront classifies one word, so reading
+// the whole table, 3 KB, is most of what it does: 8192 groups of one buffer
+// 38.5 us with the table read, 37.0 without.)
+struct ArgRange {
+    const ArgTables &t;
+    __device__ __forceinline__ explicit ArgRange(const ArgTables &tab) : t(tab) {}
+    __device__ __forceinline__ ChunkRange group(uint64_t G) const
+    {
+        if (t.nbuf == 1) return range_of(t.bufs[0]);
+        const ArgLanes lanes(t);
+        return range_of(lanes.buf(lanes.find(G)));
+    }
+};
+// The same for several words of a wavefront: the table is read once.
 struct ArgRanges {
     ArgLanes lanes;
     __device__ __forceinline__ explicit ArgRanges(const ArgTables &tab) : lanes(tab) {}
     __device__ __forceinline__ ChunkRange group(uint64_t G) const { return range_of(lanes.buf(lanes.find(G))); }
 };
 __device__ __forceinline__ DevRanges ranges_of(const DevTables &t) { return DevRanges(t); }
-__device__ __forceinline__ ArgRanges ranges_of(const ArgTables &t) { return ArgRanges(t); }
+__device__ __forceinline__ ArgRange ranges_of(const ArgTables &t) { return ArgRange(t); }
 
 // Bitmap words g[0..U) (each one 64-chunk group of one buffer; g >= ngroups:
 // none), computed by one wavefront: chunk i differs iff its K replay
