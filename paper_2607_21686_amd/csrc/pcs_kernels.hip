@@ -423,10 +423,8 @@ __device__ __forceinline__ TileBuf tile_buf(const DevTables &tab, uint64_t G)
 }
 
 // The argument tables in a wavefront's registers: lane l holds buffers l and
-// 64 + l % 32 and ring l % 16.  Every load is issued before any is used, so a
-// workgroup learns its buffer in one round trip to memory; a search, one
-// dependent load a step and several more for the chosen entry, took
-// 5,700 cycles of an 8-chunk tile's 20,000.
+// 64 + l % 32 and ring l % 16.  A search, one dependent load a step and several
+// more for the chosen entry, took 5,700 cycles of an 8-chunk tile's 20,000.
 static_assert(kArgBufs == 96 && kArgRings == 16, "lanes of ArgLanes");
 struct ArgLanes {
     ArgBuf lo, hi;
@@ -443,6 +441,19 @@ struct ArgLanes {
         valid_lo = __ballot(lane < t.nbuf);
         valid_hi = __ballot(lane < 32 && 64 + lane < t.nbuf);
         rings = __ballot(lane < t.nring);
+    }
+    // Asks for every field to be in its register here, so that all loads are in
+    // flight together and a workgroup learns its buffer in one round trip to
+    // memory.  The compiler on its own moves the loads of a chosen entry's fields
+    // behind the choice, a second round trip: 32 MiB ring windows restored in
+    // 12.4 us and fingerprinted in 16.0, with this 12.1 and 15.7.  (Not for
+    // classification, which needs few fields: 6.6 against 7.5 us there.)
+    __device__ __forceinline__ void hold()
+    {
+        asm volatile("" : "+v"(lo.addr), "+v"(lo.nbytes), "+v"(lo.chunk_begin), "+v"(lo.group_begin), "+v"(lo.aux),
+                          "+v"(hi.addr), "+v"(hi.nbytes), "+v"(hi.chunk_begin), "+v"(hi.group_begin), "+v"(hi.aux));
+        asm volatile("" : "+v"(ring.win), "+v"(ring.first), "+v"(ring.head), "+v"(ring.stride), "+v"(ring.inv_win),
+                          "+v"(ring_buf));
     }
     // The buffer of group G: the last one that begins at or before it (an
     // empty buffer begins where the next one does and loses).
@@ -503,7 +514,8 @@ __device__ __forceinline__ TileBuf tile_buf(const ArgTables &tab, uint64_t G)
             b.g = Geom{a.addr, a.nbytes, r.win, r.first, r.head, r.stride, r.inv_win};
         }
     } else {
-        const ArgLanes lanes(tab);
+        ArgLanes lanes(tab);
+        lanes.hold();
         b.index = lanes.find(G);
         a = lanes.buf(b.index);
         b.g = lanes.geom(b.index, a);
