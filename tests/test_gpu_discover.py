@@ -195,18 +195,18 @@ def _distance_abi(pcs, ctx, ref, bufs):
     return int(cnt.value), float(d.value)
 
 
-@pytest.mark.parametrize("case", ["small", "large"])
+@pytest.mark.parametrize("case", ["small", "large", "many"])
 def test_distance_counts_differing_chunks(pcs, case):
     """D = differing chunks / chunks, against the oracle's fingerprints of the
     same bytes and of a reference copy with chosen chunks changed (Sec. 4's
     metric, taken bit-exactly).  'small' carries its tables in the kernel
-    arguments and runs as sub-tiles; 'large' (more than 16 buffers, more than
-    128 groups) uploads them and runs whole-group tiles."""
-    rng = np.random.default_rng(91 if case == "small" else 92)
+    arguments and runs as sub-tiles, 'large' (more than 128 groups) as
+    whole-group tiles; 'many' (more than 96 buffers) stages its tables."""
+    rng = np.random.default_rng({"small": 91, "large": 92, "many": 93}[case])
     if case == "small":
         sizes = [5000, 1, 3 * 4096 + 17, 64 * 4096 + 8, 0]
     else:
-        sizes = [40 << 20] + [int(rng.integers(1, 3 * 4096)) for _ in range(20)]
+        sizes = [40 << 20] + [int(rng.integers(1, 3 * 4096)) for _ in range(20 if case == "large" else 100)]
     log("distance:", case, "sizes", sizes[:4], "...")
     bufs = [rng.integers(0, 256, size=n, dtype=np.uint8) for n in sizes]
     total = sum(oracle.chunk_count(n) for n in sizes)

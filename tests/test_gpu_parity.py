@@ -86,10 +86,10 @@ def test_small_job_boundary(ctx, pcs, groups):
     ctx.delete(plain)
 
 
-@pytest.mark.parametrize("nbuf", [8, 9, 16, 17])
+@pytest.mark.parametrize("nbuf", [8, 9, 16, 17, 95, 96, 97])
 def test_argument_table_boundary(ctx, pcs, nbuf):
-    """Jobs of at most 16 buffers and 64 runs carry their tables in the kernel
-    arguments, larger ones upload them: both sides of the buffer limit, with
+    """Jobs of at most 96 buffers, 16 of them wrapped rings, carry their tables in
+    the kernel arguments, larger ones stage them: both sides of the buffer limit, with
     empty and ragged buffers and a wrapped ring: fingerprints, roots, the
     fused checkpoint, restore, and an incremental checkpoint with changes."""
     rng = np.random.default_rng(700 + nbuf)

@@ -2,9 +2,8 @@
 tiles of argument-table jobs widen from 256 to 1024 lanes (fingerprints up
 to 1024 groups, incremental checkpoints up to 2048 groups): chunk
 fingerprints, buffer and session roots, the stored bytes of incremental
-checkpoints and their restores, against the oracle; and on both sides of
-the node count up to which a small job's Merkle lists load into LDS in one
-pass.  Three ragged buffers, so the tables travel in the kernel arguments."""
+checkpoints and their restores, against the oracle; and long Merkle lists, in
+argument tables (up to 96 buffers) and device tables (more)."""
 import numpy as np
 import pytest
 import torch
@@ -97,10 +96,9 @@ def test_incremental_width_boundary(pcs, groups):
 
 @pytest.mark.parametrize("groups", [4096, 4100])
 def test_merkle_lists_past_one_lds_pass(pcs, groups):
-    """Argument-table jobs whose buffer lists hold more than 4096 Merkle
-    nodes together reduce them list by list through memory instead of in
-    one LDS pass: both sides of that bound, fingerprints and the fused
-    checkpoint's roots against the oracle."""
+    """Argument-table jobs of about 4096 Merkle nodes, whose lists' first
+    level every CU reduces: fingerprints and the fused checkpoint's roots
+    against the oracle."""
     rng = np.random.default_rng([47, groups])
     sizes = sizes_for(groups)
     bufs = [rng.integers(0, 256, size=n, dtype=np.uint8) for n in sizes]
@@ -121,21 +119,18 @@ def test_merkle_lists_past_one_lds_pass(pcs, groups):
         ctx.close()
 
 
-@pytest.mark.parametrize("case", ["2 long, argument tables", "1 long + 16 short, device tables",
-                                  "5 long, in-workgroup passes"])
-def test_merkle_long_lists(pcs, case):
-    """Buffers of more than 4096 groups: up to four such lists first have their
-    64-value blocks reduced by a grid-wide launch (argument and device
-    tables); with more, each list's workgroup does it.  Fingerprints, buffer
-    and session roots, and the fused checkpoint's roots against the oracle."""
-    rng = np.random.default_rng([53, len(case)])
-    if case.startswith("2 long"):
-        sizes = [4100 * GROUP - 3, 4097 * GROUP + 11, 5]
-    elif case.startswith("1 long"):
-        sizes = [4099 * GROUP + 7] + [int(rng.integers(1, 3 * 4096)) for _ in range(16)]
-    else:
-        sizes = [4097 * GROUP + k for k in range(5)]
-    log("merkle long lists:", case)
+@pytest.mark.parametrize("nlong,nshort", [(2, 1), (1, 16), (5, 0), (1, 96), (5, 92)])
+def test_merkle_long_lists(pcs, nlong, nshort):
+    """Buffers of more than 4096 groups.  In argument tables (up to 96 buffers)
+    every list's first level is a grid-wide launch; in device tables up to
+    four long lists have their 64-value blocks reduced by a grid-wide launch
+    first, and with more, each list's workgroup passes through memory.
+    Fingerprints, buffer and session roots, and the fused checkpoint's roots
+    against the oracle."""
+    rng = np.random.default_rng([53, nlong, nshort])
+    sizes = [(4097 + i % 3) * GROUP + (11 * i - 3 if i else 7) for i in range(nlong)]
+    sizes += [int(rng.integers(1, 3 * 4096)) for _ in range(nshort)]
+    log("merkle long lists:", nlong, "long", nshort, "short")
     bufs = [rng.integers(0, 256, size=n, dtype=np.uint8) for n in sizes]
     h, r, s = oracle.fingerprint(bufs)
     d = [dev(b) for b in bufs]

@@ -77,16 +77,19 @@ def test_noalloc_matches_fingerprint_on_shrinking_calls(pcs):
     rng = np.random.default_rng(701)
     ctx = pcs.Context(arena(64 << 20))
     before = ctx.arena_stats()
-    # 1: device tables (21 buffers), whole-group tiles (> 128 groups), a wrapping ring.
+    # 1: device tables (101 buffers), whole-group tiles (> 128 groups), a wrapping ring.
     ring = W.Ring(6, 40, 2048, 33, 24, 40 * 2048 + 4096)
-    sizes = [24 << 20, 8 << 20] + [int(rng.integers(0, 5 * 4096)) for _ in range(18)]
+    sizes = [24 << 20, 8 << 20] + [int(rng.integers(0, 5 * 4096)) for _ in range(98)]
     descs, logical, keep1 = _job(pcs, rng, sizes, ring)
     _check(pcs, ctx, descs, logical, "large, device tables")
-    # 2: smaller, still device tables (17 buffers), sub-tiles (<= 128 groups).
-    sizes = [3 << 20] + [int(rng.integers(1, 3 * 4096)) for _ in range(16)]
+    # 2: smaller, still device tables (97 buffers), sub-tiles (<= 128 groups).
+    sizes = [3 << 20] + [int(rng.integers(1, 3 * 4096)) for _ in range(96)]
     descs, logical, keep2 = _job(pcs, rng, sizes)
     _check(pcs, ctx, descs, logical, "smaller, device tables")
-    # 3: smaller again, tables in the kernel arguments (3 buffers).
+    # 3: smaller again, tables in the kernel arguments (21 buffers, then 3).
+    sizes = [24 << 20, 8 << 20] + [int(rng.integers(0, 5 * 4096)) for _ in range(18)]
+    descs, logical, keep3 = _job(pcs, rng, sizes, ring)
+    _check(pcs, ctx, descs, logical, "large, argument tables")
     descs, logical, keep3 = _job(pcs, rng, [5000, 1, 64 * 4096 + 8])
     _check(pcs, ctx, descs, logical, "small, argument tables")
     # 4: empty buffers only (no chunks; roots of the empty input).
@@ -99,7 +102,7 @@ def test_noalloc_matches_fingerprint_on_shrinking_calls(pcs):
 def test_noalloc_outputs_optional_and_no_timing_events(pcs):
     rng = np.random.default_rng(702)
     ctx = pcs.Context(arena(16 << 20))
-    sizes = [int(rng.integers(1, 9 * 4096)) for _ in range(20)]
+    sizes = [int(rng.integers(1, 9 * 4096)) for _ in range(100)]  # staged tables: a "map" launch
     descs, logical, keep = _job(pcs, rng, sizes)
     T = sum(oracle.chunk_count(n) for n in sizes)
     h = zeros_u64(T)
