@@ -87,3 +87,46 @@ def test_tail(pcs, name):
             assert int(olab.sum()) == (0 if not flips else len({0, max(i for i, k in enumerate(sizes) if k)}))
         ctx.delete(snap)
     ctx.close()
+
+
+@pytest.mark.parametrize("name", ["96 ragged", "2 x 64 groups", "mixed"])
+def test_tail_beside_a_busy_stream(pcs, name):
+    """The same hand-over between workgroups while another stream keeps the CUs,
+    caches and memory busy: every root, count and label of forty turns."""
+    sizes = JOBS[name]
+    rng = np.random.default_rng(len(name))
+    bufs = [rng.integers(0, 256, size=k, dtype=np.uint8) for k in sizes]
+    log("tail beside a busy stream", name)
+    h, r, s = oracle.fingerprint(bufs)
+    n, T, cpb = len(bufs), h.size, [oracle.chunk_count(k) for k in sizes]
+    words = oracle.bitmap_words(cpb)
+    turns = 40
+    side, load = torch.cuda.Stream(), torch.cuda.Stream()
+    d = [dev(b) for b in bufs]
+    back = [torch.zeros_like(t) for t in d]
+    ref = torch.from_numpy(h.view(np.int64).copy()).cuda()
+    ref[T // 2] += 1
+    big = torch.zeros(1 << 30, dtype=torch.uint8, device="cuda")
+    ar, ar2 = arena(256 << 20), arena((1 << 30) + (64 << 20))
+    R = torch.zeros((2 * turns, n), dtype=torch.int64, device="cuda")
+    S = torch.zeros((2 * turns, 1), dtype=torch.int64, device="cuda")
+    bad = torch.full((turns, words), -1, dtype=torch.int64, device="cuda")
+    lab = torch.full((turns, n), 9, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    ctx, other = pcs.Context(ar, stream=side), pcs.Context(ar2, stream=load)
+    plan = pcs.BufArray([pcs.flat(t, k) for t, k in zip(d, sizes)])
+    dst = pcs.BufArray([pcs.flat(t, k) for t, k in zip(back, sizes)])
+    for i in range(turns):
+        other.delete(other.checkpoint([pcs.flat(big)], hash=True))
+        ctx.fingerprint(plan, None, R[2 * i], S[2 * i])
+        snap = ctx.checkpoint(plan, hash=True, roots=R[2 * i + 1], session_root=S[2 * i + 1])
+        ctx.restore_verify(snap, dst, bad[i], lab[i])
+        ctx.delete(snap)
+        if i % 8 == 0:
+            assert ctx.distance(ref, plan) == 1 / T
+    torch.cuda.synchronize()
+    assert (R.cpu().numpy().view(np.uint64) == r).all() and (S.cpu().numpy().view(np.uint64) == s).all()
+    assert not bad.any() and not lab.any()
+    assert all(np.array_equal(host(t)[:k], b) for t, k, b in zip(back, sizes, bufs))
+    ctx.close()
+    other.close()
