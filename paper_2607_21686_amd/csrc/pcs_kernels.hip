@@ -1273,7 +1273,7 @@ struct ArgItems {
     uint32_t total;
     __device__ __forceinline__ ArgItems(const ArgTables &t, uint32_t tiles, bool pre)
     {
-        const uint32_t lane = threadIdx.x & 63, per = kGroupChunks / tiles;
+        const uint32_t lane = threadIdx.x & 63;
         uint32_t base = 0;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -1281,9 +1281,8 @@ struct ArgItems {
             const ArgBuf &b = t.bufs[j < kArgBufs ? j : 0];
             const uint64_t n = j < t.nbuf ? chunks_of(b.nbytes) : 0;
             begin[h] = (uint64_t)b.group_begin * tiles;
-            count[h] = (n + per - 1) / per;
-            if (pre) count[h] = (count[h] + 63) / 64;
-            items[h] = (uint32_t)((count[h] + 63) / 64);
+            count[h] = merkle_values(n, tiles, pre);
+            items[h] = merkle_items(count[h]);
             incl[h] = base + wave_incl_scan(items[h]);
             base = lane_word(incl[h], 63);
         }
@@ -1298,12 +1297,14 @@ struct ArgItems {
         list = a ? lane_word(begin[0], l) : lane_word(begin[1], l);
         const uint64_t cnt = a ? lane_word(count[0], l) : lane_word(count[1], l);
         const uint32_t first = a ? lane_word(incl[0] - items[0], l) : lane_word(incl[1] - items[1], l);
-        const uint64_t off = 64ull * (i - first);
-        at = list + off;
-        n = (uint32_t)umin(64, cnt - off);
+        at = list + 64ull * (i - first);
+        n = merkle_item_values(cnt, i - first);
     }
 };
 
+// Room for the items of any job: the most groups a job may have, their first
+// level done, in lists that each end in a partial item.
+constexpr int kMerkleItems = 4352;
 // Every root of a job in the argument tables, by one workgroup of NT lanes:
 // its wavefronts share the items of all lists (four in flight each), then the
 // lists themselves, then wavefront 0 takes the session's.  Lists one after
@@ -1340,12 +1341,12 @@ __device__ void merkle_args(const ArgTables &tab, uint32_t tiles, const uint64_t
         uint32_t n = b < 64 ? lane_word(it.items[0], l) : lane_word(it.items[1], l);
         const uint64_t *p = part + (b < 64 ? lane_word(it.incl[0], l) : lane_word(it.incl[1], l)) - n;
         uint64_t v = empty_hash();
-        if (n <= 64) {
+        if (ITEMS < kMerkleItems || n <= 64) {  // (the callers with less room have lists of at most 64 items)
             if (lane < n) v = p[lane];
-        } else {
-            const uint32_t nb = (n + 63) / 64;
+        } else {  // a buffer of more than 64 GiB
+            const uint32_t nb = merkle_items(n);
             for (uint32_t k = 0; k < nb; ++k) {
-                const uint32_t c = min(64u, n - 64 * k);
+                const uint32_t c = merkle_item_values(n, k);
                 const uint64_t r = lane_word(wave_merkle<1, 6>(lane < c ? p[64 * k + lane] : 0, c), 0);
                 if (lane == k) v = r;
             }
@@ -1371,9 +1372,6 @@ __device__ void merkle_args(const ArgTables &tab, uint32_t tiles, const uint64_t
     __syncthreads();
 }
 
-// Room for the items of any job: the most groups a job may have, their first
-// level done, in lists that each end in a partial item.
-constexpr int kMerkleItems = 4352;
 __global__ __launch_bounds__(1024) void k_merkle_args(const ArgTables tab, uint32_t tiles,
                                                       const uint64_t *__restrict__ in, bool pre)
 {

@@ -251,6 +251,22 @@ struct ArgTables {
 static_assert(kArgBufs <= 256, "a buffer number fits in ring_buf");
 static_assert(sizeof(ArgTables) + 224 <= 4096, "argument tables must fit in the kernel arguments");
 
+// The Merkle list of a buffer of a job in the argument tables: one value per
+// tile (`tiles` of them to a group), or, once its aligned blocks of 64 are
+// reduced (pre), one per block; and its items, the blocks of 64 a wavefront
+// reduces at once.
+constexpr uint64_t merkle_values(uint64_t nchunks, uint32_t tiles, bool pre)
+{
+    const uint64_t per = kGroupChunks / tiles, n = nchunks / per + (nchunks % per != 0);
+    return pre ? n / 64 + (n % 64 != 0) : n;
+}
+constexpr uint32_t merkle_items(uint64_t values) { return (uint32_t)(values / 64 + (values % 64 != 0)); }
+constexpr uint32_t merkle_item_values(uint64_t values, uint32_t item)
+{
+    const uint64_t left = values - 64ull * item;
+    return left < 64 ? (uint32_t)left : 64;
+}
+
 // Buffer lists of a Merkle launch that hold more than kMerkleLdsValues
 // values (a buffer of more than 1 GiB): when at most kLongLists of them, a
 // grid-wide pass reduces their aligned 64-value blocks first,

@@ -1,6 +1,6 @@
 // Host-only test of the address arithmetic the kernels use (pcs_layout.h:
 // locate, chunk_loc) against the piece list of the same descriptor
-// (pcs_host.h: describe), and of the argument-table and move-item rules.
+// (pcs_host.h: describe), and of the Merkle-item and move-item rules.
 #include <cinttypes>
 #include <cstdio>
 #include <cstdlib>
@@ -126,11 +126,61 @@ static void test_move_items()
         }
 }
 
+// A promote-odd tree over v, level by level.
+static uint64_t node(uint64_t l, uint64_t r) { return (l ^ 0x9E3779B97F4A7C15ull) * 3 + (r + 1) * 0xC2B2AE3D27D4EB4Full; }
+static uint64_t tree(std::vector<uint64_t> v)
+{
+    while (v.size() > 1) {
+        for (size_t i = 0; 2 * i < v.size(); ++i) v[i] = 2 * i + 1 < v.size() ? node(v[2 * i], v[2 * i + 1]) : v[2 * i];
+        v.resize((v.size() + 1) / 2);
+    }
+    return v[0];
+}
+
+// A list reduced item by item, as the argument-table kernels do it (the first
+// level of long lists apart, more than 64 items in blocks of their own), has
+// the root of the whole tree.
+static std::vector<uint64_t> by_items(const std::vector<uint64_t> &v)
+{
+    std::vector<uint64_t> part;
+    for (uint32_t k = 0; k < merkle_items(v.size()); ++k) {
+        const auto at = v.begin() + 64ull * k;
+        part.push_back(tree(std::vector<uint64_t>(at, at + merkle_item_values(v.size(), k))));
+    }
+    return part;
+}
+static void test_merkle_items()
+{
+    for (uint64_t blocks : {1ull, 2ull, 63ull, 64ull, 65ull, 4095ull, 4096ull, 4097ull, 262144ull})
+        for (int64_t d : {-65, -63, -1, 0, 1, 62})
+            for (uint32_t tiles : {1u, kSmallTiles}) {
+                const uint64_t values = 64 * blocks + (uint64_t)d;
+                if (values == 0 || values >> 40 || values > 1ull << 24) continue;
+                const uint64_t per = kGroupChunks / tiles;
+                CHECK(merkle_values(values * per, tiles, false) == values);
+                CHECK(merkle_values(values * per - per + 1, tiles, false) == values);
+                std::vector<uint64_t> v(values);
+                for (uint64_t i = 0; i < values; ++i) v[i] = i * 0xD1B54A32D192ED03ull + blocks;
+                const uint64_t want = tree(v);
+                for (bool pre : {false, true}) {
+                    std::vector<uint64_t> list = v;
+                    if (pre) list = by_items(v);
+                    CHECK(list.size() == merkle_values(values * per, tiles, pre));
+                    std::vector<uint64_t> part = by_items(list);
+                    if (part.size() > 4096) continue;  // beyond one workgroup: such a list has its first level done
+                    if (part.size() > 64) part = by_items(part);
+                    CHECK(part.size() <= 64);
+                    CHECK(tree(part) == want);
+                }
+            }
+}
+
 int main()
 {
     test_rings(1);
     test_large(2);
     test_move_items();
+    test_merkle_items();
     printf("ok\n");
     return 0;
 }

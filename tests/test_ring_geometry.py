@@ -1,8 +1,8 @@
 """The kernels' address arithmetic on the CPU: where a logical byte of a flat
 buffer or ring window lies (locate) and how a chunk's bytes are described
 (chunk_loc), against the piece list of the same descriptor and, for rings too
-many to list, against exact integer arithmetic; and the work items of a bank
-shrink's moves.  The checks live in tests/host/test_geometry.cpp, compiled
+many to list, against exact integer arithmetic; the work items of a bank
+shrink's moves; and the items of Merkle lists, to the most a buffer can have.  The checks live in tests/host/test_geometry.cpp, compiled
 with g++ under UndefinedBehaviorSanitizer."""
 import os
 import shutil
