@@ -1987,25 +1987,27 @@ constexpr uint32_t kPackWriteBackMaxRounds = kStaggerMaxRounds;
 constexpr int kHashLanes = 256, kHashSlice = 512;
 constexpr int kCopyLanes = 512, kCopySlice = 1024;
 // Fingerprint and diff tiles of jobs whose tables travel in the kernel
-// arguments take 1024 lanes up to a few rounds of groups: one workgroup per
-// CU then keeps the whole CU's loads in flight, where 256-lane tiles leave
-// part of a round's CUs with one tile and others with two (measured:
-// incremental checkpoints of flat 64-512 MiB 4-9% faster, the growing bank's
-// late steps 8%; fingerprints of flat 64-256 MiB 8-15%).  With device tables
-// a tile's first access is a dependent load of its group-map entry, which
-// four 256-lane tiles per CU hide and one 1024-lane tile does not (a wrapping
-// KV ring window: diff 115 -> 131 us, fingerprint 89 -> 106 us), so those
-// keep 256 lanes.  Above the bounds the wide tiles stop paying: a diff of
-// 4096 groups is even and one of 8192 groups 19% slower; a fingerprint of
-// 2048 groups is 5% faster on a flat buffer and 1.5% slower on a 64-run KV
-// ring window.
-// A job of many buffers has many partial groups, and a 1024-lane tile of a few
-// chunks holds its CU as long as a full one, so wide tiles are for at most 16
-// buffers (fingerprints of 53 buffers of 66 B to 57 MB, 12 groups a buffer: 38
-// us with wide tiles, 33 with 256 lanes; a diff of 64 buffers of 32
-// groups each: 98 us with wide tiles, 93.5 with 256 lanes).
-constexpr uint64_t kWideDiffGroups = 2048, kWideHashGroups = 1024;
-inline bool wide_pays(uint32_t nbuf) { return nbuf <= 16; }
+// arguments take 1024 lanes where that saves a round of tiles.  A CU holds two
+// 1024-lane tiles (64 registers) or three 256-lane ones, whose round takes half
+// as long again (26 us for 512 groups, 39 for 760, without the roots).  So wide tiles
+// pay up to two tiles per CU (one round either way) and from three to four (two
+// rounds either way); between, and from four on, they need a round more or
+// gain nothing.  Fingerprint / incremental checkpoint, us, 1024 against 256
+// lanes, one flat buffer, groups (256 CUs): 256 19.8 / 26.2 against 20.9 / 26.9; 512
+// 30.9 / 37.8, 31.6 / 38.4; 513 38.0 / 45.8, 35.4 / 42.0; 760 45.3 / 52.4, 44.1 / 50.8;
+// 840 49.2 / 56.5, 53.6 / 60.3; 1024 55.4 / 62.7, 57.7 / 63.8; 1100 64.3 / 73.2, 58.4 /
+// 65.4; 1536 76.3 / 84.3, 75.2 / 81.7; 2048 96.3 / 105.7, 95.4 / 102.4.  20 buffers and
+// ring windows draw the line at the same places, and so do 2 to 96 buffers of
+// equal or mixed sizes: what a job of many buffers was thought to lose to its
+// partial groups is the round begun at 513 groups.
+// With device tables a tile's first access is a dependent load of its group-map
+// entry, which three 256-lane tiles per CU hide and two 1024-lane tiles do not
+// (a wrapping KV ring window: diff 115 -> 131 us, fingerprint 89 -> 106 us), so
+// those keep 256 lanes.
+inline bool wide_pays(uint64_t ngroups, uint32_t cus)
+{
+    return ngroups <= 2ull * cus || (ngroups > 3ull * cus && ngroups <= 4ull * cus);
+}
 constexpr int kSmallLanes = 256;  // sub-tiles of small jobs: 8 chunks per workgroup
 // A sub-tile moves whole chunks in one step (8 granules per lane): a small
 // job's time is a tile's latency, one load round trip per step.
@@ -2708,7 +2710,7 @@ hipError_t launch_tile(const Tab &tab, uint64_t ngroups, int mode, uint64_t *nod
     constexpr bool kArgTab = std::is_same<Tab, ArgTables>::value;
     switch (mode) {
     case kModeHash:
-        if (kArgTab && ngroups <= kWideHashGroups && wide_pays(tab.nbuf))
+        if (kArgTab && wide_pays(ngroups, dev.cus))
             run_kernel((k_hash<Tab, kModeHash, kPackLanes, kHashSlice, kGroupChunks, false>), grid, dim3(kPackLanes), s,
                        tab, nodes, flag_mask, arena_base);
         else
@@ -2727,7 +2729,7 @@ hipError_t launch_tile(const Tab &tab, uint64_t ngroups, int mode, uint64_t *nod
                        nodes, flag_mask, arena_base);
         break;
     case kModeDiff:
-        if (kArgTab && ngroups <= kWideDiffGroups && wide_pays(tab.nbuf))
+        if (kArgTab && wide_pays(ngroups, dev.cus))
             run_kernel((k_hash<Tab, kModeDiff, kPackLanes, kHashSlice, kGroupChunks, false>), grid, dim3(kPackLanes), s,
                        tab, nodes, flag_mask, arena_base);
         else

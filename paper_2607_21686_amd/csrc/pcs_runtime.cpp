@@ -1169,7 +1169,8 @@ int pcs_fingerprint_noalloc(pcs_ctx *c, const pcs_buf *bufs, uint32_t n, uint64_
     }
     int st = with_tables(sg, [&](const auto &tab) {
         return launch(c, "hash", [&] {
-            return launch_tile(tab, G, kModeHash, want_roots ? d_nodes : nullptr, nullptr, 0, s, tiles);
+            return launch_tile(tab, G, kModeHash, want_roots ? d_nodes : nullptr, nullptr, 0, s, tiles,
+                               c->dev);
         });
     });
     if (st || !want_roots) return st;
@@ -1280,7 +1281,7 @@ int pcs_distance(pcs_ctx *c, const pcs_buf *bufs, uint32_t n, const uint64_t *d_
         uint64_t *d_total = (uint64_t *)(scr + o_total);
         hipStream_t s = c->stream;
         int st = with_tables(sg, [&](const auto &tab) {
-            return launch(c, "hash", [&] { return launch_tile(tab, G, kModeDiff, nullptr, d_mask, 0, s, tiles); });
+            return launch(c, "hash", [&] { return launch_tile(tab, G, kModeDiff, nullptr, d_mask, 0, s, tiles, c->dev); });
         });
         if (st) return st;
         if (!finishes) {
@@ -1541,7 +1542,7 @@ int pcs_checkpoint(pcs_ctx *c, const pcs_buf *plan, uint32_t n, pcs_snap parent,
     hipStream_t s = c->stream;
     int st = with_tables(sg, [&](const auto &tab) {
         return launch(c, "incremental", [&] {
-            return launch_tile(tab, G, kModeDiff, d_nodes, d_mask, 0, s, tiles);
+            return launch_tile(tab, G, kModeDiff, d_nodes, d_mask, 0, s, tiles, c->dev);
         });
     });
     if (st) return st;

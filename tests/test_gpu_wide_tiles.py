@@ -1,6 +1,6 @@
 """GPU parity on both sides of the job sizes where fingerprint and diff
-tiles of argument-table jobs widen from 256 to 1024 lanes (fingerprints up
-to 1024 groups, incremental checkpoints up to 2048 groups): chunk
+tiles of argument-table jobs change between 256 and 1024 lanes (1024 up to two
+groups per CU and from three to four: 512, 768 and 1024 groups on 256 CUs): chunk
 fingerprints, buffer and session roots, the stored bytes of incremental
 checkpoints and their restores, against the oracle; and long Merkle lists, in
 argument tables (up to 96 buffers) and device tables (more)."""
@@ -29,7 +29,7 @@ def sizes_for(groups):
     return s
 
 
-@pytest.mark.parametrize("groups", [1024, 1025])
+@pytest.mark.parametrize("groups", [512, 513, 768, 769, 1024, 1025])
 def test_fingerprint_width_boundary(pcs, groups):
     rng = np.random.default_rng([41, groups])
     sizes = sizes_for(groups)
@@ -48,7 +48,7 @@ def test_fingerprint_width_boundary(pcs, groups):
         ctx.close()
 
 
-@pytest.mark.parametrize("groups", [2048, 2049])
+@pytest.mark.parametrize("groups", [512, 513, 768, 769, 1024, 1025, 2048, 2049])
 def test_incremental_width_boundary(pcs, groups):
     rng = np.random.default_rng([43, groups])
     sizes = sizes_for(groups)
