@@ -438,8 +438,11 @@ int pcs_bank_shrink(pcs_ctx *ctx, const pcs_bank_part *h_parts, uint32_t nparts,
  *                 (may be NULL).
  * The comparison and the count run on the device; the call then waits for
  * the context's stream (the result is a host value).  d_ref_hashes may be
- * NULL only when the buffers hold no chunks.  Takes arena scratch of 16 bytes
- * per 64-chunk group (PCS_E_NOMEM if it cannot).
+ * NULL only when the buffers hold no chunks.  A job of at most 128 groups of
+ * 64 chunks without an empty buffer, whose tables travel in the kernel
+ * arguments (as pcs_restore's), takes no arena space; another takes scratch
+ * of 16 bytes per group and space for the tables it stages (PCS_E_NOMEM if
+ * the arena cannot hold them).
  */
 int pcs_distance(pcs_ctx *ctx, const pcs_buf *h_bufs, uint32_t n, const uint64_t *d_ref_hashes,
                  uint64_t *h_differing, double *h_distance);

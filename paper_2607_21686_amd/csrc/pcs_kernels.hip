@@ -922,8 +922,8 @@ __device__ __forceinline__ void hash_tile(const Tab &tab, uint64_t *__restrict__
         // are not at stake.  One granule at a time, located anew each, took for
         // 2048 rings of 257 KiB, each with one such chunk, 193 us a
         // fingerprint, 261 a pack with fingerprint, 299 a restore (k_copy) and
-        // 268 a verified one; so 107, 210, 186 and 200 (without such chunks
-        // 99, 205, 180 and 192).
+        // 268 a verified one; so 108, 207, 186 and 197 (without such chunks
+        // 98, 206, 182 and 194).
         constexpr bool kAhead = T != 1024 || MODE == kModePack || MODE == kModeVerify;
         uint4 r[U];
         const auto load_slice = [&](uint32_t x) {
