@@ -2183,26 +2183,23 @@ __device__ __forceinline__ void place_group(const uint32_t (&k)[4], bool ok, uin
     }
 }
 
-// Exclusive prefix of x over the 1024 threads of a workgroup (ws: 33 words).
+// Exclusive prefix of x over the NT threads (at most 1024) of a workgroup (ws: a
+// word per wavefront): each wavefront scans the totals itself, behind one barrier.
+template <int NT>
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t *ws)
 {
-    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const uint32_t incl = wave_incl_scan(x);
     if (lane == 63) ws[wave] = incl;
     __syncthreads();
-    if (wave == 0) {
-        const uint32_t w = lane < 16 ? ws[lane] : 0;
-        const uint32_t wi = wave_incl_scan(w);
-        if (lane < 16) ws[16 + lane] = wi - w;
-    }
-    __syncthreads();
-    return incl - x + ws[16 + wave];
+    const uint32_t w = wave_incl_scan(ws[lane & (NT / 64 - 1)]);  // (lanes past the wavefronts: unused)
+    return incl - x + (wave ? lane_word(w, wave - 1) : 0);
 }
 
 // Selection of a bank of at most kSelectOneWorkgroupEntries scores in one
-// workgroup of 1024 lanes: the `keep` best-ranked entries (a smaller key, or
+// workgroup of NT lanes (256 up to 1024 scores, else 1024): the `keep` best-ranked entries (a smaller key, or
 // an equal key at a lower index, ranks first) in increasing index order.
-//   0. Sixteen ranges of a multiple of 64 whole groups, one per wavefront;
+//   0. A range of a multiple of 64 whole groups per wavefront;
 //      each lane holds its R groups of its wavefront's range (the smallest R
 //      of 1, 2, 4 and 8 that does), read once, all loads in flight.
 //      The single scores before and after the whole groups
@@ -2223,28 +2220,31 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t *ws)
 //   3. Each wavefront compacts its kept indices with ballots.
 // Larger banks take the multi-workgroup selection (k_sel_*), which follows
 // the same steps with a launch per pass.
-// Measured (us, up to 32768 scores): 5.2 at 512, 5.8 at 4096, 7.5 at 8192, 11.5
-// at 16384, 20 at 32768 (distinct scores; with every pass run, as many ties make
-// it, 5.7, 6.4, 8.4, 12.8 and 22); reading the scores anew in each of four 8-bit passes,
-// one load in flight, took 13 at 8192 and 38 at 32768.  At 65536 (16 groups a
-// lane) one workgroup takes 42, the five launches 40.
+// Measured (us a call, distinct scores / nearly all tied, so that every pass runs):
+// 4.2 / 4.9 at 512, 4.2 / 5.2 at 1024, 5.3 / 7.2 at 3000, 8.0 / 11.8 at 8000, 22 / 36 at
+// 30000.  Reading the scores anew in each of four 8-bit passes, one load in
+// flight, took 14 / 18 and 41 / 57 at the last two.  1024 lanes at 512 scores: 4.9
+// / 5.8, most of it barriers of sixteen wavefronts of which two hold scores, and
+// 4.9 / 5.2 with four passes of 8 bits.  At 65536 (16 groups a lane) one workgroup
+// takes 42, the five launches 40.
 constexpr uint32_t kSelectOneWorkgroupEntries = 32768;
 constexpr uint32_t kSelDigits = 2048;
-template <int R>
-__global__ __launch_bounds__(1024) void k_shrink_select(uint64_t scores, uint32_t n, uint32_t keep,
+template <int R, int NT>
+__global__ __launch_bounds__(NT) void k_shrink_select(uint64_t scores, uint32_t n, uint32_t keep,
                                                         uint32_t *__restrict__ kept)
 {
-    // Per range: keys below K* (cnt[r]) and equal to K* (cnt[18 + r]); range 0
-    // = the single scores before the whole groups, 1 + w = wavefront w's
-    // groups, 17 = the single scores after.
+    // Per range: keys below K* (cnt[r]) and equal to K* (cnt[kRanges + r]);
+    // range 0 = the single scores before the whole groups, 1 + w = wavefront
+    // w's groups, the last = the single scores after.
     constexpr int kSelCopies = R > 1 ? 2 : 1;
-    __shared__ uint32_t hist[kSelCopies][kSelDigits];
-    __shared__ uint32_t cnt[36];
-    __shared__ uint32_t ws[33];
+    constexpr uint32_t kWaves = NT / 64, kRanges = kWaves + 2, kPer = kSelDigits / NT;
+    __shared__ __attribute__((aligned(16))) uint32_t hist[kSelCopies][kSelDigits];
+    __shared__ uint32_t cnt[2 * kRanges];
+    __shared__ uint32_t ws[kWaves];
     __shared__ uint32_t pick[3];
     const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const SelView v = sel_view(scores, n);
-    const uint64_t nfull = v.gf1 - v.gf0, per = (nfull + 1023) / 1024 * 64;  // at most 64 R
+    const uint64_t nfull = v.gf1 - v.gf0, per = (nfull + NT - 1) / NT * 64;  // at most 64 R
     const uint64_t w0 = v.gf0 + umin(wave * per, nfull), w1 = v.gf0 + umin(wave * per + per, nfull);
     const SelSingle es = sel_single(v, scores, n, lane, wave == 0);
     uint32_t rk[R][4];
@@ -2260,14 +2260,16 @@ __global__ __launch_bounds__(1024) void k_shrink_select(uint64_t scores, uint32_
     uint32_t *const mine = hist[wave % kSelCopies];
 
     uint32_t prefix = 0, pmask = 0, need = keep;  // need: 1-based rank of K* among the candidates
+    // Thread t's buckets are kPer t .. kPer t + kPer - 1; it clears them for the
+    // next pass as it reads them.
+#pragma unroll
+    for (int c = 0; c < kSelCopies; ++c)
+#pragma unroll
+        for (uint32_t i = 0; i < kPer; ++i) hist[c][kPer * t + i] = 0;
+    __syncthreads();
 #pragma unroll 1
     for (int p = 0; p < 3; ++p) {
         const uint32_t shift = p == 0 ? 21 : p == 1 ? 10 : 0, digits = p == 2 ? kSelDigits / 2 : kSelDigits;
-#pragma unroll
-        for (int c = 0; c < kSelCopies; ++c)
-#pragma unroll
-            for (uint32_t i = 0; i < kSelDigits; i += 1024) hist[c][i + t] = 0;
-        __syncthreads();
 #pragma unroll
         for (int u = 0; u < R; ++u)
 #pragma unroll
@@ -2275,18 +2277,29 @@ __global__ __launch_bounds__(1024) void k_shrink_select(uint64_t scores, uint32_
                 if (rok[u] && (rk[u][j] & pmask) == prefix) atomicAdd(&mine[(rk[u][j] >> shift) & (digits - 1)], 1u);
         if (es.in && (ek & pmask) == prefix) atomicAdd(&mine[(ek >> shift) & (digits - 1)], 1u);
         __syncthreads();
-        uint32_t h0 = 0, h1 = 0;  // buckets 2t and 2t + 1
+        uint32_t h[kPer], sum = 0;
 #pragma unroll
-        for (int c = 0; c < kSelCopies; ++c) {
-            h0 += hist[c][2 * t];
-            h1 += hist[c][2 * t + 1];
-        }
-        const uint32_t before = block_excl_scan(h0 + h1, ws);
-        if (before < need && before + h0 + h1 >= need) {
-            const bool second = before + h0 < need;
-            pick[0] = 2 * t + (second ? 1 : 0);
-            pick[1] = need - before - (second ? h0 : 0);
-            pick[2] = second ? h1 : h0;
+        for (uint32_t i = 0; i < kPer; ++i) h[i] = 0;
+#pragma unroll
+        for (int c = 0; c < kSelCopies; ++c)
+#pragma unroll
+            for (uint32_t i = 0; i < kPer; ++i) {
+                h[i] += hist[c][kPer * t + i];
+                hist[c][kPer * t + i] = 0;
+            }
+#pragma unroll
+        for (uint32_t i = 0; i < kPer; ++i) sum += h[i];
+        uint32_t before = block_excl_scan<NT>(sum, ws);
+        if (before < need && before + sum >= need) {
+#pragma unroll
+            for (uint32_t i = 0; i < kPer; ++i) {
+                if (before < need && before + h[i] >= need) {
+                    pick[0] = kPer * t + i;
+                    pick[1] = need - before;
+                    pick[2] = h[i];
+                }
+                before += h[i];
+            }
         }
         __syncthreads();
         prefix |= pick[0] << shift;
@@ -2310,16 +2323,16 @@ __global__ __launch_bounds__(1024) void k_shrink_select(uint64_t scores, uint32_
         }
     if (lane == 0) {
         cnt[1 + wave] = lt;
-        cnt[19 + wave] = eq;
+        cnt[kRanges + 1 + wave] = eq;
     }
     if (wave == 0) {
         uint32_t c[4];
         count_singles(es, ek, prefix, c);
         if (lane == 0) {
             cnt[0] = c[0];
-            cnt[18] = c[1];
-            cnt[17] = c[2];
-            cnt[35] = c[3];
+            cnt[kRanges] = c[1];
+            cnt[kRanges - 1] = c[2];
+            cnt[2 * kRanges - 1] = c[3];
         }
     }
     __syncthreads();
@@ -2329,7 +2342,7 @@ __global__ __launch_bounds__(1024) void k_shrink_select(uint64_t scores, uint32_
     const auto range_start = [&](uint32_t r, uint32_t &pos, uint32_t &rank) {
         pos = rank = 0;
         for (uint32_t x = 0; x < r; ++x) {
-            const uint32_t e = cnt[18 + x];
+            const uint32_t e = cnt[kRanges + x];
             pos += cnt[x] + (need > rank ? min(need - rank, e) : 0u);
             rank += e;
         }
@@ -2337,7 +2350,7 @@ __global__ __launch_bounds__(1024) void k_shrink_select(uint64_t scores, uint32_
     if (wave == 0) {
         uint32_t ph, rh, pt, rt;
         range_start(0, ph, rh);
-        range_start(17, pt, rt);
+        range_start(kRanges - 1, pt, rt);
         place_singles(es, ek, prefix, need, ph, rh, pt, rt, kept);
     }
     uint32_t pos, rank;
@@ -2392,7 +2405,7 @@ __global__ __launch_bounds__(1024) void k_sel_hist(uint64_t scores, uint32_t n, 
     constexpr uint32_t kShift = P == 0 ? 24 : P == 1 ? 12 : 0;
     constexpr uint32_t kAbove = P == 0 ? 0 : P == 1 ? 0xFF000000u : 0xFFFFF000u;  // bits already known
     __shared__ uint32_t hist[kBuckets];
-    __shared__ uint32_t ws[33];
+    __shared__ uint32_t ws[16];
     __shared__ uint32_t flag;
     const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const SelView v = sel_view(scores, n);
@@ -2429,7 +2442,7 @@ __global__ __launch_bounds__(1024) void k_sel_hist(uint64_t scores, uint32_t n, 
         h[i] = t * kPer + i < kBuckets ? agent_load(&global[t * kPer + i]) : 0;
         sum += h[i];
     }
-    uint32_t cum = block_excl_scan(sum, ws);
+    uint32_t cum = block_excl_scan<1024>(sum, ws);
     if (cum < need && cum + sum >= need) {
         uint32_t i = 0;
 #pragma unroll
@@ -2459,7 +2472,7 @@ __global__ __launch_bounds__(1024) void k_sel_count(uint64_t scores, uint32_t n,
                                                     uint32_t *__restrict__ eq_out, uint32_t *__restrict__ pos_out,
                                                     uint32_t *__restrict__ rank_out)
 {
-    __shared__ uint32_t ws[33];
+    __shared__ uint32_t ws[16];
     __shared__ uint32_t flag;
     const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const SelView v = sel_view(scores, n);
@@ -2502,9 +2515,9 @@ __global__ __launch_bounds__(1024) void k_sel_count(uint64_t scores, uint32_t n,
         a += agent_load(&lt_out[r]);
         b += agent_load(&eq_out[r]);
     }
-    uint32_t LT = block_excl_scan(a, ws);
+    uint32_t LT = block_excl_scan<1024>(a, ws);
     __syncthreads();
-    uint32_t EQ = block_excl_scan(b, ws);
+    uint32_t EQ = block_excl_scan<1024>(b, ws);
     for (uint32_t r = s0; r < s1; ++r) {
         pos_out[r] = LT + min(need, EQ);
         rank_out[r] = EQ;
@@ -2909,10 +2922,11 @@ hipError_t launch_shrink_select(const float *scores, uint32_t n, uint32_t keep, 
     const uint64_t sc = (uint64_t)scores;
     if (n <= kSelectOneWorkgroupEntries) {
         // R groups of four scores a lane.
-        if (n <= 4096) run_kernel(k_shrink_select<1>, dim3(1), dim3(1024), s, sc, n, keep, kept);
-        else if (n <= 8192) run_kernel(k_shrink_select<2>, dim3(1), dim3(1024), s, sc, n, keep, kept);
-        else if (n <= 16384) run_kernel(k_shrink_select<4>, dim3(1), dim3(1024), s, sc, n, keep, kept);
-        else run_kernel(k_shrink_select<8>, dim3(1), dim3(1024), s, sc, n, keep, kept);
+        if (n <= 1024) run_kernel(k_shrink_select<1, 256>, dim3(1), dim3(256), s, sc, n, keep, kept);
+        else if (n <= 4096) run_kernel(k_shrink_select<1, 1024>, dim3(1), dim3(1024), s, sc, n, keep, kept);
+        else if (n <= 8192) run_kernel(k_shrink_select<2, 1024>, dim3(1), dim3(1024), s, sc, n, keep, kept);
+        else if (n <= 16384) run_kernel(k_shrink_select<4, 1024>, dim3(1), dim3(1024), s, sc, n, keep, kept);
+        else run_kernel(k_shrink_select<8, 1024>, dim3(1), dim3(1024), s, sc, n, keep, kept);
         return hipGetLastError();
     }
     if (!scratch || (scratch & 255) || !unit) return hipErrorInvalidValue;

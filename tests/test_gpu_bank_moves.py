@@ -89,10 +89,10 @@ def test_large_selection_buckets(pcs, n, kind):
     ctx.close()
 
 
-@pytest.mark.parametrize("n", [4095, 4097, 8192, 8193, 16384, 16385, 32767, 32768])
+@pytest.mark.parametrize("n", [3, 255, 257, 1023, 1024, 1025, 1027, 4095, 4097, 8192, 8193, 16384, 16385, 32767, 32768])
 def test_one_workgroup_selection(pcs, n):
-    """Both sides of the sizes where a lane holds 1, 2, 4 and 8 groups of
-    scores, at every alignment of the first one, with many ties."""
+    """Both sides of the sizes where the workgroup has 256 and 1024 lanes and a lane
+    holds 1, 2, 4 and 8 groups of scores, at every alignment of the first one, with many ties."""
     rng = np.random.default_rng(n)
     s = np.round(rng.standard_normal(n + 3) * 50).astype(np.float32)
     ctx = pcs.Context(arena(4 << 20))
@@ -108,7 +108,7 @@ def test_one_workgroup_selection(pcs, n):
 
 
 @pytest.mark.parametrize("low_bits", [0, 9, 20], ids=["ties", "10-bit buckets", "21-bit buckets"])
-@pytest.mark.parametrize("n", [1, 5, 512, 4097, 32768])
+@pytest.mark.parametrize("n", [1, 5, 512, 1024, 4097, 32768])
 def test_selection_of_whole_buckets(pcs, n, low_bits):
     """Runs of up to 32 scores that share every key bit above `low_bits`, so
     that a run is kept whole, all but one, or with one more: the search ends
