@@ -513,7 +513,9 @@ def _timed(args, ctx, step, kernels):
     third pass of the same steps with the timing events on, as each kernel
     dispatch's own begin and end (these kernels run for tens to hundreds of
     microseconds, so the few microseconds of dispatch latency that events
-    recorded around a launch would add are not small against them)."""
+    recorded around a launch would add are not small against them).  In that
+    third pass alone a small job's roots take a launch of their own ("merkle"),
+    which otherwise its fingerprint launch finishes."""
     import torch
     global _STEP_DIST
     for _ in range(args.warmup):
